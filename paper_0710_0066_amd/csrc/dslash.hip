@@ -12,6 +12,7 @@
 // and renumbered per XCD; with several rhs four of them share each link load.
 #include "internal.h"
 #include "site_io.h"
+#include "split.h"
 
 namespace sap {
 
@@ -143,7 +144,8 @@ __device__ __forceinline__ void load_link_raw(const typename vec2<R>::type* U, l
 
 // Work-item mappings (MAP):
 //  SITE  one work-item per (site, rhs); a workgroup holds 256 sites of one parity (half
-//        hop) or 128 sites of each parity (full operator), workgroups rhs-fastest.
+//        hop) or 128 sites of each parity (full operator). Only the rhs-slowest order with
+//        several rhs runs it here; the rhs-fastest order is the split kernel (split.hip).
 //  LANE4 a wavefront holds 16 sites x 4 rhs: the four lanes of a site read the same link
 //        address in the same load instruction, so the link is fetched once for 4 rhs; a
 //        workgroup holds 64 sites (half hop) or 32 sites of each parity (full).
@@ -1882,6 +1884,35 @@ template <class R> static void launch_slabd(const HopArgs<R>& A, hipStream_t st)
 
 void launch_slabd16(const HopArgs<h16>& A, hipStream_t st) { launch_slabd<h16>(A, st); }
 
+// Mapping of an untuned context (W = lattice sites times right-hand sides). Half hop, FP32 and
+// FP64: the split kernel in marching order up to W = 1.9e6, above it the LDS slabs where the
+// tile they choose keeps at most as many halo sites as tile sites and fills its wavefronts.
+// Measured (us, split / slab): FP32 24^3x48 1 rhs 30 / 39, 2 rhs 45 / 49, 3 rhs 62 / 60, 12 rhs
+// 309 / 256; FP64 2 rhs 123 / 145, 3 rhs 174 / 164, 12 rhs 656 / 564; 24x10x6x14 with 12 rhs,
+// where the slab tile is small, 10 / 15 and 20 / 27. FP16 (issue-bound: the split kernel only
+// pays while it adds wavefronts): half hop split up to 7e5, marching up to 4e6, then the LDS
+// slab (16^3x32 3 rhs 14 / 16 / 24 us for split / march1 / slabd, 8 rhs 31 / 27 / 26; 24^3x48
+// 2 rhs 39 / 36 / 47, 12 rhs 250 / 196 / 186). Full operator: marching (launch_march1; FP16 from
+// W = 4e5 on: 16^3x32 1 rhs 11.1 / 12.1 us for split / march1, 5 rhs 41 / 36).
+int hop_default_map(const Geo& g, bool full, int prec, int nrhs) {
+  const double W = 2.0 * g.Vh * nrhs;
+  if (prec == SAP_F16) {
+    if (W <= (full ? 4e5 : 7e5)) return HOP_MAP_SITE;
+    return full || W <= 4e6 ? HOP_MAP_MARCH1 : HOP_MAP_SLABD;
+  }
+  if (full || W <= 1.9e6) return HOP_MAP_MARCH1;
+  int TA, TB, S, H;
+  if (prec == SAP_F32) {
+    slabd_tile(g, kSlabdUnit, TA, TB, S, H);
+  } else {
+    slab_tile(g, std::min(512, std::max(g.L3h, 80 * 1024 / 384)), TA, TB);
+    S = TA * TB * g.L3h;
+    H = 2 * ((TA < g.L1 ? TB * g.L3h : 0) + (TB < g.L2 ? TA * g.L3h : 0));
+  }
+  const bool good = H <= S && 4 * S >= 3 * ((S + 63) / 64 * 64) && S >= 128;
+  return !good ? HOP_MAP_MARCH1 : prec == SAP_F32 ? HOP_MAP_SLABD : HOP_MAP_SLAB1W;
+}
+
 int slabd_norm_slots(const Geo& g, int nlb) {
   if (nlb <= 0 || g.L0 % nlb) return 0;
   int TA, TB, S, H;
@@ -1903,6 +1934,22 @@ template <class R> static void launch_stream(const HopArgs<R>& A, hipStream_t st
   hipLaunchKernelGGL((hop_stream_kernel<R, S>), dim3((unsigned)nwg), dim3(S), lds, st, A, T, nrange, nchunk);
 }
 
+// x0-marching with one rhs per work-item: the split kernel in that order, the
+// register-blocked body where the launch is bound by memory beyond the MALL. Measured (us,
+// register-blocked against split): apply_M FP64 on 24^3x48, 1 rhs 158 / 133, 2 rhs 248 / 241,
+// 3 rhs 338 / 352, 12 rhs 1253 / 1390; on 16^3x32, 5 rhs 102 / 87, 12 rhs 238 / 266; apply_M
+// FP32 on 24^3x48, 1 rhs 67 / 44, 3 rhs 173 / 164, 12 rhs 642 / 652: the split order wins
+// while the input stays within 200 MB (the MALL holds 256 MB); the FP32 half hop (24^3x48,
+// 12 rhs: 329 / 309) always, the FP64 one (16^3x32, 12 rhs: 117 / 99; 24^3x48, 12 rhs:
+// 625 / 655) up to twice that input. Slices of fewer than 16 chunks of 64 sites leave some
+// of the 8 XCDs idle or short in this order and run in the linear one.
+template <class R> static void launch_march1(const HopArgs<R>& A, hipStream_t st) {
+  const bool full = A.parity_out < 0, f32 = std::is_same<R, float>::value;
+  const double in = 2.0 * A.g.Vh * A.nrhs * 24 * sizeof(R);      // bytes of the whole input field
+  if ((!full && f32) || in <= (full ? 200e6 : 400e6)) launch_split<R>(A, A.g.V3h >= 16 * TILE, st);
+  else launch_march<R, 1>(A, st);
+}
+
 template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t st) {
   const bool full = A.parity_out < 0;
   if (A.map == HOP_MAP_STREAM && !full) {
@@ -1910,11 +1957,12 @@ template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t st) {
     return;
   }
   switch (A.map) {
-    case HOP_MAP_MARCH1: launch_march<R, 1>(A, st); return;
+    case HOP_MAP_SITE: launch_split<R>(A, false, st); return;
+    case HOP_MAP_MARCH1: launch_march1<R>(A, st); return;
     case HOP_MAP_MARCH2: launch_march<R, 2>(A, st); return;
     case HOP_MAP_MARCH4: launch_march<R, 4>(A, st); return;
     case HOP_MAP_WALK1:
-      if (full) launch_march<R, 1>(A, st);
+      if (full) launch_march1<R>(A, st);
       else launch_walk<R, 1>(A, st);
       return;
     case HOP_MAP_WALK2:
@@ -1922,15 +1970,15 @@ template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t st) {
       else launch_walk<R, 2>(A, st);
       return;
     case HOP_MAP_BAND1:
-      if (full) launch_march<R, 1>(A, st);
+      if (full) launch_march1<R>(A, st);
       else launch_band<R, 1>(A, st);
       return;
     case HOP_MAP_SLAB1:
-      if (full) launch_march<R, 1>(A, st);
+      if (full) launch_march1<R>(A, st);
       else launch_slab<R, 1>(A, st, 40 * 1024);
       return;
     case HOP_MAP_SLAB1W:
-      if (full) launch_march<R, 1>(A, st);
+      if (full) launch_march1<R>(A, st);
       else launch_slab<R, 1>(A, st, 80 * 1024);
       return;
     case HOP_MAP_SLAB2:
@@ -1938,7 +1986,7 @@ template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t st) {
       else launch_slab<R, 2>(A, st, 80 * 1024);
       return;
     case HOP_MAP_SLABD:
-      if (full) launch_march<R, 1>(A, st);
+      if (full) launch_march1<R>(A, st);
       else launch_slabd<R>(A, st);
       return;
     default: break;
@@ -1955,26 +2003,26 @@ template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t st) {
   int map = (A.map == HOP_MAP_STREAM || A.map >= HOP_MAP_REG2) ? HOP_MAP_SITE : A.map;
   const bool sweep = map >= HOP_SWEEP;
   if (sweep) map -= HOP_SWEEP;
-  if (A.nrhs == 1) map = HOP_MAP_SITE;                       // LANE4 / WAVE4 need several rhs
+  if (A.nrhs == 1 || (map == HOP_MAP_SITE && !sweep)) {      // the grouped and sweep orders need several rhs
+    launch_split<R>(A, false, st);
+    return;
+  }
   const bool grouped = map != HOP_MAP_SITE;
   const long long per = grouped ? (full ? 32 : 64) : (full ? 128 : 256);
   const long long groups = grouped ? (A.nrhs + 3) / 4 : A.nrhs;
   const long long chunks = (A.g.Vh + per - 1) / per;
   const dim3 grid((unsigned)round8(chunks * groups)), blk(256);
 #define SAP_HOP(F, M, SW) hipLaunchKernelGGL((hop_kernel<R, F, M, SW>), grid, blk, 0, st, A, chunks)
-#define SAP_HOP_MAPS(F, SW)                                                              \
+#define SAP_HOP_MAPS(F)                                                                  \
   do {                                                                                   \
-    if (map == HOP_MAP_LANE4) SAP_HOP(F, HOP_MAP_LANE4, SW);                             \
-    else if (map == HOP_MAP_WAVE4) SAP_HOP(F, HOP_MAP_WAVE4, SW);                        \
-    else SAP_HOP(F, HOP_MAP_SITE, SW);                                                   \
+    if (map == HOP_MAP_SITE) SAP_HOP(F, HOP_MAP_SITE, true);                             \
+    else if (map == HOP_MAP_LANE4 && sweep) SAP_HOP(F, HOP_MAP_LANE4, true);             \
+    else if (map == HOP_MAP_LANE4) SAP_HOP(F, HOP_MAP_LANE4, false);                     \
+    else if (sweep) SAP_HOP(F, HOP_MAP_WAVE4, true);                                     \
+    else SAP_HOP(F, HOP_MAP_WAVE4, false);                                               \
   } while (0)
-  if (full) {
-    if (sweep) SAP_HOP_MAPS(true, true);
-    else SAP_HOP_MAPS(true, false);
-  } else {
-    if (sweep) SAP_HOP_MAPS(false, true);
-    else SAP_HOP_MAPS(false, false);
-  }
+  if (full) SAP_HOP_MAPS(true);
+  else SAP_HOP_MAPS(false);
 #undef SAP_HOP_MAPS
 #undef SAP_HOP
 }

@@ -10,6 +10,7 @@
 // band maps, which exist for FP32/FP64 only, fall back to the marching order).
 #include "internal.h"
 #include "site_io.h"
+#include "split.h"
 
 namespace sap {
 
@@ -175,6 +176,13 @@ template <> void launch_hop<h16>(const HopArgs<h16>& A, hipStream_t st) {
     default: break;
   }
   const bool full = A.parity_out < 0;
+  // few wavefronts: the eight hops of a site on the eight wavefronts of a workgroup. Measured
+  // (us, split / site): half hop on 16^3x32, 1 rhs 6.6 / 7.2, 3 rhs 13.8 / 13.1, on
+  // 16x8^3, 1 rhs 3.9 / 6.7; full operator on 16^3x32, 1 rhs 11.1 / 11.2, 3 rhs 26.5 / 23.7
+  if (2.0 * A.g.Vh * A.nrhs <= (full ? 1.5e5 : 3e5)) {
+    launch_split<h16>(A, false, st);
+    return;
+  }
   const long long per = full ? 128 : 256;
   const long long chunks = (A.g.Vh + per - 1) / per;
   const long long n = chunks * A.nrhs;

@@ -106,7 +106,7 @@ void hop_sel(sap_ctx* c, double2* out, const double2* in, int colour, int outer,
   A.a = 1.0;
   A.b = -c->geom.kappa;
   A.g5_in = A.g5_out = 0;
-  A.map = HOP_MAP_SITE;
+  A.map = HOP_MAP_MARCH1;
   launch_hop<double>(A, s);
 }
 
@@ -223,7 +223,7 @@ int hop_odd(sap_ctx* c, double2* out, const double2* in, bool dag, hipStream_t s
   A.x = {nullptr, 0, 0};
   A.U = gauge_of<double>(c); A.g = c->g; A.nrhs = 1; A.parity_out = 1;
   A.lb = c->geom.l0_sub; A.slb = 0; A.colour = 0; A.block = -1;
-  A.a = 0.0; A.b = 1.0; A.g5_in = A.g5_out = dag ? 1 : 0; A.map = HOP_MAP_SITE;
+  A.a = 0.0; A.b = 1.0; A.g5_in = A.g5_out = dag ? 1 : 0; A.map = HOP_MAP_MARCH1;
   launch_hop<double>(A, s);
   return SAP_OK;
 }
@@ -241,7 +241,7 @@ int apply_weo(sap_ctx* c, double2* out, const double2* in, double rho, double2* 
   A.U = gauge_of<double>(c); A.g = c->g; A.nrhs = 1; A.parity_out = 0;
   A.lb = c->geom.l0_sub; A.slb = 0; A.colour = 0; A.block = -1;
   const double k = c->geom.kappa;
-  A.a = 1.0 + rho; A.b = -k * k; A.g5_in = A.g5_out = 0; A.map = HOP_MAP_SITE;
+  A.a = 1.0 + rho; A.b = -k * k; A.g5_in = A.g5_out = 0; A.map = HOP_MAP_MARCH1;
   launch_hop<double>(A, s);
   SAP_HIP_CHECK(c, hipGetLastError());
   return SAP_OK;
@@ -671,7 +671,7 @@ int hmc_trajectory(sap_ctx* c, double* U, const sap_hmc_params* P, sap_hmc_info*
   A.x = A.in;
   A.U = gauge_of<double>(c); A.g = c->g; A.nrhs = 1; A.parity_out = -1;
   A.lb = c->geom.l0; A.slb = c->geom.l0; A.colour = 0; A.block = -1;
-  A.a = 1.0; A.b = -c->geom.kappa; A.g5_in = A.g5_out = 0; A.map = HOP_MAP_SITE;
+  A.a = 1.0; A.b = -c->geom.kappa; A.g5_in = A.g5_out = 0; A.map = HOP_MAP_MARCH1;
   launch_hop<double>(A, s);
   if ((rc = sap_pack_spinor(c, w->f[0], P->xi2, 1, SAP_F64, stream))) return rc;
   if ((rc = heat_bath(c, chi, w->f[0], &P->action_solve, s))) goto fail;

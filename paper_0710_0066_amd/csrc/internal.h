@@ -75,7 +75,8 @@ template <class R> struct HopArgs {
 };
 
 // Work-item mappings of the hop kernel for several right-hand sides.
-enum { HOP_MAP_SITE = 0,    // one (site, rhs) per work-item, workgroups rhs-fastest
+enum { HOP_MAP_SITE = 0,    // split kernel: a site's eight hops on eight wavefronts (FP16: one
+                            // (site, rhs) per work-item on larger launches), rhs-fastest
        HOP_MAP_LANE4 = 1,   // wavefront = 16 sites x 4 rhs: four lanes share each link load
        HOP_MAP_WAVE4 = 2,   // workgroup = 64 sites x 4 rhs, one rhs per wavefront
        HOP_MAP_STREAM = 3,  // half hop only: x0-streaming, input slice staged in LDS
@@ -102,6 +103,8 @@ enum { HOP_MAP_SITE = 0,    // one (site, rhs) per work-item, workgroups rhs-fas
 constexpr int HOP_WALK_T = 8;   // slices per walk
 
 template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t s);
+// mapping of an untuned context for the full operator or the half hop (prec: sap_prec)
+int hop_default_map(const Geo& g, bool full, int prec, int nrhs);
 // partials per system of the norm the LDS-staged slab kernel (HOP_MAP_SLABD, FP32 even-odd
 // hop) can add to its output for systems of nlb slices
 int slabd_norm_slots(const Geo& g, int nlb);
@@ -166,12 +169,12 @@ template <class S> constexpr int prec_of() {
   return std::is_same<S, double>::value ? SAP_F64 : std::is_same<S, float>::value ? SAP_F32 : SAP_F16;
 }
 
-// mapping used for a hop launch: the tuned (or set) one, else SITE for one rhs and LANE4
-// for several (LANE4 is SITE for FP16 storage)
+// mapping used for a hop launch: the tuned (or set) one, else the rule on the lattice, the
+// precision and the number of rhs
 inline int hop_map_for(const sap_ctx* c, bool full, int prec, int nrhs) {
   const int m = c->hop_map[full ? 1 : 0][prec][nrhs > 64 ? 64 : nrhs];
   if (m >= 0) return m;
-  return nrhs <= 1 ? sap::HOP_MAP_SITE : sap::HOP_MAP_LANE4;
+  return sap::hop_default_map(c->g, full, prec, nrhs);
 }
 
 // error helpers (api.hip)
