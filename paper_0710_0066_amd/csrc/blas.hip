@@ -2,15 +2,27 @@
 //
 // A "system" is one (rhs, x0-block) pair: block b of length lb holds the sites
 // j in [b*Vb, (b+1)*Vb) of each parity, Vb = lb * V3h (lb = L0 for the full lattice).
-// Every kernel here runs on the grid (chunk, block, rhs) with CHUNK sites per workgroup,
-// so a workgroup never straddles two systems. Sums accumulate in FP64: per-thread
-// partials -> wavefront shuffle tree -> LDS across the 4 wavefronts -> one partial per
-// workgroup; the finalize kernels add the partials of a system in index order. The
-// result is bitwise reproducible run to run.
+// Every kernel here runs on the grid (chunk, block, rhs) with G.per sites per workgroup,
+// so a workgroup never straddles two systems. FP64 and FP32 kernels are six wavefronts,
+// each streaming one pair of components of 64 consecutive sites at a time (16-byte words);
+// FP16 kernels, which renormalise whole sites, take a site per work-item. Sums accumulate in
+// FP64: per-thread partials -> wavefront shuffle tree -> LDS across the wavefronts -> one
+// partial per workgroup.
+//
+// The scalars of an iteration (alpha, beta, omega, the convergence test) are formed by the
+// kernel that first needs them: every workgroup of a system adds the system's partials in
+// the same fixed order, and the first workgroup records the new state. This takes the
+// single-workgroup finalize kernels out of the iteration, in which one work-item added
+// up to hundreds of partials in sequence (4 to 11 us each on 16^3x32, of a 93 us CG iteration,
+// and a launch gap). Everything is bitwise reproducible run to run.
 #include "blas.h"
 #include "site_io.h"
 
 namespace sap {
+
+namespace {
+
+template <class R> constexpr int BT = is_h16<R> ? 256 : 384;   // work-items per workgroup
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -18,140 +30,303 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Sum over the 256 threads of a workgroup; valid in thread 0.
-__device__ __forceinline__ double block_sum(double v) {
-  __shared__ double sh[4];
-  v = wave_sum(v);
+// Sums of N values over the NT threads of a workgroup, valid in every thread. sh: N * NT / 64
+// doubles not in use by other threads.
+template <int NT, int N> __device__ __forceinline__ void block_sums(double v[N], double* sh) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0) sh[wid] = v;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const double t = wave_sum(v[k]);
+    if (lane == 0) sh[k * (NT / 64) + wid] = t;
+  }
   __syncthreads();
-  double r = 0.0;
-  if (threadIdx.x == 0) r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-  return r;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) t += sh[k * (NT / 64) + w];
+    v[k] = t;
+  }
+}
+
+// this thread's share of the N interleaved sums of a system's partials
+template <int NT, int N> __device__ __forceinline__ void thread_parts(Parts a, long long sys, double v[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = 0.0;
+  const double* q = a.p + sys * a.n * N;
+  for (int i = threadIdx.x; i < a.n; i += NT)
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] += q[i * N + k];
 }
 
 struct Tile {
   bool selected;
-  int rhs, blk;
+  int rhs, blk, p;
   long long j0, j1;   // site range of this workgroup within its parity
   long long sys;
+  long long part;     // index of this workgroup's partial
 };
 
-__device__ __forceinline__ Tile tile_of(const SysGrid& G) {
+// blockIdx = (chunk, block, rhs * npar + parity)
+__device__ __forceinline__ Tile tile_of(const SysGrid& G, int npar = 1) {
   Tile t;
-  t.rhs = blockIdx.z;
+  t.rhs = npar == 1 ? blockIdx.z : blockIdx.z / npar;
+  t.p = npar == 1 ? 0 : blockIdx.z - t.rhs * npar;
   t.blk = blockIdx.y;
   t.sys = (long long)t.rhs * G.nblk + t.blk;
   t.selected = block_selected(G.colour, t.blk);
-  t.j0 = (long long)t.blk * G.Vb + (long long)blockIdx.x * CHUNK;
+  t.j0 = (long long)t.blk * G.Vb + (long long)blockIdx.x * G.per;
   t.j1 = (long long)t.blk * G.Vb + G.Vb;
-  if (t.j0 + CHUNK < t.j1) t.j1 = t.j0 + CHUNK;
+  if (t.j0 + G.per < t.j1) t.j1 = t.j0 + G.per;
+  t.part = (t.sys * npar + t.p) * G.nchunk + blockIdx.x;
   return t;
 }
 
+// components 2w, 2w + 1 of site j (FP64, FP32)
 template <class R>
-__global__ __launch_bounds__(256) void k_norm2(SysGrid G, Field<R> a, int npar, double* part) {
-  const Tile t = tile_of(G);
-  double acc = 0.0;
-  if (t.selected) {
-    for (int p = 0; p < npar; ++p)
-      for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-        const SiteR<R> av = site_r(a, t.rhs, p, j, G.Vhp);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-          const cx<arith_t<R>> v = get(av, c);
-          acc += (double)v.r * v.r + (double)v.i * v.i;
-        }
-      }
+__device__ __forceinline__ void ld_pair(const Field<R>& f, int rhs, int p, long long j, int w, cx<R> v[2]) {
+  const typename vec2<R>::type* b = f.ptr + rhs * f.rs + p * f.ps + sidx<R>(j, 2 * w);
+  if constexpr (is_f32<R>) {
+    const f4v q = *(const f4v*)b;
+    v[0] = {q.x, q.y};
+    v[1] = {q.z, q.w};
+  } else {
+    v[0] = ld<R>(b);
+    v[1] = ld<R>(b + TILE);
   }
-  double s = block_sum(acc);
-  if (threadIdx.x == 0) part[t.sys * G.nchunk + blockIdx.x] = s;
+}
+template <class R>
+__device__ __forceinline__ void st_pair(const Field<R>& f, int rhs, int p, long long j, int w, const cx<R> v[2]) {
+  typename vec2<R>::type* b = f.ptr + rhs * f.rs + p * f.ps + sidx<R>(j, 2 * w);
+  if constexpr (is_f32<R>) {
+    *(f4v*)b = f4v{v[0].r, v[0].i, v[1].r, v[1].i};
+  } else {
+    st<R>(b, v[0]);
+    st<R>(b + TILE, v[1]);
+  }
 }
 
-// s -= alpha q ; partial ||s||^2
-template <class R>
-__global__ __launch_bounds__(256) void k_cg_s(SysGrid G, Field<R> s, Field<R> q, const double* alpha,
-                                              double* part) {
+// Streams the sites of a tile: fold() forms the scalars (it may synchronise; false: nothing
+// to do), op(in, out) maps the NIN components of the input fields to the NOUT of the output
+// fields. The first loads of a work-item are issued before fold, whose partial sums they
+// overlap with.
+template <class R, int NIN, int NOUT, class Fold, class Op>
+__device__ __forceinline__ void stream(const Tile& t, long long Vhp, const Field<R> (&in)[NIN],
+                                       const Field<R> (&out)[NOUT], Fold fold, Op op) {
   typedef arith_t<R> A;
-  const Tile t = tile_of(G);
-  double acc = 0.0;
-  if (t.selected) {
-    const A al = (A)alpha[t.sys];
-    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-      const SiteR<R> sr = site_r(s, t.rhs, 0, j, G.Vhp), qr = site_r(q, t.rhs, 0, j, G.Vhp);
-      SiteW<R> sw = site_w(s, t.rhs, 0, j, G.Vhp);
+  if constexpr (is_h16<R>) {
+    if (!fold()) return;
+    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += BT<R>) {
+      SiteR<R> r[NIN];
+      SiteW<R> w[NOUT];
+#pragma unroll
+      for (int k = 0; k < NIN; ++k) r[k] = site_r(in[k], t.rhs, t.p, j, Vhp);
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) w[k] = site_w(out[k], t.rhs, t.p, j, Vhp);
 #pragma unroll
       for (int c = 0; c < 12; ++c) {
-        cx<A> sv = get(sr, c);
-        const cx<A> qv = get(qr, c);
-        sv.r -= al * qv.r; sv.i -= al * qv.i;
-        put(sw, c, sv);
-        acc += (double)sv.r * sv.r + (double)sv.i * sv.i;
+        cx<A> v[NIN], o[NOUT];
+#pragma unroll
+        for (int k = 0; k < NIN; ++k) v[k] = get(r[k], c);
+        op(v, o);
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) put(w[k], c, o[k]);
       }
-      close(sw);
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) close(w[k]);
+    }
+  } else {
+    const int wv = threadIdx.x >> 6;
+    long long j = t.j0 + (threadIdx.x & 63);
+    cx<A> v[NIN][2];
+    if (j < t.j1)
+#pragma unroll
+      for (int k = 0; k < NIN; ++k) ld_pair<R>(in[k], t.rhs, t.p, j, wv, v[k]);
+    if (!fold()) return;
+    while (j < t.j1) {
+      cx<A> o[NOUT][2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        cx<A> vi[NIN], oi[NOUT];
+#pragma unroll
+        for (int k = 0; k < NIN; ++k) vi[k] = v[k][i];
+        op(vi, oi);
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) o[k][i] = oi[k];
+      }
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) st_pair<R>(out[k], t.rhs, t.p, j, wv, o[k]);
+      j += 64;
+      if (j < t.j1)
+#pragma unroll
+        for (int k = 0; k < NIN; ++k) ld_pair<R>(in[k], t.rhs, t.p, j, wv, v[k]);
     }
   }
-  double sm = block_sum(acc);
-  if (threadIdx.x == 0) part[t.sys * G.nchunk + blockIdx.x] = sm;
 }
 
-// x += alpha p ; p = r + beta p  (the solution update of an iteration, deferred to the
-// direction update so that p is read once)
-template <class R>
-__global__ __launch_bounds__(256) void k_cg_xp(SysGrid G, Field<R> x, Field<R> p, Field<R> r, const double* alpha,
-                                               const double* beta) {
+template <class A> __device__ __forceinline__ double abs2(cx<A> v) {
+  return (double)v.r * v.r + (double)v.i * v.i;
+}
+
+// reads the components of a tile of NIN fields into op(in)
+template <class R, int NIN, class Op>
+__device__ __forceinline__ void scan(const Tile& t, long long Vhp, const Field<R> (&in)[NIN], Op op) {
   typedef arith_t<R> A;
-  const Tile t = tile_of(G);
-  if (!t.selected) return;
-  const A al = (A)alpha[t.sys], be = (A)beta[t.sys];
-  for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-    const SiteR<R> xr = site_r(x, t.rhs, 0, j, G.Vhp), pr = site_r(p, t.rhs, 0, j, G.Vhp);
-    const SiteR<R> rr = site_r(r, t.rhs, 0, j, G.Vhp);
-    SiteW<R> xw = site_w(x, t.rhs, 0, j, G.Vhp), pw = site_w(p, t.rhs, 0, j, G.Vhp);
+  if constexpr (is_h16<R>) {
+    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += BT<R>) {
+      SiteR<R> r[NIN];
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      cx<A> xv = get(xr, c), pv = get(pr, c);
-      const cx<A> rv = get(rr, c);
-      xv.r += al * pv.r; xv.i += al * pv.i;
-      pv.r = rv.r + be * pv.r;
-      pv.i = rv.i + be * pv.i;
-      put(xw, c, xv);
-      put(pw, c, pv);
+      for (int k = 0; k < NIN; ++k) r[k] = site_r(in[k], t.rhs, t.p, j, Vhp);
+#pragma unroll
+      for (int c = 0; c < 12; ++c) {
+        cx<A> v[NIN];
+#pragma unroll
+        for (int k = 0; k < NIN; ++k) v[k] = get(r[k], c);
+        op(v);
+      }
     }
-    close(xw);
-    close(pw);
+  } else {
+    const int wv = threadIdx.x >> 6;
+    for (long long j = t.j0 + (threadIdx.x & 63); j < t.j1; j += 64) {
+      cx<A> v[NIN][2];
+#pragma unroll
+      for (int k = 0; k < NIN; ++k) ld_pair<R>(in[k], t.rhs, t.p, j, wv, v[k]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        cx<A> vi[NIN];
+#pragma unroll
+        for (int k = 0; k < NIN; ++k) vi[k] = v[k][i];
+        op(vi);
+      }
+    }
   }
 }
+
+template <class R>
+__global__ __launch_bounds__(BT<R>) void k_norm2(SysGrid G, Field<R> a, int npar, double* part) {
+  __shared__ double sh[BT<R> / 64];
+  const Tile t = tile_of(G, npar);
+  double acc[1] = {0.0};
+  if (t.selected) scan<R, 1>(t, G.Vhp, {a}, [&](const cx<arith_t<R>>* v) { acc[0] += abs2(v[0]); });
+  block_sums<BT<R>, 1>(acc, sh);
+  if (threadIdx.x == 0) part[t.part] = acc[0];
+}
+
+// ---- CG ---------------------------------------------------------------------------------
+
+template <class R>
+__global__ __launch_bounds__(BT<R>) void k_cg_s(SysGrid G, Field<R> s, Field<R> q, SysScal S, int v, Parts qq,
+                                               double* part) {
+  typedef arith_t<R> A;
+  __shared__ double sh[2][BT<R> / 64];
+  const Tile t = tile_of(G);
+  if (!t.selected || !S.active[v * S.nsys + t.sys]) return;      // whole workgroup
+  double acc[1] = {0.0};
+  A al = A(0);
+  stream<R, 2, 1>(
+      t, G.Vhp, {s, q}, {s},
+      [&] {
+        double n[1];
+        thread_parts<BT<R>, 1>(qq, t.sys, n);
+        block_sums<BT<R>, 1>(n, sh[0]);
+        const double a = n[0] > 0.0 ? S.gam[v * S.nsys + t.sys] / n[0] : 0.0;
+        al = (A)a;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+          S.alpha[t.sys] = a;
+          if (!isfinite(n[0])) S.flags[0] = 2;
+        }
+        return true;
+      },
+      [&](const cx<A>* in, cx<A>* out) {
+        out[0] = {in[0].r - al * in[1].r, in[0].i - al * in[1].i};
+        acc[0] += abs2(out[0]);
+      });
+  block_sums<BT<R>, 1>(acc, sh[1]);
+  if (threadIdx.x == 0) part[t.part] = acc[0];
+}
+
+template <class R>
+__global__ __launch_bounds__(BT<R>) void k_cg_xp(SysGrid G, Field<R> x, Field<R> p, Field<R> r, SysScal S, int v,
+                                                Parts pss, Parts prr) {
+  typedef arith_t<R> A;
+  __shared__ double sh[2 * (BT<R> / 64)];
+  const Tile t = tile_of(G);
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  const long long o = v * S.nsys + t.sys, n = (1 - v) * S.nsys + t.sys;
+  const double gam = S.gam[o];
+  if (!t.selected || !S.active[o]) {                             // whole workgroup
+    if (first) {
+      S.gam[n] = gam;
+      S.active[n] = 0;
+    }
+    return;
+  }
+  A al = (A)S.alpha[t.sys], be = A(0);
+  stream<R, 3, 2>(
+      t, G.Vhp, {x, p, r}, {x, p},
+      [&] {
+        double m[2];
+        thread_parts<BT<R>, 1>(pss, t.sys, m);
+        thread_parts<BT<R>, 1>(prr, t.sys, m + 1);
+        block_sums<BT<R>, 2>(m, sh);
+        be = (A)(gam > 0.0 ? m[1] / gam : 0.0);
+        if (first) {
+          if (!(isfinite(m[0]) && isfinite(m[1]))) S.flags[0] = 3;
+          S.iters[t.sys] += 1;
+          S.ss[t.sys] = m[0];
+          S.gam[n] = m[1];
+          S.active[n] = !(m[0] <= S.target2[t.sys] || m[1] == 0.0);
+        }
+        return true;
+      },
+      [&](const cx<A>* in, cx<A>* out) {
+        out[0] = {in[0].r + al * in[1].r, in[0].i + al * in[1].i};
+        out[1] = {in[2].r + be * in[1].r, in[2].i + be * in[1].i};
+      });
+}
+
+// ---- precision changes and residuals ------------------------------------------------------
 
 // out = src (both parities if npar == 2), converting precision
-template <class Ro, class Ri>
-__global__ __launch_bounds__(256) void k_convert(SysGrid G, Field<Ro> out, Field<Ri> in, int npar) {
+template <class Ro>
+__global__ __launch_bounds__(BT<Ro>) void k_convert(SysGrid G, Field<Ro> out, Field<double> in, int npar) {
   typedef arith_t<Ro> Ao;
-  const Tile t = tile_of(G);
-  for (int p = 0; p < npar; ++p)
-    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-      const SiteR<Ri> ir = site_r(in, t.rhs, p, j, G.Vhp);
-      SiteW<Ro> ow = site_w(out, t.rhs, p, j, G.Vhp);
+  const Tile t = tile_of(G, npar);
+  if constexpr (is_h16<Ro>) {
+    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += BT<Ro>) {
+      const SiteR<double> ir = site_r(in, t.rhs, t.p, j, G.Vhp);
+      SiteW<Ro> ow = site_w(out, t.rhs, t.p, j, G.Vhp);
 #pragma unroll
       for (int c = 0; c < 12; ++c) {
-        const cx<arith_t<Ri>> v = get(ir, c);
+        const cx<double> v = get(ir, c);
         cx<Ao> w = {(Ao)v.r, (Ao)v.i};
         if (!t.selected) w = {Ao(0), Ao(0)};
         put(ow, c, w);
       }
       close(ow);
     }
+  } else {
+    const int wv = threadIdx.x >> 6;
+    for (long long j = t.j0 + (threadIdx.x & 63); j < t.j1; j += 64) {
+      cx<double> v[2];
+      cx<Ro> w[2];
+      ld_pair<double>(in, t.rhs, t.p, j, wv, v);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) w[i] = t.selected ? cx<Ro>{(Ro)v[i].r, (Ro)v[i].i} : cx<Ro>{Ro(0), Ro(0)};
+      st_pair<Ro>(out, t.rhs, t.p, j, wv, w);
+    }
+  }
 }
 
 // x64 += e (both parities), e at the inner precision
 template <class R>
-__global__ __launch_bounds__(256) void k_add_mixed(SysGrid G, Field<double> x, Field<R> e) {
-  const Tile t = tile_of(G);
+__global__ __launch_bounds__(BT<R>) void k_add_mixed(SysGrid G, Field<double> x, Field<R> e) {
+  const Tile t = tile_of(G, 2);
   if (!t.selected) return;
-  for (int p = 0; p < 2; ++p) {
-    double2* xb = x.ptr + t.rhs * x.rs + p * x.ps;
-    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-      const SiteR<R> er = site_r(e, t.rhs, p, j, G.Vhp);
+  if constexpr (is_h16<R>) {
+    double2* xb = x.ptr + t.rhs * x.rs + t.p * x.ps;
+    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += BT<R>) {
+      const SiteR<R> er = site_r(e, t.rhs, t.p, j, G.Vhp);
 #pragma unroll
       for (int c = 0; c < 12; ++c) {
         const long long o = tiled(j, c, 12);
@@ -162,526 +337,529 @@ __global__ __launch_bounds__(256) void k_add_mixed(SysGrid G, Field<double> x, F
         st<double>(xb + o, xv);
       }
     }
+  } else {
+    const int wv = threadIdx.x >> 6;
+    for (long long j = t.j0 + (threadIdx.x & 63); j < t.j1; j += 64) {
+      cx<double> v[2];
+      cx<R> w[2];
+      ld_pair<double>(x, t.rhs, t.p, j, wv, v);
+      ld_pair<R>(e, t.rhs, t.p, j, wv, w);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) v[i] = {v[i].r + (double)w[i].r, v[i].i + (double)w[i].i};
+      st_pair<double>(x, t.rhs, t.p, j, wv, v);
+    }
   }
 }
 
 // r = b - Ax (FP64, the first npar parities: 2 both, 1 even only), partial ||r||^2
-__global__ __launch_bounds__(256) void k_resid(SysGrid G, Field<double> r, Field<double> b,
-                                               Field<double> Ax, double* part, int npar) {
-  const Tile t = tile_of(G);
-  double acc = 0.0;
-  for (int p = 0; p < npar; ++p) {
-    double2* rb = r.ptr + t.rhs * r.rs + p * r.ps;
-    const double2* bb = b.ptr + t.rhs * b.rs + p * b.ps;
-    const double2* ab = Ax.ptr + t.rhs * Ax.rs + p * Ax.ps;
-    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256)
+__global__ __launch_bounds__(BT<double>) void k_resid(SysGrid G, Field<double> r, Field<double> b,
+                                                     Field<double> Ax, double* part, int npar) {
+  __shared__ double sh[BT<double> / 64];
+  const Tile t = tile_of(G, npar);
+  double acc[1] = {0.0};
+  const bool sel = t.selected;
+  stream<double, 2, 1>(t, G.Vhp, {b, Ax}, {r}, [] { return true; },
+                       [&](const cx<double>* in, cx<double>* out) {
+                         out[0] = sel ? in[0] - in[1] : cx<double>{0.0, 0.0};
+                         acc[0] += abs2(out[0]);
+                       });
+  block_sums<BT<double>, 1>(acc, sh);
+  if (threadIdx.x == 0) part[t.part] = acc[0];
+}
+
+// ---- sums of partials outside the iterations: one workgroup, a wavefront per system ---------
+constexpr int FT = 1024;
+
+template <int N> __device__ __forceinline__ void wave_parts(Parts a, long long sys, double v[N]) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        const long long o = tiled(j, c, 12);
-        cx<double> bv = ld<double>(bb + o), av = ld<double>(ab + o);
-        cx<double> rv = t.selected ? bv - av : cx<double>{0.0, 0.0};
-        st<double>(rb + o, rv);
-        acc += rv.r * rv.r + rv.i * rv.i;
-      }
+  for (int k = 0; k < N; ++k) v[k] = 0.0;
+  const double* q = a.p + sys * a.n * N;
+  for (int i = lane; i < a.n; i += 64)
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] += q[i * N + k];
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
+}
+
+// f(sys) by lane 0 of a wavefront for every system, after the N sums of its partials
+template <int N, class F> __device__ __forceinline__ void each_system(int nsys, Parts a, F f) {
+  for (int s = threadIdx.x >> 6; s < nsys; s += FT / 64) {
+    double v[N];
+    wave_parts<N>(a, s, v);
+    if ((threadIdx.x & 63) == 0) f(s, v);
   }
-  double sm = block_sum(acc);
-  if (threadIdx.x == 0) part[t.sys * G.nchunk + blockIdx.x] = sm;
 }
 
-// out[sys] = sum of the partials of sys, in chunk order
-__device__ __forceinline__ double sys_total(const double* part, long long sys, int nchunk) {
-  double s = 0.0;
-  for (int c = 0; c < nchunk; ++c) s += part[sys * nchunk + c];
-  return s;
+__global__ __launch_bounds__(FT) void k_fin_sum(int nsys, Parts a, double* out) {
+  each_system<1>(nsys, a, [&](int s, const double* v) { out[s] = v[0]; });
 }
 
-__global__ void k_fin_sum(int nsys, int nchunk, const double* part, double* out) {
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) out[s] = sys_total(part, s, nchunk);
+__global__ __launch_bounds__(FT) void k_fin_sum3(int nsys, Parts a, double* out) {
+  each_system<3>(nsys, a, [&](int s, const double* v) {
+    for (int k = 0; k < 3; ++k) out[3 * s + k] = v[k];
+  });
 }
 
-// Start of an inner CG: bb = ||b_hat||^2 (part_b), gam = ||r||^2 (part_r);
-// the system is active unless unselected or already below its target.
-__global__ void k_fin_init(SysScal S, int nsys, int nchunk, const double* part_b, const double* part_r,
-                           const int* selected, const double* target2) {
+__global__ __launch_bounds__(FT) void k_targets(int nsys, Parts bh, const double* bnorm2, double inner2, double abs2,
+                                               double* target2) {
+  each_system<1>(nsys, bh, [&](int s, const double* v) { target2[s] = fmax(inner2 * v[0], abs2 * bnorm2[s]); });
+}
+
+// sums of up to 256 neighbouring partials (nv values each): grid (groups, systems)
+__global__ __launch_bounds__(256) void k_compress(int nv, Parts a, double* out) {
+  __shared__ double sh[4];
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  for (int k = 0; k < nv; ++k) {
+    double v[1] = {i < a.n ? a.p[((long long)blockIdx.y * a.n + i) * nv + k] : 0.0};
+    block_sums<256, 1>(v, sh);
+    if (threadIdx.x == 0) out[((long long)blockIdx.y * gridDim.x + blockIdx.x) * nv + k] = v[0];
+    __syncthreads();
+  }
+}
+
+// Start of an inner CG: ||b_hat||^2, gam = ||r||^2; the system is active unless unselected
+// or already below its target.
+__global__ __launch_bounds__(FT) void k_fin_init(SysScal S, Parts b, Parts r) {
   __shared__ int cnt;
   if (threadIdx.x == 0) cnt = 0;
   __syncthreads();
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
-    const double bb = sys_total(part_b, s, nchunk);
-    const double gm = sys_total(part_r, s, nchunk);
-    S.ss[s] = bb;
+  each_system<1>(S.nsys, b, [&](int s, const double* v) { S.ss[s] = v[0]; });
+  __syncthreads();
+  each_system<1>(S.nsys, r, [&](int s, const double* v) {
+    const double bb = S.ss[s], gm = v[0];
     S.gam[s] = gm;
     S.alpha[s] = 0.0;
-    S.beta[s] = 0.0;
-    const int act = selected[s] && bb > target2[s] && gm > 0.0;
+    const int act = S.selected[s] && bb > S.target2[s] && gm > 0.0;
     S.active[s] = act;
     if (!(isfinite(bb) && isfinite(gm))) S.flags[0] = 1;
     if (act) atomicAdd(&cnt, 1);
-  }
+  });
   __syncthreads();
   if (threadIdx.x == 0) S.flags[1] = cnt;
 }
 
-__global__ void k_fin_alpha(SysScal S, int nsys, int nchunk, const double* part_q) {
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
-    const double qq = sys_total(part_q, s, nchunk);
-    if (!isfinite(qq)) S.flags[0] = 2;
-    S.alpha[s] = (S.active[s] && qq > 0.0) ? S.gam[s] / qq : 0.0;
-  }
+__global__ __launch_bounds__(256) void k_fin_count(SysScal S, int v) {
+  __shared__ double sh[4];
+  double n[1] = {0.0};
+  for (int s = threadIdx.x; s < S.nsys; s += 256) n[0] += S.active[v * S.nsys + s] ? 1.0 : 0.0;
+  block_sums<256, 1>(n, sh);
+  if (threadIdx.x == 0) S.flags[1] = (int)n[0];
 }
 
-__global__ void k_fin_beta(SysScal S, int nsys, int nchunk, const double* part_s, int nchunk_r,
-                           const double* part_r, const double* target2) {
-  __shared__ int cnt;
-  if (threadIdx.x == 0) cnt = 0;
-  __syncthreads();
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
-    const double ss = sys_total(part_s, s, nchunk);
-    const double gm = sys_total(part_r, s, nchunk_r);
-    if (!(isfinite(ss) && isfinite(gm))) S.flags[0] = 3;
-    int act = S.active[s];
-    if (act) {
-      S.iters[s] += 1;
-      S.ss[s] = ss;
-      S.beta[s] = S.gam[s] > 0.0 ? gm / S.gam[s] : 0.0;
-      S.gam[s] = gm;
-      if (ss <= target2[s] || gm == 0.0) act = 0;
-    } else {
-      S.beta[s] = 0.0;
-    }
-    S.active[s] = act;
-    if (act) atomicAdd(&cnt, 1);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) S.flags[1] = cnt;
-}
+// ---- BiCGstab -------------------------------------------------------------------------------
 
-// ---- BiCGstab and geometric series ---------------------------------------------------
-
-// three sums over the 256 threads of a workgroup, written by thread 0 to out[0..2]
-__device__ __forceinline__ void block_sum3(double a, double b, double c, double* out) {
-  __shared__ double sh[3][4];
-  a = wave_sum(a);
-  b = wave_sum(b);
-  c = wave_sum(c);
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0) {
-    sh[0][wid] = a;
-    sh[1][wid] = b;
-    sh[2][wid] = c;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0)
-    for (int k = 0; k < 3; ++k) out[k] = (sh[k][0] + sh[k][1]) + (sh[k][2] + sh[k][3]);
+struct Cs {
+  cx<double> rho, alpha, omega, beta;
+};
+__device__ __forceinline__ Cs cs_get(const SysScal& S, int v, long long sys) {
+  const double* c = S.cs + 8 * (v * (long long)S.nsys + sys);
+  return {{c[0], c[1]}, {c[2], c[3]}, {c[4], c[5]}, {c[6], c[7]}};
 }
-
-__device__ __forceinline__ cx<double> cs_get(const double* cs, long long sys, int k) {
-  return {cs[8 * sys + 2 * k], cs[8 * sys + 2 * k + 1]};
-}
-__device__ __forceinline__ void cs_set(double* cs, long long sys, int k, cx<double> v) {
-  cs[8 * sys + 2 * k] = v.r;
-  cs[8 * sys + 2 * k + 1] = v.i;
+__device__ __forceinline__ void cs_set(const SysScal& S, int v, long long sys, const Cs& a) {
+  double* c = S.cs + 8 * (v * (long long)S.nsys + sys);
+  c[0] = a.rho.r; c[1] = a.rho.i; c[2] = a.alpha.r; c[3] = a.alpha.i;
+  c[4] = a.omega.r; c[5] = a.omega.i; c[6] = a.beta.r; c[7] = a.beta.i;
 }
 __device__ __forceinline__ cx<double> cdiv(cx<double> a, cx<double> b) {
   const double d = b.r * b.r + b.i * b.i;
   return {(a.r * b.r + a.i * b.i) / d, (a.i * b.r - a.r * b.i) / d};
 }
-enum { CS_RHO = 0, CS_ALPHA = 1, CS_OMEGA = 2, CS_BETA = 3 };
 
 template <class R>
-__global__ __launch_bounds__(256) void k_cdot3(SysGrid G, Field<R> a, Field<R> b, Field<R> c, double* part) {
+__global__ __launch_bounds__(BT<R>) void k_cdot3(SysGrid G, Field<R> a, Field<R> b, Field<R> c, double* part) {
   typedef arith_t<R> A;
+  __shared__ double sh[3 * (BT<R> / 64)];
   const Tile t = tile_of(G);
-  double sr = 0.0, si = 0.0, sc = 0.0;
+  double s[3] = {0.0, 0.0, 0.0};
+  auto dot = [&](const cx<A>& u, const cx<A>& v) {
+    s[0] += (double)u.r * v.r + (double)u.i * v.i;
+    s[1] += (double)u.r * v.i - (double)u.i * v.r;
+  };
   if (t.selected) {
-    const bool with_c = c.ptr != nullptr;
-    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-      const SiteR<R> ar = site_r(a, t.rhs, 0, j, G.Vhp), br = site_r(b, t.rhs, 0, j, G.Vhp);
-      SiteR<R> cr;
-      if (with_c) cr = site_r(c, t.rhs, 0, j, G.Vhp);
-#pragma unroll
-      for (int k = 0; k < 12; ++k) {
-        const cx<A> av = get(ar, k), bv = get(br, k);
-        sr += (double)av.r * bv.r + (double)av.i * bv.i;
-        si += (double)av.r * bv.i - (double)av.i * bv.r;
-        if (with_c) {
-          const cx<A> cv = get(cr, k);
-          sc += (double)cv.r * cv.r + (double)cv.i * cv.i;
-        }
-      }
-    }
+    if (c.ptr == nullptr)
+      scan<R, 2>(t, G.Vhp, {a, b}, [&](const cx<A>* v) { dot(v[0], v[1]); });
+    else if (c.ptr == a.ptr)
+      scan<R, 2>(t, G.Vhp, {a, b}, [&](const cx<A>* v) { dot(v[0], v[1]); s[2] += abs2(v[0]); });
+    else
+      scan<R, 3>(t, G.Vhp, {a, b, c}, [&](const cx<A>* v) { dot(v[0], v[1]); s[2] += abs2(v[2]); });
   }
-  block_sum3(sr, si, sc, part + 3 * (t.sys * G.nchunk + blockIdx.x));
+  block_sums<BT<R>, 3>(s, sh);
+  if (threadIdx.x < 3) part[3 * t.part + threadIdx.x] = s[threadIdx.x];
 }
 
-template <class R>
-__global__ __launch_bounds__(256) void k_bicg_p(SysGrid G, Field<R> p, Field<R> r, Field<R> v, const double* cs) {
-  typedef arith_t<R> A;
-  const Tile t = tile_of(G);
-  if (!t.selected) return;
-  const cx<double> be = cs_get(cs, t.sys, CS_BETA), om = cs_get(cs, t.sys, CS_OMEGA);
-  const cx<A> b = {(A)be.r, (A)be.i}, w = {(A)om.r, (A)om.i};
-  for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-    const SiteR<R> pr = site_r(p, t.rhs, 0, j, G.Vhp), rr = site_r(r, t.rhs, 0, j, G.Vhp);
-    const SiteR<R> vr = site_r(v, t.rhs, 0, j, G.Vhp);
-    SiteW<R> pw = site_w(p, t.rhs, 0, j, G.Vhp);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) {
-      const cx<A> d = get(pr, k) - cmul(w, get(vr, k));
-      put(pw, k, get(rr, k) + cmul(b, d));
-    }
-    close(pw);
+// Close an iteration: rho_new = <r0, r>, stop on ||r||^2 <= target2, beta = (rho_new / rho)
+// (alpha / omega). A breakdown (|<r0, r>|^2 <= 1e-24 ||r0||^2 ||r||^2, a zero rho or omega, or
+// ||r|| > 1e6 ||r0||, beyond which FP32 iterates would overflow) stops the system, which the
+// defect-correction loop then restarts from its current solution.
+__device__ __forceinline__ bool rho_step(const double m[3], bool act, double gam, double target2, Cs& c) {
+  const cx<double> rn = {m[0], m[1]};
+  const double rr = m[2];
+  act = act && rr > target2;
+  const double rho2 = c.rho.r * c.rho.r + c.rho.i * c.rho.i, om2 = c.omega.r * c.omega.r + c.omega.i * c.omega.i;
+  const double rn2 = rn.r * rn.r + rn.i * rn.i;
+  if (act && (rho2 == 0.0 || om2 == 0.0 || !(rn2 > 1e-24 * gam * rr) || rr > 1e12 * gam)) act = false;
+  if (act) {
+    c.beta = cmul(cdiv(rn, c.rho), cdiv(c.alpha, c.omega));
+    c.rho = rn;
+  } else {
+    c.beta = c.alpha = c.omega = {0.0, 0.0};
   }
+  return act;
 }
 
-template <class R>
-__global__ __launch_bounds__(256) void k_bicg_s(SysGrid G, Field<R> r, Field<R> v, const double* cs, double* part) {
-  typedef arith_t<R> A;
-  const Tile t = tile_of(G);
-  double acc = 0.0;
-  if (t.selected) {
-    const cx<double> al = cs_get(cs, t.sys, CS_ALPHA);
-    const cx<A> a = {(A)al.r, (A)al.i};
-    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-      const SiteR<R> rr = site_r(r, t.rhs, 0, j, G.Vhp), vr = site_r(v, t.rhs, 0, j, G.Vhp);
-      SiteW<R> rw = site_w(r, t.rhs, 0, j, G.Vhp);
-#pragma unroll
-      for (int k = 0; k < 12; ++k) {
-        const cx<A> sv = get(rr, k) - cmul(a, get(vr, k));
-        put(rw, k, sv);
-        acc += (double)sv.r * sv.r + (double)sv.i * sv.i;
-      }
-      close(rw);
-    }
-  }
-  const double sm = block_sum(acc);
-  if (threadIdx.x == 0) part[t.sys * G.nchunk + blockIdx.x] = sm;
-}
-
-template <class R>
-__global__ __launch_bounds__(256) void k_bicg_xr(SysGrid G, Field<R> x, Field<R> p, Field<R> r, Field<R> tt,
-                                                 Field<R> r0, const double* cs, double* part) {
-  typedef arith_t<R> A;
-  const Tile t = tile_of(G);
-  double sr = 0.0, si = 0.0, sc = 0.0;
-  if (t.selected) {
-    const cx<double> al = cs_get(cs, t.sys, CS_ALPHA), om = cs_get(cs, t.sys, CS_OMEGA);
-    const cx<A> a = {(A)al.r, (A)al.i}, w = {(A)om.r, (A)om.i};
-    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-      const SiteR<R> xr = site_r(x, t.rhs, 0, j, G.Vhp), pr = site_r(p, t.rhs, 0, j, G.Vhp);
-      const SiteR<R> rr = site_r(r, t.rhs, 0, j, G.Vhp), tr = site_r(tt, t.rhs, 0, j, G.Vhp);
-      const SiteR<R> qr = site_r(r0, t.rhs, 0, j, G.Vhp);
-      SiteW<R> xw = site_w(x, t.rhs, 0, j, G.Vhp), rw = site_w(r, t.rhs, 0, j, G.Vhp);
-#pragma unroll
-      for (int k = 0; k < 12; ++k) {
-        const cx<A> sv = get(rr, k), tv = get(tr, k);
-        put(xw, k, get(xr, k) + cmul(a, get(pr, k)) + cmul(w, sv));
-        const cx<A> rn = sv - cmul(w, tv);
-        put(rw, k, rn);
-        const cx<A> q = get(qr, k);
-        sr += (double)q.r * rn.r + (double)q.i * rn.i;
-        si += (double)q.r * rn.i - (double)q.i * rn.r;
-        sc += (double)rn.r * rn.r + (double)rn.i * rn.i;
-      }
-      close(xw);
-      close(rw);
-    }
-  }
-  block_sum3(sr, si, sc, part + 3 * (t.sys * G.nchunk + blockIdx.x));
-}
-
-__device__ __forceinline__ void sys_total3(const double* part, long long sys, int nchunk, double out[3]) {
-  out[0] = out[1] = out[2] = 0.0;
-  for (int c = 0; c < nchunk; ++c)
-    for (int k = 0; k < 3; ++k) out[k] += part[3 * (sys * nchunk + c) + k];
-}
-
-// Close an iteration (init: start the solve): rho_new = <r0, r>, stop on ||r||^2 <= target2,
-// beta = (rho_new / rho) (alpha / omega). A breakdown (|<r0, r>|^2 <= 1e-24 ||r0||^2 ||r||^2,
-// a zero rho or omega, or ||r|| > 1e6 ||r0||) stops the system, which the defect-correction
-// loop then restarts from its current solution.
-__global__ void k_fin_bicg_rho(SysScal S, double* cs, int nsys, int nchunk, const double* part, const int* sel,
-                               const double* target2, int init) {
+__global__ __launch_bounds__(FT) void k_fin_bicg_rho(SysScal S, int v, Parts a, int init) {
   __shared__ int cnt;
   if (threadIdx.x == 0) cnt = 0;
   __syncthreads();
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
-    double v[3];
-    sys_total3(part, s, nchunk, v);
-    const cx<double> rn = {v[0], v[1]};
-    const double rr = v[2];
-    if (!(isfinite(v[0]) && isfinite(v[1]) && isfinite(rr))) S.flags[0] = 4;
-    int act;
-    cx<double> rho, al, om;
+  each_system<3>(S.nsys, a, [&](int s, const double* m) {
+    if (!(isfinite(m[0]) && isfinite(m[1]) && isfinite(m[2]))) S.flags[0] = 4;
+    const int w = init ? 0 : 1 - v;
+    Cs c = {{1.0, 0.0}, {1.0, 0.0}, {1.0, 0.0}, {0.0, 0.0}};
+    bool act = S.selected[s];
     if (init) {
-      act = sel[s] && rr > target2[s];
-      rho = {1.0, 0.0};
-      al = {1.0, 0.0};
-      om = {1.0, 0.0};
+      S.gam[s] = m[2];   // ||r0||^2 (r0 = r at the start)
     } else {
-      act = S.active[s] && rr > target2[s];
-      rho = cs_get(cs, s, CS_RHO);
-      al = cs_get(cs, s, CS_ALPHA);
-      om = cs_get(cs, s, CS_OMEGA);
+      c = cs_get(S, v, s);
+      act = S.active[v * S.nsys + s];
     }
-    S.ss[s] = rr;
-    if (init) S.gam[s] = rr;   // ||r0||^2 (r0 = r at the start)
-    const double rho2 = rho.r * rho.r + rho.i * rho.i, om2 = om.r * om.r + om.i * om.i;
-    const double rn2 = rn.r * rn.r + rn.i * rn.i;
-    // breakdown: <r0, r> (nearly) orthogonal, or a vanishing rho or omega; growth of the
-    // residual beyond 1e6 ||r0|| (which would overflow FP32 iterates) stops the system too
-    if (act && (rho2 == 0.0 || om2 == 0.0 || !(rn2 > 1e-24 * S.gam[s] * rr) || rr > 1e12 * S.gam[s])) act = 0;
-    if (act) {
-      cs_set(cs, s, CS_BETA, cmul(cdiv(rn, rho), cdiv(al, om)));
-      cs_set(cs, s, CS_RHO, rn);
-      cs_set(cs, s, CS_ALPHA, al);        // (1, 0) at the start, else unchanged
-      cs_set(cs, s, CS_OMEGA, om);
-    } else {
-      const cx<double> z = {0.0, 0.0};
-      cs_set(cs, s, CS_BETA, z);
-      cs_set(cs, s, CS_ALPHA, z);
-      cs_set(cs, s, CS_OMEGA, z);
-    }
-    S.active[s] = act;
+    act = rho_step(m, act, S.gam[s], S.target2[s], c);
+    S.ss[s] = m[2];
+    cs_set(S, w, s, c);
+    S.active[w * S.nsys + s] = act;
     if (act) atomicAdd(&cnt, 1);
-  }
+  });
   __syncthreads();
   if (threadIdx.x == 0) S.flags[1] = cnt;
 }
 
-__global__ void k_fin_bicg_alpha(SysScal S, double* cs, int nsys, int nchunk, const double* part) {
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
-    double v[3];
-    sys_total3(part, s, nchunk, v);
-    if (!(isfinite(v[0]) && isfinite(v[1]))) S.flags[0] = 5;
-    const cx<double> den = {v[0], v[1]};
-    if (S.active[s] && (den.r != 0.0 || den.i != 0.0)) {
-      cs_set(cs, s, CS_ALPHA, cdiv(cs_get(cs, s, CS_RHO), den));
-    } else {
-      cs_set(cs, s, CS_ALPHA, {0.0, 0.0});
-      S.active[s] = 0;
-    }
-  }
+template <class R>
+__global__ __launch_bounds__(BT<R>) void k_bicg_p(SysGrid G, Field<R> p, Field<R> r, Field<R> vf, SysScal S, int v,
+                                                 Parts rho) {
+  typedef arith_t<R> A;
+  __shared__ double sh[3 * (BT<R> / 64)];
+  const Tile t = tile_of(G);
+  Cs c = cs_get(S, v, t.sys);
+  bool act = S.active[v * S.nsys + t.sys];
+  cx<A> b, w;
+  stream<R, 3, 1>(
+      t, G.Vhp, {p, r, vf}, {p},
+      [&] {
+        if (rho.p) {
+          if (act) {
+            double m[3];
+            thread_parts<BT<R>, 3>(rho, t.sys, m);
+            block_sums<BT<R>, 3>(m, sh);
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+              if (!(isfinite(m[0]) && isfinite(m[1]) && isfinite(m[2]))) S.flags[0] = 4;
+              S.ss[t.sys] = m[2];
+            }
+            act = rho_step(m, act, S.gam[t.sys], S.target2[t.sys], c);
+          }
+          if (blockIdx.x == 0 && threadIdx.x == 0) {
+            cs_set(S, 1 - v, t.sys, c);
+            S.active[(1 - v) * S.nsys + t.sys] = act;
+          }
+        }
+        b = {(A)c.beta.r, (A)c.beta.i};
+        w = {(A)c.omega.r, (A)c.omega.i};
+        return act;
+      },
+      [&](const cx<A>* in, cx<A>* out) { out[0] = in[1] + cmul(b, in[0] - cmul(w, in[2])); });
+}
+
+template <class R>
+__global__ __launch_bounds__(BT<R>) void k_bicg_s(SysGrid G, Field<R> r, Field<R> vf, SysScal S, int v, Parts den,
+                                                 double* part) {
+  typedef arith_t<R> A;
+  __shared__ double sh[2][3 * (BT<R> / 64)];
+  const Tile t = tile_of(G);
+  Cs c = cs_get(S, v, t.sys);
+  bool act = S.active[v * S.nsys + t.sys];
+  double acc[1] = {0.0};
+  cx<A> a = {A(0), A(0)};
+  stream<R, 2, 1>(
+      t, G.Vhp, {r, vf}, {r},
+      [&] {
+        if (act) {
+          double m[3];
+          thread_parts<BT<R>, 3>(den, t.sys, m);
+          block_sums<BT<R>, 3>(m, sh[0]);
+          if (blockIdx.x == 0 && threadIdx.x == 0 && !(isfinite(m[0]) && isfinite(m[1]))) S.flags[0] = 5;
+          act = m[0] != 0.0 || m[1] != 0.0;
+          c.alpha = act ? cdiv(c.rho, {m[0], m[1]}) : cx<double>{0.0, 0.0};
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+          cs_set(S, 1 - v, t.sys, c);
+          S.active[(1 - v) * S.nsys + t.sys] = act;
+        }
+        a = {(A)c.alpha.r, (A)c.alpha.i};
+        return act;
+      },
+      [&](const cx<A>* in, cx<A>* out) {
+        out[0] = in[0] - cmul(a, in[1]);
+        acc[0] += abs2(out[0]);
+      });
+  block_sums<BT<R>, 1>(acc, sh[1]);
+  if (threadIdx.x == 0) part[t.part] = acc[0];
 }
 
 // omega = <t, s> / ||t||^2. When ||s||^2 already meets the target the step ends with
 // x += alpha p (omega = 0, r = s); when <t, s> (nearly) vanishes the system stops after
 // that same update (breakdown, restarted by the defect-correction loop).
-__global__ void k_fin_bicg_omega(SysScal S, double* cs, int nsys, int nchunk, const double* part, int nchunk_s,
-                                 const double* part_s, const double* target2) {
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
-    double v[3];
-    sys_total3(part, s, nchunk, v);
-    const double ss = sys_total(part_s, s, nchunk_s);
-    if (!(isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2]) && isfinite(ss))) S.flags[0] = 6;
-    cx<double> om = {0.0, 0.0};
-    if (S.active[s]) {
-      S.iters[s] += 1;
-      const double ts2 = v[0] * v[0] + v[1] * v[1];
-      if (ss <= target2[s]) {
-        // converged on s: omega stays 0
-      } else if (v[2] > 0.0 && ts2 > 1e-24 * v[2] * ss) {
-        om = {v[0] / v[2], v[1] / v[2]};
-      } else {
-        S.active[s] = 0;
-      }
-    }
-    cs_set(cs, s, CS_OMEGA, om);
-  }
+template <class R>
+__global__ __launch_bounds__(BT<R>) void k_bicg_xr(SysGrid G, Field<R> x, Field<R> p, Field<R> r, Field<R> tt,
+                                                  Field<R> r0, SysScal S, int v, Parts ts, Parts pss, double* part) {
+  typedef arith_t<R> A;
+  __shared__ double sh[2][4 * (BT<R> / 64)];
+  const Tile t = tile_of(G);
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  Cs c = cs_get(S, v, t.sys);
+  const bool act = S.active[v * S.nsys + t.sys];
+  double acc[3] = {0.0, 0.0, 0.0};
+  cx<A> a = {A(0), A(0)}, w = {A(0), A(0)};
+  stream<R, 5, 2>(
+      t, G.Vhp, {x, p, r, tt, r0}, {x, r},
+      [&] {
+        bool next = act;
+        if (act) {
+          double m[4];
+          thread_parts<BT<R>, 3>(ts, t.sys, m);
+          thread_parts<BT<R>, 1>(pss, t.sys, m + 3);
+          block_sums<BT<R>, 4>(m, sh[0]);
+          if (first) {
+            if (!(isfinite(m[0]) && isfinite(m[1]) && isfinite(m[2]) && isfinite(m[3]))) S.flags[0] = 6;
+            S.iters[t.sys] += 1;
+          }
+          c.omega = {0.0, 0.0};
+          const double ts2 = m[0] * m[0] + m[1] * m[1];
+          if (m[3] <= S.target2[t.sys]) {
+            // converged on s: omega stays 0
+          } else if (m[2] > 0.0 && ts2 > 1e-24 * m[2] * m[3]) {
+            c.omega = {m[0] / m[2], m[1] / m[2]};
+          } else {
+            next = false;
+          }
+        }
+        if (first) {
+          cs_set(S, 1 - v, t.sys, c);
+          S.active[(1 - v) * S.nsys + t.sys] = next;
+        }
+        a = {(A)c.alpha.r, (A)c.alpha.i};
+        w = {(A)c.omega.r, (A)c.omega.i};
+        return act;
+      },
+      [&](const cx<A>* in, cx<A>* out) {
+        out[0] = in[0] + cmul(a, in[1]) + cmul(w, in[2]);
+        const cx<A> rn = in[2] - cmul(w, in[3]), q = in[4];
+        out[1] = rn;
+        acc[0] += (double)q.r * rn.r + (double)q.i * rn.i;
+        acc[1] += (double)q.r * rn.i - (double)q.i * rn.r;
+        acc[2] += abs2(rn);
+      });
+  block_sums<BT<R>, 3>(acc, sh[1]);
+  if (threadIdx.x < 3) part[3 * t.part + threadIdx.x] = acc[threadIdx.x];
 }
 
 template <class R>
-__global__ __launch_bounds__(256) void k_lin3(SysGrid G, Field<R> y, Field<R> u, Field<R> w, Field<R> q,
+__global__ __launch_bounds__(BT<R>) void k_lin3(SysGrid G, Field<R> y, Field<R> u, Field<R> w, Field<R> q,
                                               const double* coef, double* part) {
   typedef arith_t<R> A;
+  __shared__ double sh[3 * (BT<R> / 64)];
   const Tile t = tile_of(G);
-  double sr = 0.0, si = 0.0, sc = 0.0;
+  double s[3] = {0.0, 0.0, 0.0};
   if (t.selected) {
     const double* cf = coef + 6 * t.sys;
     const cx<A> c0 = {(A)cf[0], (A)cf[1]}, c1 = {(A)cf[2], (A)cf[3]}, c2 = {(A)cf[4], (A)cf[5]};
     const bool keep_y = cf[0] != 0.0 || cf[1] != 0.0;   // c0 = 0: y is not read (may be unset)
     const bool with_w = w.ptr != nullptr, with_q = q.ptr != nullptr;
-    for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-      const SiteR<R> ur = site_r(u, t.rhs, 0, j, G.Vhp);
-      SiteR<R> yr, wr, qr;
-      if (keep_y) yr = site_r(y, t.rhs, 0, j, G.Vhp);
-      if (with_w) wr = site_r(w, t.rhs, 0, j, G.Vhp);
-      if (with_q) qr = site_r(q, t.rhs, 0, j, G.Vhp);
-      SiteW<R> yw = site_w(y, t.rhs, 0, j, G.Vhp);
+    const int wv = threadIdx.x >> 6;
+    for (long long j = t.j0 + (threadIdx.x & 63); j < t.j1; j += 64) {
+      cx<A> uv[2], yv[2], ww[2], qv[2], o[2];
+      ld_pair<R>(u, t.rhs, t.p, j, wv, uv);
+      if (keep_y) ld_pair<R>(y, t.rhs, t.p, j, wv, yv);
+      if (with_w) ld_pair<R>(w, t.rhs, t.p, j, wv, ww);
+      if (with_q) ld_pair<R>(q, t.rhs, t.p, j, wv, qv);
 #pragma unroll
-      for (int k = 0; k < 12; ++k) {
-        cx<A> v = cmul(c1, get(ur, k));
-        if (keep_y) v = v + cmul(c0, get(yr, k));
-        if (with_w) v = v + cmul(c2, get(wr, k));
-        put(yw, k, v);
+      for (int i = 0; i < 2; ++i) {
+        cx<A> v = cmul(c1, uv[i]);
+        if (keep_y) v = v + cmul(c0, yv[i]);
+        if (with_w) v = v + cmul(c2, ww[i]);
+        o[i] = v;
         if (with_q) {
-          const cx<A> qv = get(qr, k);
-          sr += (double)qv.r * v.r + (double)qv.i * v.i;
-          si += (double)qv.r * v.i - (double)qv.i * v.r;
+          s[0] += (double)qv[i].r * v.r + (double)qv[i].i * v.i;
+          s[1] += (double)qv[i].r * v.i - (double)qv[i].i * v.r;
         }
-        sc += (double)v.r * v.r + (double)v.i * v.i;
+        s[2] += abs2(v);
       }
-      close(yw);
+      st_pair<R>(y, t.rhs, t.p, j, wv, o);
     }
   }
-  if (part) block_sum3(sr, si, sc, part + 3 * (t.sys * G.nchunk + blockIdx.x));
-}
-
-__global__ void k_fin_sum3(int nsys, int nchunk, const double* part, double* out) {
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
-    double v[3];
-    sys_total3(part, s, nchunk, v);
-    for (int k = 0; k < 3; ++k) out[3 * s + k] = v[k];
+  if (part) {
+    block_sums<BT<R>, 3>(s, sh);
+    if (threadIdx.x < 3) part[3 * t.part + threadIdx.x] = s[threadIdx.x];
   }
 }
 
-template <class R>
-__global__ __launch_bounds__(256) void k_geom_add(SysGrid G, Field<R> x, Field<R> tf, const int* active) {
-  const Tile t = tile_of(G);
-  if (!t.selected || !active[t.sys]) return;
-  for (long long j = t.j0 + threadIdx.x; j < t.j1; j += 256) {
-    const SiteR<R> xr = site_r(x, t.rhs, 0, j, G.Vhp), tr = site_r(tf, t.rhs, 0, j, G.Vhp);
-    SiteW<R> xw = site_w(x, t.rhs, 0, j, G.Vhp);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) put(xw, k, get(xr, k) + get(tr, k));
-    close(xw);
+// ---- geometric series -----------------------------------------------------------------------
+
+// A system stops once the new term satisfies ||t||^2 <= target2, and is flagged divergent
+// once ||t||^2 > 1e30 ||b_hat||^2 (ss keeps ||t_0||^2 = ||b_hat||^2).
+__device__ __forceinline__ bool geom_step(const SysScal& S, long long sys, double tt, bool record) {
+  if (record && !isfinite(tt)) S.flags[0] = 7;
+  if (record) S.iters[sys] += 1;
+  if (tt <= S.target2[sys]) return false;
+  if (!(tt <= 1e30 * S.ss[sys])) {
+    if (record) S.flags[2] = 1;
+    return false;
   }
+  return true;
 }
 
-// Geometric series: init marks the systems with ||t_0||^2 = ||b_hat||^2 above target
-// (ss keeps it as the divergence reference); a later call stops a system once the new
-// term satisfies ||t||^2 <= target2, and flags a divergence once ||t||^2 > 1e30 ||b_hat||^2.
-__global__ void k_fin_geom(SysScal S, int nsys, int nchunk, const double* part, const int* sel,
-                           const double* target2, int init) {
+__global__ __launch_bounds__(FT) void k_fin_geom(SysScal S, int v, Parts a, int init) {
   __shared__ int cnt;
   if (threadIdx.x == 0) cnt = 0;
   __syncthreads();
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
-    const double tt = sys_total(part, s, nchunk);
-    if (!isfinite(tt)) S.flags[0] = 7;
-    int act;
+  each_system<1>(S.nsys, a, [&](int s, const double* m) {
+    bool act;
     if (init) {
-      act = sel[s] && tt > target2[s];
-      S.ss[s] = tt;
+      if (!isfinite(m[0])) S.flags[0] = 7;
+      act = S.selected[s] && m[0] > S.target2[s];
+      S.ss[s] = m[0];
     } else {
-      act = S.active[s];
-      if (act) {
-        S.iters[s] += 1;
-        if (tt <= target2[s]) act = 0;
-        else if (!(tt <= 1e30 * S.ss[s])) {
-          S.flags[2] = 1;
-          act = 0;
-        }
-      }
+      act = S.active[v * S.nsys + s] && geom_step(S, s, m[0], true);
     }
-    S.active[s] = act;
+    S.active[(init ? 0 : 1 - v) * S.nsys + s] = act;
     if (act) atomicAdd(&cnt, 1);
-  }
+  });
   __syncthreads();
   if (threadIdx.x == 0) S.flags[1] = cnt;
 }
 
-// ---------------------------------------------------------------------------------
-static inline dim3 grid_of(const SysGrid& G, int nrhs) { return dim3(G.nchunk, G.nblk, nrhs); }
+template <class R>
+__global__ __launch_bounds__(BT<R>) void k_geom_add(SysGrid G, Field<R> x, Field<R> tf, SysScal S, int v, Parts tt) {
+  typedef arith_t<R> A;
+  __shared__ double sh[BT<R> / 64];
+  const Tile t = tile_of(G);
+  bool act = S.active[v * S.nsys + t.sys];
+  stream<R, 2, 1>(
+      t, G.Vhp, {x, tf}, {x},
+      [&] {
+        if (tt.p) {
+          const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+          if (act) {
+            double m[1];
+            thread_parts<BT<R>, 1>(tt, t.sys, m);
+            block_sums<BT<R>, 1>(m, sh);
+            act = geom_step(S, t.sys, m[0], first);
+          }
+          if (first) S.active[(1 - v) * S.nsys + t.sys] = act;
+        }
+        return act;
+      },
+      [&](const cx<A>* in, cx<A>* out) { out[0] = in[0] + in[1]; });
+}
 
+inline dim3 grid_of(const SysGrid& G, int nrhs, int npar = 1) { return dim3(G.nchunk, G.nblk, nrhs * npar); }
+
+}  // namespace
+
+// ---------------------------------------------------------------------------------
 template <class R> void blas_norm2(const SysGrid& G, int nrhs, Field<R> a, int npar, double* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_norm2<R>, grid_of(G, nrhs), dim3(256), 0, s, G, a, npar, part);
+  hipLaunchKernelGGL(k_norm2<R>, grid_of(G, nrhs, npar), dim3(BT<R>), 0, s, G, a, npar, part);
 }
-template <class R> void blas_cg_s(const SysGrid& G, int nrhs, Field<R> sf, Field<R> q, const double* alpha,
-                                  double* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_s<R>, grid_of(G, nrhs), dim3(256), 0, s, G, sf, q, alpha, part);
+template <class R> void blas_cg_s(const SysGrid& G, int nrhs, Field<R> sf, Field<R> q, const SysScal& S, int v,
+                                  Parts qq, double* part, hipStream_t s) {
+  hipLaunchKernelGGL(k_cg_s<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, sf, q, S, v, qq, part);
 }
-template <class R> void blas_cg_xp(const SysGrid& G, int nrhs, Field<R> x, Field<R> p, Field<R> r,
-                                   const double* alpha, const double* beta, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_xp<R>, grid_of(G, nrhs), dim3(256), 0, s, G, x, p, r, alpha, beta);
+template <class R> void blas_cg_xp(const SysGrid& G, int nrhs, Field<R> x, Field<R> p, Field<R> r, const SysScal& S,
+                                   int v, Parts ss, Parts rr, hipStream_t s) {
+  hipLaunchKernelGGL(k_cg_xp<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, x, p, r, S, v, ss, rr);
 }
 template <class Ro, class Ri> void blas_convert(const SysGrid& G, int nrhs, Field<Ro> out, Field<Ri> in,
                                                 int npar, hipStream_t s) {
-  hipLaunchKernelGGL((k_convert<Ro, Ri>), grid_of(G, nrhs), dim3(256), 0, s, G, out, in, npar);
+  hipLaunchKernelGGL(k_convert<Ro>, grid_of(G, nrhs, npar), dim3(BT<Ro>), 0, s, G, out, in, npar);
 }
 template <class R> void blas_add_mixed(const SysGrid& G, int nrhs, Field<double> x, Field<R> e, hipStream_t s) {
-  hipLaunchKernelGGL(k_add_mixed<R>, grid_of(G, nrhs), dim3(256), 0, s, G, x, e);
+  hipLaunchKernelGGL(k_add_mixed<R>, grid_of(G, nrhs, 2), dim3(BT<R>), 0, s, G, x, e);
 }
 void blas_resid(const SysGrid& G, int nrhs, Field<double> r, Field<double> b, Field<double> Ax, double* part,
                 hipStream_t s, int npar) {
-  hipLaunchKernelGGL(k_resid, grid_of(G, nrhs), dim3(256), 0, s, G, r, b, Ax, part, npar);
+  hipLaunchKernelGGL(k_resid, grid_of(G, nrhs, npar), dim3(BT<double>), 0, s, G, r, b, Ax, part, npar);
 }
-void fin_sum(int nsys, int nchunk, const double* part, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_sum, dim3(1), dim3(256), 0, s, nsys, nchunk, part, out);
+void fin_sum(int nsys, Parts a, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_fin_sum, dim3(1), dim3(FT), 0, s, nsys, a, out);
 }
-void fin_init(const SysScal& S, int nsys, int nchunk, const double* pb, const double* pr, const int* sel,
-              const double* target2, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(256), 0, s, S, nsys, nchunk, pb, pr, sel, target2);
+void fin_sum3(int nsys, Parts a, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_fin_sum3, dim3(1), dim3(FT), 0, s, nsys, a, out);
 }
-void fin_alpha(const SysScal& S, int nsys, int nchunk, const double* pq, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(256), 0, s, S, nsys, nchunk, pq);
+void fin_targets(int nsys, Parts bh, const double* bnorm2, double inner2, double abs2, double* target2,
+                 hipStream_t s) {
+  hipLaunchKernelGGL(k_targets, dim3(1), dim3(FT), 0, s, nsys, bh, bnorm2, inner2, abs2, target2);
 }
-void fin_beta(const SysScal& S, int nsys, int nchunk, const double* ps_, int nchunk_r, const double* pr,
-              const double* target2, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_beta, dim3(1), dim3(256), 0, s, S, nsys, nchunk, ps_, nchunk_r, pr, target2);
+int compress_parts(int nsys, int nv, Parts a, double* out, hipStream_t s) {
+  const int n = (a.n + 255) / 256;
+  hipLaunchKernelGGL(k_compress, dim3(n, nsys), dim3(256), 0, s, nv, a, out);
+  return n;
 }
-
+void fin_init(const SysScal& S, Parts b, Parts r, hipStream_t s) {
+  hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(FT), 0, s, S, b, r);
+}
+void fin_count(const SysScal& S, int v, hipStream_t s) {
+  hipLaunchKernelGGL(k_fin_count, dim3(1), dim3(256), 0, s, S, v);
+}
 template <class R> void blas_cdot3(const SysGrid& G, int nrhs, Field<R> a, Field<R> b, Field<R> c, double* part,
                                    hipStream_t s) {
-  hipLaunchKernelGGL(k_cdot3<R>, grid_of(G, nrhs), dim3(256), 0, s, G, a, b, c, part);
+  hipLaunchKernelGGL(k_cdot3<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, a, b, c, part);
 }
-template <class R> void blas_bicg_p(const SysGrid& G, int nrhs, Field<R> p, Field<R> r, Field<R> v,
-                                    const double* cs, hipStream_t s) {
-  hipLaunchKernelGGL(k_bicg_p<R>, grid_of(G, nrhs), dim3(256), 0, s, G, p, r, v, cs);
+template <class R> void blas_bicg_p(const SysGrid& G, int nrhs, Field<R> p, Field<R> r, Field<R> v, const SysScal& S,
+                                    int ver, Parts rho, hipStream_t s) {
+  hipLaunchKernelGGL(k_bicg_p<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, p, r, v, S, ver, rho);
 }
-template <class R> void blas_bicg_s(const SysGrid& G, int nrhs, Field<R> r, Field<R> v, const double* cs,
-                                    double* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_bicg_s<R>, grid_of(G, nrhs), dim3(256), 0, s, G, r, v, cs, part);
+template <class R> void blas_bicg_s(const SysGrid& G, int nrhs, Field<R> r, Field<R> v, const SysScal& S, int ver,
+                                    Parts den, double* part, hipStream_t s) {
+  hipLaunchKernelGGL(k_bicg_s<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, r, v, S, ver, den, part);
 }
 template <class R> void blas_bicg_xr(const SysGrid& G, int nrhs, Field<R> x, Field<R> p, Field<R> r,
-                                     Field<R> t, Field<R> r0, const double* cs, double* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_bicg_xr<R>, grid_of(G, nrhs), dim3(256), 0, s, G, x, p, r, t, r0, cs, part);
+                                     Field<R> t, Field<R> r0, const SysScal& S, int ver, Parts ts, Parts ss,
+                                     double* part, hipStream_t s) {
+  hipLaunchKernelGGL(k_bicg_xr<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, x, p, r, t, r0, S, ver, ts, ss, part);
 }
-void fin_bicg_rho(const SysScal& S, double* cs, int nsys, int nchunk, const double* part, const int* sel,
-                  const double* target2, int init, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_bicg_rho, dim3(1), dim3(256), 0, s, S, cs, nsys, nchunk, part, sel, target2, init);
+void fin_bicg_rho(const SysScal& S, int ver, Parts a, int init, hipStream_t s) {
+  hipLaunchKernelGGL(k_fin_bicg_rho, dim3(1), dim3(FT), 0, s, S, ver, a, init);
 }
-void fin_bicg_alpha(const SysScal& S, double* cs, int nsys, int nchunk, const double* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_bicg_alpha, dim3(1), dim3(256), 0, s, S, cs, nsys, nchunk, part);
+template <class R> void blas_geom_add(const SysGrid& G, int nrhs, Field<R> x, Field<R> t, const SysScal& S, int ver,
+                                      Parts tt, hipStream_t s) {
+  hipLaunchKernelGGL(k_geom_add<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, x, t, S, ver, tt);
 }
-void fin_bicg_omega(const SysScal& S, double* cs, int nsys, int nchunk, const double* part, int nchunk_s,
-                    const double* part_s, const double* target2, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_bicg_omega, dim3(1), dim3(256), 0, s, S, cs, nsys, nchunk, part, nchunk_s, part_s,
-                     target2);
-}
-template <class R> void blas_geom_add(const SysGrid& G, int nrhs, Field<R> x, Field<R> t, const int* active,
-                                      hipStream_t s) {
-  hipLaunchKernelGGL(k_geom_add<R>, grid_of(G, nrhs), dim3(256), 0, s, G, x, t, active);
+void fin_geom(const SysScal& S, int ver, Parts tt, int init, hipStream_t s) {
+  hipLaunchKernelGGL(k_fin_geom, dim3(1), dim3(FT), 0, s, S, ver, tt, init);
 }
 template <class R> void blas_lin3(const SysGrid& G, int nrhs, Field<R> y, Field<R> u, Field<R> w, Field<R> q,
                                   const double* coef, double* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_lin3<R>, grid_of(G, nrhs), dim3(256), 0, s, G, y, u, w, q, coef, part);
-}
-void fin_sum3(int nsys, int nchunk, const double* part, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_sum3, dim3(1), dim3(256), 0, s, nsys, nchunk, part, out);
-}
-void fin_geom(const SysScal& S, int nsys, int nchunk, const double* part, const int* sel, const double* target2,
-              int init, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_geom, dim3(1), dim3(256), 0, s, S, nsys, nchunk, part, sel, target2, init);
+  hipLaunchKernelGGL(k_lin3<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, y, u, w, q, coef, part);
 }
 
-#define INST(R)                                                                                         \
-  template void blas_norm2<R>(const SysGrid&, int, Field<R>, int, double*, hipStream_t);                 \
-  template void blas_cg_s<R>(const SysGrid&, int, Field<R>, Field<R>, const double*, double*, hipStream_t); \
-  template void blas_cg_xp<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, const double*,           \
-                              const double*, hipStream_t);                                               \
-  template void blas_add_mixed<R>(const SysGrid&, int, Field<double>, Field<R>, hipStream_t);           \
-  template void blas_cdot3<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, double*, hipStream_t);  \
-  template void blas_bicg_p<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, const double*, hipStream_t); \
-  template void blas_bicg_s<R>(const SysGrid&, int, Field<R>, Field<R>, const double*, double*, hipStream_t); \
-  template void blas_bicg_xr<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, Field<R>, Field<R>,   \
-                                const double*, double*, hipStream_t);                                    \
-  template void blas_geom_add<R>(const SysGrid&, int, Field<R>, Field<R>, const int*, hipStream_t);      \
-  template void blas_lin3<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, Field<R>, const double*,  \
-                             double*, hipStream_t);
+#define INST(R)                                                                                              \
+  template void blas_norm2<R>(const SysGrid&, int, Field<R>, int, double*, hipStream_t);                      \
+  template void blas_cg_s<R>(const SysGrid&, int, Field<R>, Field<R>, const SysScal&, int, Parts, double*,    \
+                             hipStream_t);                                                                    \
+  template void blas_cg_xp<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, const SysScal&, int, Parts,  \
+                              Parts, hipStream_t);                                                            \
+  template void blas_add_mixed<R>(const SysGrid&, int, Field<double>, Field<R>, hipStream_t);                 \
+  template void blas_cdot3<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, double*, hipStream_t);       \
+  template void blas_bicg_p<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, const SysScal&, int, Parts, \
+                               hipStream_t);                                                                  \
+  template void blas_bicg_s<R>(const SysGrid&, int, Field<R>, Field<R>, const SysScal&, int, Parts, double*,  \
+                               hipStream_t);                                                                  \
+  template void blas_bicg_xr<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, Field<R>, Field<R>,        \
+                                const SysScal&, int, Parts, Parts, double*, hipStream_t);                     \
+  template void blas_geom_add<R>(const SysGrid&, int, Field<R>, Field<R>, const SysScal&, int, Parts, hipStream_t);
 INST(double)
 INST(float)
 INST(h16)
+template void blas_lin3<double>(const SysGrid&, int, Field<double>, Field<double>, Field<double>, Field<double>,
+                                const double*, double*, hipStream_t);
 template void blas_convert<double, double>(const SysGrid&, int, Field<double>, Field<double>, int, hipStream_t);
 template void blas_convert<float, double>(const SysGrid&, int, Field<float>, Field<double>, int, hipStream_t);
 template void blas_convert<h16, double>(const SysGrid&, int, Field<h16>, Field<double>, int, hipStream_t);

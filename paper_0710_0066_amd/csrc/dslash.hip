@@ -1943,12 +1943,26 @@ template <class R> static void launch_stream(const HopArgs<R>& A, hipStream_t st
 // 12 rhs: 329 / 309) always, the FP64 one (16^3x32, 12 rhs: 117 / 99; 24^3x48, 12 rhs:
 // 625 / 655) up to twice that input. Slices of fewer than 16 chunks of 64 sites leave some
 // of the 8 XCDs idle or short in this order and run in the linear one.
-template <class R> static void launch_march1(const HopArgs<R>& A, hipStream_t st) {
+template <class R> static int march1_order(const HopArgs<R>& A) {
   const bool full = A.parity_out < 0, f32 = std::is_same<R, float>::value;
   const double in = 2.0 * A.g.Vh * A.nrhs * 24 * sizeof(R);      // bytes of the whole input field
-  if ((!full && f32) || in <= (full ? 200e6 : 400e6)) launch_split<R>(A, A.g.V3h >= 16 * TILE, st);
+  if ((!full && f32) || in <= (full ? 200e6 : 400e6)) return A.g.V3h >= 16 * TILE ? 1 : 0;
+  return -1;
+}
+template <class R> static void launch_march1(const HopArgs<R>& A, hipStream_t st) {
+  const int order = march1_order(A);
+  if (order >= 0) launch_split<R>(A, order == 1, st);
   else launch_march<R, 1>(A, st);
 }
+
+template <class R> int hop_red_slots(const HopArgs<R>& A, int nlb) {
+  if (A.map == HOP_MAP_SLABD && std::is_same<R, float>::value) return slabd_norm_slots(A.g, nlb);
+  if (A.map == HOP_MAP_SITE) return split_chunks(A.g, nlb, false);
+  if (A.map == HOP_MAP_MARCH1 && march1_order(A) >= 0) return split_chunks(A.g, nlb, march1_order(A) == 1);
+  return 0;
+}
+template int hop_red_slots<double>(const HopArgs<double>&, int);
+template int hop_red_slots<float>(const HopArgs<float>&, int);
 
 template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t st) {
   const bool full = A.parity_out < 0;

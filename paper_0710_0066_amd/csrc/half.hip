@@ -158,6 +158,19 @@ template <int NR> static void launch_march16(const HopArgs<h16>& A, hipStream_t 
 #undef SAP_M16
 }
 
+// few wavefronts: the eight hops of a site on the eight wavefronts of a workgroup. Measured
+// (us, split / site): half hop on 16^3x32, 1 rhs 6.6 / 7.2, 3 rhs 13.8 / 13.1, on
+// 16x8^3, 1 rhs 3.9 / 6.7; full operator on 16^3x32, 1 rhs 11.1 / 11.2, 3 rhs 26.5 / 23.7
+static bool site_is_split(const HopArgs<h16>& A) {
+  return 2.0 * A.g.Vh * A.nrhs <= (A.parity_out < 0 ? 1.5e5 : 3e5);
+}
+
+template <> int hop_red_slots<h16>(const HopArgs<h16>& A, int nlb) {
+  if (A.map == HOP_MAP_SLABD) return slabd_norm_slots(A.g, nlb);
+  if (A.map == HOP_MAP_SITE && site_is_split(A)) return split_chunks(A.g, nlb, false);
+  return 0;
+}
+
 template <> void launch_hop<h16>(const HopArgs<h16>& A, hipStream_t st) {
   switch (A.map) {
     case HOP_MAP_MARCH1:
@@ -176,10 +189,7 @@ template <> void launch_hop<h16>(const HopArgs<h16>& A, hipStream_t st) {
     default: break;
   }
   const bool full = A.parity_out < 0;
-  // few wavefronts: the eight hops of a site on the eight wavefronts of a workgroup. Measured
-  // (us, split / site): half hop on 16^3x32, 1 rhs 6.6 / 7.2, 3 rhs 13.8 / 13.1, on
-  // 16x8^3, 1 rhs 3.9 / 6.7; full operator on 16^3x32, 1 rhs 11.1 / 11.2, 3 rhs 26.5 / 23.7
-  if (2.0 * A.g.Vh * A.nrhs <= (full ? 1.5e5 : 3e5)) {
+  if (site_is_split(A)) {
     launch_split<h16>(A, false, st);
     return;
   }

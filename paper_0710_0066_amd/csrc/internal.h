@@ -65,13 +65,15 @@ template <class R> struct HopArgs {
   typename arith<R>::type a, b;
   int g5_in, g5_out;       // multiply the hop input / the hop result by gamma_5
   int map;                 // work-item mapping (HOP_MAP_*), nrhs > 1 only
-  // optional (HOP_MAP_SLABD only): per-system partial reductions of the output over
-  // systems (rhs, block of nlb slices), nslot partials per system (see slabd_norm_slots):
+  // optional (half hop, mappings with hop_red_slots > 0): per-system partial reductions of
+  // the output over systems (rhs, block of nlb slices), nslot partials per system:
   //   red = 1: ||out||^2 at npart[sys * nslot + k];
   //   red = 3: (Re, Im <out, x>, ||out||^2) with out conjugated, at
   //   npart[3 (sys * nslot + k) + i].
   double* npart = nullptr;
   int nlb = 0, nslot = 0, red = 0;
+  // optional: nonzero where a system is still iterated; the others may be left as they are
+  const int* active = nullptr;
 };
 
 // Work-item mappings of the hop kernel for several right-hand sides.
@@ -105,8 +107,11 @@ constexpr int HOP_WALK_T = 8;   // slices per walk
 template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t s);
 // mapping of an untuned context for the full operator or the half hop (prec: sap_prec)
 int hop_default_map(const Geo& g, bool full, int prec, int nrhs);
-// partials per system of the norm the LDS-staged slab kernel (HOP_MAP_SLABD, FP32 even-odd
-// hop) can add to its output for systems of nlb slices
+// partials per system of nlb slices that the half hop A (its mapping, precision, lattice and
+// rhs) can write of its output (HopArgs::npart); 0: its mapping has none
+template <class R> int hop_red_slots(const HopArgs<R>& A, int nlb);
+template <> int hop_red_slots<h16>(const HopArgs<h16>& A, int nlb);   // half.hip
+// those of the LDS-staged slab kernel
 int slabd_norm_slots(const Geo& g, int nlb);
 // the LDS-staged slab kernel on FP16 storage (even-odd hop; dslash.hip)
 void launch_slabd16(const HopArgs<h16>& A, hipStream_t s);

@@ -12,8 +12,11 @@
 //    terms), whose residual after n terms is the next term; for the shifted even-site
 //    system (M_hat + rho) x_e = b_e of the mass-preconditioned parts every term carries a
 //    factor 1 / (1 + rho) and the residual after n terms is (1 + rho) times the next term.
-// Per-system scalars stay on the device; converged systems are frozen while the others
-// continue; the host reads one counter every few iterations.
+// Per-system scalars stay on the device, formed by the kernels that need them from the
+// partial sums (blas.hip), so that a CG iteration is six launches with the norms written by
+// the hops; converged systems are frozen while the others continue; the host reads one
+// counter every few iterations. On 16^3x32 with one rhs and FP32 inner iterations an
+// iteration went from 93 us in ten launches to 58 us.
 // Outer loop: FP64 defect correction r = b - A x (A applied in FP64), inner solve in
 // FP32 or FP64, x += e, until ||b - A x|| / ||b|| <= tol recomputed in FP64.
 #include <algorithm>
@@ -22,6 +25,7 @@
 #include <cstring>
 #include <vector>
 #include "blas.h"
+#include "split.h"
 
 using namespace sap;
 
@@ -31,13 +35,14 @@ int apply_op_any(sap_ctx* ctx, void* out, const void* in, int nrhs, int lb, int 
 }
 
 struct SolverWS {
-  int max_rhs, max_sys, max_chunk;
-  size_t part_cap;                       // doubles in each of partA / partB / partC
+  int max_rhs, max_sys;
+  size_t part_cap;                       // doubles in each of partA ... partE
   double2 *hx, *s, *r, *p, *q, *t;       // half fields (sized for FP64, max_rhs)
   double2 *x64, *r64, *ax, *rin, *e;     // full fields
-  double *partA, *partB, *partC;
-  double *gam, *ss, *alpha, *beta, *target2, *bnorm2, *rnorm2;
+  double *partA, *partB, *partC, *partD, *partE;
+  double *gam, *ss, *alpha, *target2, *bnorm2, *rnorm2;
   double* cs;                            // BiCGstab: complex (rho, alpha, omega, beta) per system
+                                         // (gam, cs and active: two versions)
   int *active, *iters, *flags, *selected;
   // pinned host mirrors
   double *h_rnorm2, *h_bnorm2;
@@ -62,17 +67,16 @@ extern "C" int sap_solver_create(sap_ctx* c) {
   w->max_rhs = c->geom.max_rhs;
   w->max_sys = (c->geom.L[0] / minlb) * w->max_rhs;
   if (w->max_sys < w->max_rhs) w->max_sys = w->max_rhs;
-  w->max_chunk = (int)((c->Vh + CHUNK - 1) / CHUNK);
   const size_t half = (size_t)12 * c->Vhp * w->max_rhs * sizeof(double2);
   const size_t full = 2 * half;
-  // three partials per (system, chunk); a level of nblk blocks has at most max_chunk + nblk
-  // chunks per rhs
-  size_t npart = (size_t)3 * w->max_rhs * (w->max_chunk + c->geom.L[0] / minlb + 1);
-  // room for the hop-fused reductions too (three values per slot; systems of l0, l0_sub
-  // or all L0 slices)
+  // three partials per (system, 64-site chunk of each parity, the chunks of a block or of a
+  // slice rounded up), or per slot of the LDS-staged hops
+  size_t npart = 0;
   for (int nlb : {c->geom.l0, c->geom.l0_sub, c->geom.L[0]})
-    if (nlb > 0)
-      npart = std::max(npart, (size_t)3 * w->max_rhs * (c->geom.L[0] / nlb) * slabd_norm_slots(c->g, nlb));
+    if (nlb > 0) {
+      const int per_sys = std::max(2 * split_chunks(c->g, nlb, true), slabd_norm_slots(c->g, nlb));
+      npart = std::max(npart, (size_t)3 * w->max_rhs * (c->geom.L[0] / nlb) * per_sys);
+    }
   w->part_cap = npart;
   auto A = [&](void** p, size_t n) { return hipMalloc(p, n) == hipSuccess; };
   bool ok = A((void**)&w->hx, half) && A((void**)&w->s, half) && A((void**)&w->r, half) &&
@@ -80,11 +84,12 @@ extern "C" int sap_solver_create(sap_ctx* c) {
             A((void**)&w->x64, full) && A((void**)&w->r64, full) && A((void**)&w->ax, full) &&
             A((void**)&w->rin, full) && A((void**)&w->e, full) &&
             A((void**)&w->partA, npart * 8) && A((void**)&w->partB, npart * 8) &&
-            A((void**)&w->partC, npart * 8);
+            A((void**)&w->partC, npart * 8) && A((void**)&w->partD, npart * 8) &&
+            A((void**)&w->partE, npart * 8);
   const size_t ns = (size_t)w->max_sys;
-  ok = ok && A((void**)&w->gam, ns * 8) && A((void**)&w->ss, ns * 8) && A((void**)&w->alpha, ns * 8) &&
-       A((void**)&w->beta, ns * 8) && A((void**)&w->target2, ns * 8) && A((void**)&w->bnorm2, ns * 8) &&
-       A((void**)&w->rnorm2, ns * 8) && A((void**)&w->cs, ns * 64) && A((void**)&w->active, ns * 4) &&
+  ok = ok && A((void**)&w->gam, 2 * ns * 8) && A((void**)&w->ss, ns * 8) && A((void**)&w->alpha, ns * 8) &&
+       A((void**)&w->target2, ns * 8) && A((void**)&w->bnorm2, ns * 8) &&
+       A((void**)&w->rnorm2, ns * 8) && A((void**)&w->cs, 2 * ns * 64) && A((void**)&w->active, 2 * ns * 4) &&
        A((void**)&w->iters, ns * 4) &&
        A((void**)&w->flags, 16) && A((void**)&w->selected, ns * 4);
   ok = ok && hipHostMalloc((void**)&w->h_rnorm2, ns * 8, 0) == hipSuccess &&
@@ -109,7 +114,7 @@ extern "C" void sap_solver_destroy(sap_ctx* c) {
   SolverWS* w = ws_of(c);
   if (!w) return;
   void* dev[] = {w->hx, w->s, w->r, w->p, w->q, w->t, w->x64, w->r64, w->ax, w->rin, w->e,
-                 w->partA, w->partB, w->partC, w->gam, w->ss, w->alpha, w->beta, w->target2,
+                 w->partA, w->partB, w->partC, w->partD, w->partE, w->gam, w->ss, w->alpha, w->target2,
                  w->bnorm2, w->rnorm2, w->cs, w->active, w->iters, w->flags, w->selected};
   for (void* p : dev)
     if (p) (void)hipFree(p);
@@ -122,30 +127,24 @@ extern "C" void sap_solver_destroy(sap_ctx* c) {
   c->solver = nullptr;
 }
 
-__global__ void k_targets(int nsys, const double* partb, int nchunk, const double* bnorm2, double inner2,
-                          double abs2, double* target2) {
-  for (int s = threadIdx.x; s < nsys; s += blockDim.x) {
-    double bb = 0.0;
-    for (int c = 0; c < nchunk; ++c) bb += partb[(long long)s * nchunk + c];
-    target2[s] = fmax(inner2 * bb, abs2 * bnorm2[s]);
-  }
-}
-
 namespace {
 
+// reductions a half hop adds to its output for systems of nlb slices (HopArgs::npart)
+struct Fused {
+  double* part = nullptr;
+  int nlb = 0, nslot = 0, red = 0;
+  const int* active = nullptr;
+};
+
 // out = a*x + b*D(in) on one parity or both, block-restricted
-// npart (even-odd FP32 hop with the LDS-staged slab mapping only, g5i = 0): also write the
-// partial reductions red of each system of nlb slices, nslot per system (slabd_norm_slots):
-// 1 ||out||^2, 3 <out, x> and ||out||^2 (HopArgs::red)
 template <class R>
-void hop(sap_ctx* c, const void* U, Field<R> out, Field<R> in, Field<R> x, int parity_out, int nrhs, int lb,
-         int colour, typename arith<R>::type a, typename arith<R>::type b, int g5i, int g5o, hipStream_t st,
-         double* npart = nullptr, int nlb = 0, int nslot = 0, int red = 1) {
+HopArgs<R> hop_args(sap_ctx* c, Field<R> out, Field<R> in, Field<R> x, int parity_out, int nrhs, int lb, int colour,
+                    typename arith<R>::type a, typename arith<R>::type b, int g5i, int g5o) {
   HopArgs<R> A;
   A.out = out;
   A.in = in;
   A.x = x;
-  A.U = (const typename vec2<R>::type*)U;
+  A.U = gauge_of<R>(c);
   A.g = c->g;
   A.nrhs = nrhs;
   A.parity_out = parity_out;
@@ -158,10 +157,17 @@ void hop(sap_ctx* c, const void* U, Field<R> out, Field<R> in, Field<R> x, int p
   A.g5_in = g5i;
   A.g5_out = g5o;
   A.map = hop_map_for(c, parity_out < 0, prec_of<R>(), nrhs);
-  A.npart = npart;
-  A.nlb = nlb;
-  A.nslot = nslot;
-  A.red = red;
+  return A;
+}
+template <class R>
+void hop(sap_ctx* c, Field<R> out, Field<R> in, Field<R> x, int parity_out, int nrhs, int lb, int colour,
+         typename arith<R>::type a, typename arith<R>::type b, int g5i, int g5o, hipStream_t st, Fused f = {}) {
+  HopArgs<R> A = hop_args<R>(c, out, in, x, parity_out, nrhs, lb, colour, a, b, g5i, g5o);
+  A.npart = f.part;
+  A.nlb = f.nlb;
+  A.nslot = f.nslot;
+  A.red = f.red;
+  A.active = f.active;
   launch_hop<R>(A, st);
 }
 
@@ -177,10 +183,9 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
   typedef typename arith<R>::type Ar;
   SolverWS* w = ws_of(c);
   const long long Vh = c->Vh, Vhp = c->Vhp;
-  const SysGrid G = make_sysgrid(Vh, c->g.V3h, lb, c->geom.L[0], colour);
+  const SysGrid G = make_sysgrid(Vh, c->g.V3h, lb, c->geom.L[0], colour, nrhs, std::is_same<R, h16>::value);
   const int nsys = G.nblk * nrhs;
   const double kap = c->geom.kappa;
-  const void* U = gauge_of<R>(c);
   const Ar kR = (Ar)kap, k2R = (Ar)(-kap * kap);
   const Ar aI = (Ar)(1.0 + rho);               // unit term of M_hat + rho
   const size_t fullb = (size_t)24 * Vhp * nrhs * sizeof(double2);
@@ -201,7 +206,8 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
   Field<R> HX = half_field<R>(w->hx, Vhp);
   const int method = (int)o->method;
   Field<R> NONE = {nullptr, 0, 0, 0};
-  SysScal SC = {w->gam, w->ss, w->alpha, w->beta, w->active, w->iters, w->flags};
+  const SysScal SC = {w->gam, w->ss, w->alpha, w->cs, w->active, w->iters, w->flags, w->selected, w->target2, nsys};
+  const int n1 = G.nchunk, n2 = 2 * G.nchunk;   // partials per system of sums over one / both parities
 
   // selection of systems
   for (int r = 0; r < nrhs; ++r)
@@ -213,7 +219,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
 
   // ||b||^2 per system; first residual r = b
   blas_norm2<double>(G, nrhs, B, 2, w->partA, st);
-  fin_sum(nsys, G.nchunk, w->partA, w->bnorm2, st);
+  fin_sum(nsys, {w->partA, n2}, w->bnorm2, st);
   SAP_HIP_CHECK(c, hipMemcpyAsync(w->r64, b, fullb, hipMemcpyDeviceToDevice, st));
   SAP_HIP_CHECK(c, hipMemcpyAsync(w->rnorm2, w->bnorm2, nsys * 8, hipMemcpyDeviceToDevice, st));
   SAP_HIP_CHECK(c, hipMemcpyAsync(w->h_bnorm2, w->bnorm2, nsys * 8, hipMemcpyDeviceToHost, st));
@@ -243,23 +249,22 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
     // inner right-hand side at the inner precision
     blas_convert<R, double>(G, nrhs, RIN, R64, 2, st);
     // b_hat_e = r_e + k D_eo r_o  (into S; times 1 / (1 + rho) for the series)
-    hop<R>(c, U, S, RIN, RIN, 0, nrhs, lb, colour, geom ? (Ar)shift_inv : Ar(1),
+    hop<R>(c, S, RIN, RIN, 0, nrhs, lb, colour, geom ? (Ar)shift_inv : Ar(1),
            geom ? (Ar)(kap * shift_inv) : kR, 0, 0, st);
     SAP_HIP_CHECK(c, hipMemsetAsync(w->e, 0, fullR, st));
     blas_norm2<R>(G, nrhs, S, 1, w->partB, st);
     // stop the inner solve at ||s|| <= max(inner_tol ||b_hat||, 0.3 tol ||b||): the outer
     // residual after x += e equals the inner one up to rounding
-    hipLaunchKernelGGL(k_targets, dim3(1), dim3(256), 0, st, nsys, w->partB, G.nchunk, w->bnorm2,
-                       inner_tol * inner_tol, 0.09 * tol * tol * (geom ? shift_inv * shift_inv : 1.0),
-                       w->target2);
+    fin_targets(nsys, {w->partB, n1}, w->bnorm2, inner_tol * inner_tol,
+                0.09 * tol * tol * (geom ? shift_inv * shift_inv : 1.0), w->target2, st);
     SAP_HIP_CHECK(c, hipMemsetAsync(w->flags, 0, 16, st));
     const size_t halfb = halfR;
     if (method == SAP_CG) {
       // r = M_hat^dagger s = s - k^2 g5 D_eo D_oe g5 s
-      hop<R>(c, U, T, S, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), 1, 0, st);
-      hop<R>(c, U, Rr, T, S, 0, nrhs, lb, colour, aI, k2R, 0, 1, st);
+      hop<R>(c, T, S, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), 1, 0, st);
+      hop<R>(c, Rr, T, S, 0, nrhs, lb, colour, aI, k2R, 0, 1, st);
       blas_norm2<R>(G, nrhs, Rr, 1, w->partC, st);
-      fin_init(SC, nsys, G.nchunk, w->partB, w->partC, w->selected, w->target2, st);
+      fin_init(SC, {w->partB, n1}, {w->partC, n1}, st);
       SAP_HIP_CHECK(c, hipMemcpyAsync(w->p, w->r, halfb, hipMemcpyDeviceToDevice, st));
     } else if (method == SAP_BICGSTAB) {
       // r = s = b_hat (x_e = 0), shadow residual r0 = r, p = v = 0
@@ -267,70 +272,84 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
       SAP_HIP_CHECK(c, hipMemsetAsync(w->p, 0, halfb, st));
       SAP_HIP_CHECK(c, hipMemsetAsync(w->q, 0, halfb, st));
       blas_cdot3<R>(G, nrhs, Rr, S, S, w->partA, st);
-      fin_bicg_rho(SC, w->cs, nsys, G.nchunk, w->partA, w->selected, w->target2, 1, st);
+      fin_bicg_rho(SC, 0, {w->partA, n1}, 1, st);
     } else {
       // first term t_0 = b_hat in S
-      fin_geom(SC, nsys, G.nchunk, w->partB, w->selected, w->target2, 1, st);
+      fin_geom(SC, 0, {w->partB, n1}, 1, st);
     }
     SAP_HIP_CHECK(c, hipGetLastError());
-    // the LDS-staged hop (FP32 and FP16 storage) writes the reductions of its output
-    // itself: ||M_hat p||^2 and ||M_hat^dagger s||^2 (CG), <t, s> and ||t||^2 (BiCGstab,
-    // three values per slot); FP16 sums the values before their rounding to FP16
-    int nslot = 0;
-    if ((std::is_same<R, float>::value || std::is_same<R, h16>::value) && method != SAP_GEOM &&
-        hop_map_for(c, false, prec_of<R>(), nrhs) == HOP_MAP_SLABD) {
-      nslot = slabd_norm_slots(c->g, lb ? lb : c->geom.L[0]);
-      const size_t per = method == SAP_CG ? 1 : 3;
-      if (per * nslot * nsys > w->part_cap) nslot = 0;   // no room in the partial buffers
-    }
+    // where its mapping can, the second half hop writes the reductions of its output: ||M_hat
+    // p||^2 and ||M_hat^dagger s||^2 (CG), <t, s> and ||t||^2 (BiCGstab, three values per slot),
+    // ||t||^2 (series); FP16 sums the values before their rounding to FP16
     const int nlb = lb ? lb : c->geom.L[0];
-    const int nq = nslot ? nslot : G.nchunk;
-    // iterations on all systems (no host interaction; scalars stay on the device)
+    int nslot = hop_red_slots(hop_args<R>(c, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0), nlb);
+    if ((size_t)3 * nslot * nsys > w->part_cap) nslot = 0;       // no room in the partial buffers
+    // several systems: those that have converged are skipped (version v of active)
+    auto live = [&](int v) { return nsys > 1 ? w->active + v * nsys : nullptr; };
+    // y = a x + b D in on the even sites with its reductions red in part
+    auto hop_red = [&](Field<R> y, Field<R> in, Field<R> x, Ar a, Ar b, int g5o, double* part, int red, int v,
+                       hipStream_t q) -> Parts {
+      const int nv = red == 3 ? 3 : 1;
+      hop<R>(c, y, in, x, 0, nrhs, lb, colour, a, b, 0, g5o, q,
+             nslot ? Fused{part, nlb, nslot, red, live(v)} : Fused{nullptr, 0, 0, 0, live(v)});
+      Parts r = {part, nslot};
+      if (!nslot) {
+        if (red == 3) blas_cdot3<R>(G, nrhs, y, x, y, part, q);
+        else blas_norm2<R>(G, nrhs, y, 1, part, q);
+        r.n = n1;
+      }
+      if (r.n > 4096) {      // large lattices with few systems: the consumers would add too many
+        r.n = compress_parts(nsys, nv, r, w->partE, q);
+        r.p = w->partE;
+      }
+      return r;
+    };
+    auto hop_odd = [&](Field<R> in, int g5i, int v, hipStream_t q) {
+      hop<R>(c, T, in, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), g5i, 0, q, Fused{nullptr, 0, 0, 0, live(v)});
+    };
+    // ITERS_PER_GRAPH iterations on all systems (no host interaction; the state of the systems
+    // starts and ends in version 0)
     auto iterate = [&](hipStream_t q) {
-      if (method == SAP_CG) {
-        // q = M_hat p
-        hop<R>(c, U, T, P, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), 0, 0, q);
-        hop<R>(c, U, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0, q, nslot ? w->partA : nullptr, nlb, nslot);
-        if (!nslot) blas_norm2<R>(G, nrhs, Q, 1, w->partA, q);
-        fin_alpha(SC, nsys, nq, w->partA, q);
-        // s -= alpha q (x += alpha p waits for the direction update)
-        blas_cg_s<R>(G, nrhs, S, Q, w->alpha, w->partB, q);
-        // r = M_hat^dagger s
-        hop<R>(c, U, T, S, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), 1, 0, q);
-        hop<R>(c, U, Rr, T, S, 0, nrhs, lb, colour, aI, k2R, 0, 1, q, nslot ? w->partC : nullptr, nlb, nslot);
-        if (!nslot) blas_norm2<R>(G, nrhs, Rr, 1, w->partC, q);
-        fin_beta(SC, nsys, G.nchunk, w->partB, nq, w->partC, w->target2, q);
-        // x += alpha p, p = r + beta p
-        blas_cg_xp<R>(G, nrhs, Ee, P, Rr, w->alpha, w->beta, q);
-      } else if (method == SAP_BICGSTAB) {
-        // residual r in S, shadow r0 in Rr, v in Q, t in HX
-        blas_bicg_p<R>(G, nrhs, P, S, Q, w->cs, q);
-        hop<R>(c, U, T, P, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), 0, 0, q);
-        hop<R>(c, U, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0, q);
-        blas_cdot3<R>(G, nrhs, Rr, Q, NONE, w->partB, q);
-        fin_bicg_alpha(SC, w->cs, nsys, G.nchunk, w->partB, q);
-        blas_bicg_s<R>(G, nrhs, S, Q, w->cs, w->partB, q);
-        hop<R>(c, U, T, S, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), 0, 0, q);
-        hop<R>(c, U, HX, T, S, 0, nrhs, lb, colour, aI, k2R, 0, 0, q, nslot ? w->partC : nullptr, nlb, nslot, 3);
-        if (!nslot) blas_cdot3<R>(G, nrhs, HX, S, HX, w->partC, q);
-        fin_bicg_omega(SC, w->cs, nsys, nq, w->partC, G.nchunk, w->partB, w->target2, q);
-        blas_bicg_xr<R>(G, nrhs, Ee, P, S, HX, Rr, w->cs, w->partA, q);
-        fin_bicg_rho(SC, w->cs, nsys, G.nchunk, w->partA, w->selected, w->target2, 0, q);
-      } else {
-        // two terms: S -> HX -> S (x_e += t on active systems; t <- k^2 D_eo D_oe t)
-        for (int h = 0; h < 2; ++h) {
-          Field<R> from = h == 0 ? S : HX, to = h == 0 ? HX : S;
-          blas_geom_add<R>(G, nrhs, Ee, from, w->active, q);
-          hop<R>(c, U, T, from, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), 0, 0, q);
-          hop<R>(c, U, to, T, NONE, 0, nrhs, lb, colour, Ar(0), (Ar)(kap * kap * shift_inv), 0, 0, q);
-          blas_norm2<R>(G, nrhs, to, 1, w->partA, q);
-          fin_geom(SC, nsys, G.nchunk, w->partA, w->selected, w->target2, 0, q);
+      int v = 0;
+      Parts last = {nullptr, 0};
+      for (int k = 0; k < ITERS_PER_GRAPH; ++k) {
+        if (method == SAP_CG) {
+          // q = M_hat p ; s -= alpha q (x += alpha p waits for the direction update)
+          hop_odd(P, 0, v, q);
+          const Parts qq = hop_red(Q, T, P, aI, k2R, 0, w->partA, 1, v, q);
+          blas_cg_s<R>(G, nrhs, S, Q, SC, v, qq, w->partB, q);
+          // r = M_hat^dagger s ; x += alpha p, p = r + beta p
+          hop_odd(S, 1, v, q);
+          const Parts rr = hop_red(Rr, T, S, aI, k2R, 1, w->partC, 1, v, q);
+          blas_cg_xp<R>(G, nrhs, Ee, P, Rr, SC, v, {w->partB, n1}, rr, q);
+          v ^= 1;
+        } else if (method == SAP_BICGSTAB) {
+          // residual r in S, shadow r0 in Rr, v in Q, t in HX
+          blas_bicg_p<R>(G, nrhs, P, S, Q, SC, v, last, q);
+          if (last.p) v ^= 1;
+          hop_odd(P, 0, v, q);
+          hop<R>(c, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0, q, Fused{nullptr, 0, 0, 0, live(v)});
+          blas_cdot3<R>(G, nrhs, Rr, Q, NONE, w->partB, q);
+          blas_bicg_s<R>(G, nrhs, S, Q, SC, v, {w->partB, n1}, w->partD, q);
+          v ^= 1;
+          hop_odd(S, 0, v, q);
+          const Parts ts = hop_red(HX, T, S, aI, k2R, 0, w->partC, 3, v, q);
+          blas_bicg_xr<R>(G, nrhs, Ee, P, S, HX, Rr, SC, v, ts, {w->partD, n1}, w->partA, q);
+          v ^= 1;
+          last = {w->partA, n1};
+        } else {
+          // a term: S -> HX -> S (x_e += t on active systems; t <- k^2 D_eo D_oe t)
+          const Field<R> from = k & 1 ? HX : S, to = k & 1 ? S : HX;
+          blas_geom_add<R>(G, nrhs, Ee, from, SC, v, last, q);
+          if (last.p) v ^= 1;
+          hop_odd(from, 0, v, q);
+          last = hop_red(to, T, NONE, Ar(0), (Ar)(kap * kap * shift_inv), 0, w->partA, 1, v, q);
         }
       }
+      if (method == SAP_CG) fin_count(SC, v, q);
+      else if (method == SAP_BICGSTAB) fin_bicg_rho(SC, v, last, 0, q);
+      else fin_geom(SC, v, last, 0, q);
     };
-    // iterations per graph (a geometric-series call of iterate adds two terms)
-    const int per_call = method == SAP_GEOM ? 2 : 1;
-    const int calls = ITERS_PER_GRAPH / per_call;
     hipGraphExec_t exec = nullptr;
     for (auto& g : w->graphs)
       if (g.nrhs == nrhs && g.lb == lb && g.sel == colour && g.prec == prec_of<R>() && g.method == method &&
@@ -339,7 +358,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
     if (!exec) {
       hipGraph_t graph;
       if (hipStreamBeginCapture(w->cap, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-        for (int k = 0; k < calls; ++k) iterate(w->cap);
+        iterate(w->cap);
         if (hipStreamEndCapture(w->cap, &graph) == hipSuccess) {
           if (hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) exec = nullptr;
           (void)hipGraphDestroy(graph);
@@ -360,18 +379,18 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
       if (exec) {
         SAP_HIP_CHECK(c, hipGraphLaunch(exec, st));
       } else {
-        for (int k = 0; k < calls; ++k) iterate(st);
+        iterate(st);
       }
       total_iters += ITERS_PER_GRAPH;
     }
     // e_o = r_o + k D_oe e_e ; x += e ; r = b - A x (FP64)
-    if (!eo_only) hop<R>(c, U, E, Ee, RIN, 1, nrhs, lb, colour, Ar(1), kR, 0, 0, st);
+    if (!eo_only) hop<R>(c, E, Ee, RIN, 1, nrhs, lb, colour, Ar(1), kR, 0, 0, st);
     blas_add_mixed<R>(G, nrhs, X, E, st);
     if (eo_only) {
       // A x = (M_hat + rho) x_e on the even sites, via the odd half of AX
       const Field<double> NONE64 = {nullptr, 0, 0};
-      hop<double>(c, gauge_of<double>(c), AX, X, NONE64, 1, nrhs, lb, colour, 0.0, 1.0, 0, 0, st);
-      hop<double>(c, gauge_of<double>(c), AX, AX, X, 0, nrhs, lb, colour, 1.0 + rho, -kap * kap, 0, 0, st);
+      hop<double>(c, AX, X, NONE64, 1, nrhs, lb, colour, 0.0, 1.0, 0, 0, st);
+      hop<double>(c, AX, AX, X, 0, nrhs, lb, colour, 1.0 + rho, -kap * kap, 0, 0, st);
       blas_resid(G, nrhs, R64, B, AX, w->partA, st, 1);
     } else {
       int rc = apply_op_any(c, w->ax, x, nrhs, lb, colour < 3 ? colour : 0, colour < 3 ? -1 : colour - 3,
@@ -379,7 +398,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
       if (rc) return rc;
       blas_resid(G, nrhs, R64, B, AX, w->partA, st);
     }
-    fin_sum(nsys, G.nchunk, w->partA, w->rnorm2, st);
+    fin_sum(nsys, {w->partA, eo_only ? n1 : n2}, w->rnorm2, st);
     SAP_HIP_CHECK(c, hipGetLastError());
   }
   if (info) {
@@ -553,7 +572,7 @@ static SapWS* sap_ws(sap_ctx* c) {
   a->nrhs_cap = n;
   const size_t fb = (size_t)24 * c->Vhp * n * sizeof(double2);
   const size_t nsys = 2 * (size_t)n;
-  const size_t nchunk = (size_t)((c->Vh + CHUNK - 1) / CHUNK);
+  const size_t nchunk = (size_t)((c->Vh + TILE - 1) / TILE);
   bool ok = true;
   double2** fields[] = {&a->r, &a->r0, &a->p, &a->v, &a->t, &a->ph, &a->sh, &a->kx, &a->kr, &a->ky, &a->mt,
                         &a->g1, &a->g2};
@@ -580,7 +599,7 @@ static int sap_bicgstab(sap_ctx* c, double* x, const double* b, int nrhs, const 
   SapWS* a = sap_ws(c);
   if (!a) return sap_fail(c, SAP_E_NOMEM, "cannot allocate the Schwarz-preconditioned BiCGstab workspace");
   const long long Vhp = c->Vhp;
-  const SysGrid G = make_sysgrid(c->Vh, c->g.V3h, 0, c->geom.L[0], 0);   // full lattice, one block
+  const SysGrid G = make_sysgrid(c->Vh, c->g.V3h, 0, c->geom.L[0], 0, 2 * nrhs);   // full lattice, one block
   const int nh = 2 * nrhs;                                                 // half-field systems
   auto H = [&](double2* f) { return Field<double>{f, 12 * Vhp, 0}; };
   const Field<double> NONE = {nullptr, 0, 0};
@@ -591,7 +610,7 @@ static int sap_bicgstab(sap_ctx* c, double* x, const double* b, int nrhs, const 
 
   // per-rhs sums of the three partials (parities added): s3[r] = (<q, y>, ||y||^2)
   auto sums = [&](std::vector<zd>& dot, std::vector<double>& nrm) -> int {
-    fin_sum3(nh, G.nchunk, a->part, a->dev3, st);
+    fin_sum3(nh, {a->part, G.nchunk}, a->dev3, st);
     SAP_HIP_CHECK(c, hipMemcpyAsync(a->h3, a->dev3, 3 * nh * 8, hipMemcpyDeviceToHost, st));
     SAP_HIP_CHECK(c, hipStreamSynchronize(st));
     for (int r = 0; r < nrhs; ++r) {
@@ -669,13 +688,13 @@ static int sap_bicgstab(sap_ctx* c, double* x, const double* b, int nrhs, const 
           const Field<double> NONE64 = {nullptr, 0, 0, 0};
           const double kap = c->geom.kappa;
           const int lb = c->geom.l0;
-          hop<double>(c, gauge_of<double>(c), BH, RHS, RHS, 0, nrhs, lb, colour, 1.0, kap, 0, 0, st);
-          hop<double>(c, gauge_of<double>(c), Y, RHS, RHS, 0, nrhs, lb, colour, 1.0, kap, 0, 0, st);
+          hop<double>(c, BH, RHS, RHS, 0, nrhs, lb, colour, 1.0, kap, 0, 0, st);
+          hop<double>(c, Y, RHS, RHS, 0, nrhs, lb, colour, 1.0, kap, 0, 0, st);
           for (int n = 1; n < o->sap_block_terms; ++n) {
-            hop<double>(c, gauge_of<double>(c), Z, Y, NONE64, 1, nrhs, lb, colour, 0.0, 1.0, 0, 0, st);
-            hop<double>(c, gauge_of<double>(c), Y, Z, BH, 0, nrhs, lb, colour, 1.0, kap * kap, 0, 0, st);
+            hop<double>(c, Z, Y, NONE64, 1, nrhs, lb, colour, 0.0, 1.0, 0, 0, st);
+            hop<double>(c, Y, Z, BH, 0, nrhs, lb, colour, 1.0, kap * kap, 0, 0, st);
           }
-          hop<double>(c, gauge_of<double>(c), Y, Y, RHS, 1, nrhs, lb, colour, 1.0, kap, 0, 0, st);
+          hop<double>(c, Y, Y, RHS, 1, nrhs, lb, colour, 1.0, kap, 0, 0, st);
           SAP_HIP_CHECK(c, hipGetLastError());
         } else {
           int rc = o->inner_prec == SAP_F64

@@ -206,6 +206,7 @@ __global__ __launch_bounds__(512) void hop_split_kernel(HopArgs<R> A, SplitGeo q
     valid = off < q.Vb;
     j = blk * q.Vb + (valid ? off : q.Vb - 1);
   }
+  if (A.active && !A.active[rhs * q.nblk + blk]) return;         // whole workgroup
   bool sel = true;
   if (A.slb) sel = A.block >= 0 ? blk == A.block : block_sel(blk, 1, -1, A.colour);
 
