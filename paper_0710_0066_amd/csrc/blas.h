@@ -14,6 +14,8 @@ struct SysGrid {
   int per;          // sites per workgroup of the BLAS kernels, a multiple of 64
   int nchunk;       // ceil(Vb / per)
   int colour;
+  int nrhs;
+  bool xcd;         // fields of a few MB: workgroups in the order of the split hop
   long long Vh;
   long long Vhp;     // storage sites per parity (locates the site norms of FP16 fields)
 };
@@ -33,6 +35,7 @@ struct SysScal {
   const int* selected;
   const double* target2;
   int nsys;
+  int rev = 0;          // walk the systems' sites backwards
 };
 
 // partial sums: n per system (of one value, or of three interleaved), system-major
@@ -54,6 +57,8 @@ inline SysGrid make_sysgrid(long long Vh, int V3h, int lb, int L0, int colour, i
   G.per = TILE * (int)std::max(std::min(16LL, std::max(f16 ? 4LL : 1LL, tiles / 1024)), (G.Vb / TILE + 1023) / 1024);
   G.nchunk = (int)((G.Vb + G.per - 1) / G.per);
   G.colour = lb ? colour : 0;
+  G.nrhs = nrhs;
+  G.xcd = Vh * nrhs > 25000 && Vh * nrhs <= 200000;
   G.Vh = Vh;
   G.Vhp = (Vh + TILE - 1) / TILE * TILE;
   return G;

@@ -368,5 +368,11 @@ __device__ __forceinline__ long long xcd_logical_block(long long w, long long nw
   if ((nwg & 7) != 0) return w;
   return (w & 7) * (nwg >> 3) + (w >> 3);
 }
+// the same on 32-bit ids; rev: each XCD walks its range backwards
+__device__ __forceinline__ int xcd_block(int w, int nwg, bool rev) {
+  if ((nwg & 7) != 0) return w;
+  const int per = nwg >> 3, i = w >> 3;
+  return (w & 7) * per + (rev ? per - 1 - i : i);
+}
 
 }  // namespace sap

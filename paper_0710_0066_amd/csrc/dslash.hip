@@ -1942,12 +1942,16 @@ template <class R> static void launch_stream(const HopArgs<R>& A, hipStream_t st
 // while the input stays within 200 MB (the MALL holds 256 MB); the FP32 half hop (24^3x48,
 // 12 rhs: 329 / 309) always, the FP64 one (16^3x32, 12 rhs: 117 / 99; 24^3x48, 12 rhs:
 // 625 / 655) up to twice that input. Slices of fewer than 16 chunks of 64 sites leave some
-// of the 8 XCDs idle or short in this order and run in the linear one.
+// of the 8 XCDs idle or short in this order and run in the linear one, and so do fields that
+// are read again from the XCDs' 32 MB of L2 when consecutive kernels give an XCD the same
+// sites (FP32 CG on 16^3x32: half hops 8.4 and 9.2 us marching, 7.7 and 8.2 linear and
+// alternating in direction). Launches on some of the blocks only march all the same: the
+// linear order gives each XCD a range of slices, which may hold no selected block.
 template <class R> static int march1_order(const HopArgs<R>& A) {
   const bool full = A.parity_out < 0, f32 = std::is_same<R, float>::value;
   const double in = 2.0 * A.g.Vh * A.nrhs * 24 * sizeof(R);      // bytes of the whole input field
-  if ((!full && f32) || in <= (full ? 200e6 : 400e6)) return A.g.V3h >= 16 * TILE ? 1 : 0;
-  return -1;
+  if (!((!full && f32) || in <= (full ? 200e6 : 400e6))) return -1;
+  return A.g.V3h >= 16 * TILE && (full || in > 27e6 || split_partial(A)) ? 1 : 0;
 }
 template <class R> static void launch_march1(const HopArgs<R>& A, hipStream_t st) {
   const int order = march1_order(A);

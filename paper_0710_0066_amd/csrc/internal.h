@@ -74,6 +74,7 @@ template <class R> struct HopArgs {
   int nlb = 0, nslot = 0, red = 0;
   // optional: nonzero where a system is still iterated; the others may be left as they are
   const int* active = nullptr;
+  int rev = 0;             // split kernel, linear order: walk the lattice backwards
 };
 
 // Work-item mappings of the hop kernel for several right-hand sides.

@@ -16,7 +16,7 @@
 // partial sums (blas.hip), so that a CG iteration is six launches with the norms written by
 // the hops; converged systems are frozen while the others continue; the host reads one
 // counter every few iterations. On 16^3x32 with one rhs and FP32 inner iterations an
-// iteration went from 93 us in ten launches to 58 us.
+// iteration went from 93 us in ten launches to 54 us.
 // Outer loop: FP64 defect correction r = b - A x (A applied in FP64), inner solve in
 // FP32 or FP64, x += e, until ||b - A x|| / ||b|| <= tol recomputed in FP64.
 #include <algorithm>
@@ -134,6 +134,7 @@ struct Fused {
   double* part = nullptr;
   int nlb = 0, nslot = 0, red = 0;
   const int* active = nullptr;
+  int rev = 0;
 };
 
 // out = a*x + b*D(in) on one parity or both, block-restricted
@@ -168,6 +169,7 @@ void hop(sap_ctx* c, Field<R> out, Field<R> in, Field<R> x, int parity_out, int 
   A.nslot = f.nslot;
   A.red = f.red;
   A.active = f.active;
+  A.rev = f.rev;
   launch_hop<R>(A, st);
 }
 
@@ -287,11 +289,20 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
     // several systems: those that have converged are skipped (version v of active)
     auto live = [&](int v) { return nsys > 1 ? w->active + v * nsys : nullptr; };
     // y = a x + b D in on the even sites with its reductions red in part
+    // consecutive kernels walk the lattice in opposite directions, so that each begins with
+    // what the one before left in the caches
+    int dir = 0;
+    auto turn = [&] { return dir ^= 1; };
+    auto turned = [&] {
+      SysScal t = SC;
+      t.rev = turn();
+      return t;
+    };
     auto hop_red = [&](Field<R> y, Field<R> in, Field<R> x, Ar a, Ar b, int g5o, double* part, int red, int v,
                        hipStream_t q) -> Parts {
       const int nv = red == 3 ? 3 : 1;
       hop<R>(c, y, in, x, 0, nrhs, lb, colour, a, b, 0, g5o, q,
-             nslot ? Fused{part, nlb, nslot, red, live(v)} : Fused{nullptr, 0, 0, 0, live(v)});
+             nslot ? Fused{part, nlb, nslot, red, live(v), turn()} : Fused{nullptr, 0, 0, 0, live(v), turn()});
       Parts r = {part, nslot};
       if (!nslot) {
         if (red == 3) blas_cdot3<R>(G, nrhs, y, x, y, part, q);
@@ -305,7 +316,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
       return r;
     };
     auto hop_odd = [&](Field<R> in, int g5i, int v, hipStream_t q) {
-      hop<R>(c, T, in, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), g5i, 0, q, Fused{nullptr, 0, 0, 0, live(v)});
+      hop<R>(c, T, in, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), g5i, 0, q, Fused{nullptr, 0, 0, 0, live(v), turn()});
     };
     // ITERS_PER_GRAPH iterations on all systems (no host interaction; the state of the systems
     // starts and ends in version 0)
@@ -317,30 +328,30 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
           // q = M_hat p ; s -= alpha q (x += alpha p waits for the direction update)
           hop_odd(P, 0, v, q);
           const Parts qq = hop_red(Q, T, P, aI, k2R, 0, w->partA, 1, v, q);
-          blas_cg_s<R>(G, nrhs, S, Q, SC, v, qq, w->partB, q);
+          blas_cg_s<R>(G, nrhs, S, Q, turned(), v, qq, w->partB, q);
           // r = M_hat^dagger s ; x += alpha p, p = r + beta p
           hop_odd(S, 1, v, q);
           const Parts rr = hop_red(Rr, T, S, aI, k2R, 1, w->partC, 1, v, q);
-          blas_cg_xp<R>(G, nrhs, Ee, P, Rr, SC, v, {w->partB, n1}, rr, q);
+          blas_cg_xp<R>(G, nrhs, Ee, P, Rr, turned(), v, {w->partB, n1}, rr, q);
           v ^= 1;
         } else if (method == SAP_BICGSTAB) {
           // residual r in S, shadow r0 in Rr, v in Q, t in HX
-          blas_bicg_p<R>(G, nrhs, P, S, Q, SC, v, last, q);
+          blas_bicg_p<R>(G, nrhs, P, S, Q, turned(), v, last, q);
           if (last.p) v ^= 1;
           hop_odd(P, 0, v, q);
-          hop<R>(c, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0, q, Fused{nullptr, 0, 0, 0, live(v)});
+          hop<R>(c, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0, q, Fused{nullptr, 0, 0, 0, live(v), turn()});
           blas_cdot3<R>(G, nrhs, Rr, Q, NONE, w->partB, q);
-          blas_bicg_s<R>(G, nrhs, S, Q, SC, v, {w->partB, n1}, w->partD, q);
+          blas_bicg_s<R>(G, nrhs, S, Q, turned(), v, {w->partB, n1}, w->partD, q);
           v ^= 1;
           hop_odd(S, 0, v, q);
           const Parts ts = hop_red(HX, T, S, aI, k2R, 0, w->partC, 3, v, q);
-          blas_bicg_xr<R>(G, nrhs, Ee, P, S, HX, Rr, SC, v, ts, {w->partD, n1}, w->partA, q);
+          blas_bicg_xr<R>(G, nrhs, Ee, P, S, HX, Rr, turned(), v, ts, {w->partD, n1}, w->partA, q);
           v ^= 1;
           last = {w->partA, n1};
         } else {
           // a term: S -> HX -> S (x_e += t on active systems; t <- k^2 D_eo D_oe t)
           const Field<R> from = k & 1 ? HX : S, to = k & 1 ? S : HX;
-          blas_geom_add<R>(G, nrhs, Ee, from, SC, v, last, q);
+          blas_geom_add<R>(G, nrhs, Ee, from, turned(), v, last, q);
           if (last.p) v ^= 1;
           hop_odd(from, 0, v, q);
           last = hop_red(to, T, NONE, Ar(0), (Ar)(kap * kap * shift_inv), 0, w->partA, 1, v, q);
@@ -599,7 +610,8 @@ static int sap_bicgstab(sap_ctx* c, double* x, const double* b, int nrhs, const 
   SapWS* a = sap_ws(c);
   if (!a) return sap_fail(c, SAP_E_NOMEM, "cannot allocate the Schwarz-preconditioned BiCGstab workspace");
   const long long Vhp = c->Vhp;
-  const SysGrid G = make_sysgrid(c->Vh, c->g.V3h, 0, c->geom.L[0], 0, 2 * nrhs);   // full lattice, one block
+  SysGrid G = make_sysgrid(c->Vh, c->g.V3h, 0, c->geom.L[0], 0, 2 * nrhs);
+  G.xcd = false;   // full lattice, one block
   const int nh = 2 * nrhs;                                                 // half-field systems
   auto H = [&](double2* f) { return Field<double>{f, 12 * Vhp, 0}; };
   const Field<double> NONE = {nullptr, 0, 0};

@@ -18,6 +18,11 @@ struct SplitGeo {
   FastDiv d3, d2, d1, dv, db;
 };
 
+// does the launch leave out some of the x0 blocks?
+template <class R> inline bool split_partial(const HopArgs<R>& A) {
+  return A.slb && (A.block >= 0 || A.colour != 0);
+}
+
 // 64-site workgroups of one system of nlb x0 slices (0: the full lattice): the partials of
 // its fused reductions
 int split_chunks(const Geo& g, int nlb, bool march);

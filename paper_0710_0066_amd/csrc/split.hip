@@ -192,7 +192,7 @@ __global__ __launch_bounds__(512) void hop_split_kernel(HopArgs<R> A, SplitGeo q
     valid = off < g.V3h;
     j = x * g.V3h + (valid ? off : g.V3h - 1);
   } else {
-    int w = (int)xcd_logical_block(blockIdx.x, gridDim.x);
+    int w = xcd_block(blockIdx.x, gridDim.x, A.rev != 0);
     rhs = w % A.nrhs;
     w /= A.nrhs;
     if (FULL) {
@@ -361,7 +361,10 @@ template <class R> void launch_split(const HopArgs<R>& A, bool march, hipStream_
   q.dv = fast_div(g.V3h);
   q.db = fast_div(A.lb ? A.lb : 1);
   const long long per = (long long)A.nrhs * (full ? 2 : 1);
-  const long long n = march ? 8 * per * g.L0 * q.npiece : (per * q.nblk * q.nchunk + 7) / 8 * 8;
+  // linear order: a multiple of 8 workgroups gives each XCD a range of the lattice; where some
+  // x0 blocks are left out, one more than that deals the workgroups over the XCDs one by one
+  const long long n8 = (per * q.nblk * q.nchunk + 7) / 8 * 8;
+  const long long n = march ? 8 * per * g.L0 * q.npiece : split_partial(A) ? n8 + 1 : n8;
   const dim3 grid((unsigned)n), blk(512);
 #define SAP_SPLIT(FULL, RED)                                                                             \
   do {                                                                                                   \
