@@ -323,6 +323,28 @@ int kinetic_host(sap_ctx* c, const double* P, double* K, hipStream_t s) {
 void links_changed(sap_ctx* c, hipStream_t s) { launch_gauge_to_f32(c->g, c->U64c, c->U32, c->U16, c->U64, s); }
 LinkCopies copies_of(sap_ctx* c) { return LinkCopies{c->U64c, c->U32, c->U16}; }
 
+// Momentum kicks of both integrators. The forces depend on the links only, so kicks between
+// two link moves commute and add: p -= dt_1 F_j, p -= dt_2 F_j is p -= (dt_1 + dt_2) F_j. A
+// kick of level j is therefore only noted here, and the moves (and the trajectory's end)
+// apply what is due, one force evaluation per level: the last kick of a step, the first of
+// the next and those of the levels around them share it. Of the 6 pseudo-fermion kicks of
+// two Sexton-Weingarten steps 5 are evaluated, of the 12 level-1 kicks of four such steps
+// in two level-2 leap-frog steps 9.
+template <int N> struct Kicks {
+  double due[N] = {};
+  void add(int j, double dt) { due[j] += dt; }
+  // f(j, dt) for every level with a kick due
+  template <class F> int apply(F f) {
+    for (int j = 0; j < N; ++j) {
+      const double dt = due[j];
+      due[j] = 0.0;
+      if (dt != 0.0)
+        if (int rc = f(j, dt)) return rc;
+    }
+    return SAP_OK;
+  }
+};
+
 // ---- the two-level integrator --------------------------------------------------------
 struct Traj {
   sap_ctx* c;
@@ -330,6 +352,7 @@ struct Traj {
   const double2 *phi1, *chi;
   hipStream_t s;
   const double* sx;    // per-link step scale (device) or null
+  Kicks<2> kicks;      // 0: gauge action, 1: pseudo-fermion action
 };
 
 int kick_pf(Traj& T, double dt) {
@@ -342,7 +365,11 @@ int kick_g(Traj& T, double dt) {
   SAP_HIP_CHECK(T.c, hipGetLastError());
   return SAP_OK;
 }
+int kicks_due(Traj& T) {
+  return T.kicks.apply([&](int j, double dt) { return j ? kick_pf(T, dt) : kick_g(T, dt); });
+}
 int move_links(Traj& T, double dt) {
+  if (int rc = kicks_due(T)) return rc;
   launch_update_links(T.c->g, T.c->U64, copies_of(T.c), fws(T.c)->mom, dt, T.s, T.sx);   // copies too
   SAP_HIP_CHECK(T.c, hipGetLastError());
   return SAP_OK;
@@ -352,11 +379,15 @@ int step0(Traj& T, double dt) {
   int rc;
   const double l = T.P->lambda;
   if (T.P->scheme_inner == 0) {
-    if ((rc = kick_g(T, 0.5 * dt)) || (rc = move_links(T, dt)) || (rc = kick_g(T, 0.5 * dt))) return rc;
+    T.kicks.add(0, 0.5 * dt);
+    if ((rc = move_links(T, dt))) return rc;
+    T.kicks.add(0, 0.5 * dt);
   } else {
-    if ((rc = kick_g(T, l * dt)) || (rc = move_links(T, 0.5 * dt)) || (rc = kick_g(T, (1 - 2 * l) * dt)) ||
-        (rc = move_links(T, 0.5 * dt)) || (rc = kick_g(T, l * dt)))
-      return rc;
+    T.kicks.add(0, l * dt);
+    if ((rc = move_links(T, 0.5 * dt))) return rc;
+    T.kicks.add(0, (1 - 2 * l) * dt);
+    if ((rc = move_links(T, 0.5 * dt))) return rc;
+    T.kicks.add(0, l * dt);
   }
   return SAP_OK;
 }
@@ -366,18 +397,20 @@ int step1(Traj& T, double dt) {
   const int n = T.P->n_inner;
   const double d0 = dt / n, l = T.P->lambda;
   if (T.P->scheme_outer == 0) {
-    if ((rc = kick_pf(T, 0.5 * dt))) return rc;
+    T.kicks.add(1, 0.5 * dt);
     for (int i = 0; i < n; ++i)
       if ((rc = step0(T, d0))) return rc;
-    return kick_pf(T, 0.5 * dt);
+    T.kicks.add(1, 0.5 * dt);
+    return SAP_OK;
   }
-  if ((rc = kick_pf(T, l * dt))) return rc;
+  T.kicks.add(1, l * dt);
   for (int i = 0; i < n / 2; ++i)
     if ((rc = step0(T, d0))) return rc;
-  if ((rc = kick_pf(T, (1 - 2 * l) * dt))) return rc;
+  T.kicks.add(1, (1 - 2 * l) * dt);
   for (int i = 0; i < n / 2; ++i)
     if ((rc = step0(T, d0))) return rc;
-  return kick_pf(T, l * dt);
+  T.kicks.add(1, l * dt);
+  return SAP_OK;
 }
 
 int hamiltonian(Traj& T, double* K, double* SG, double* SW, double* SR) {
@@ -406,6 +439,7 @@ struct Traj4 {
   const double2 *phi1, *phi2, *chi3, *chi4;
   hipStream_t s;
   const double* sx;
+  Kicks<5> kicks;
 };
 
 // T_P of level j: p -= dt F_j (0 gauge, 1 S1, 2 S2, 3 S3, 4 S4)
@@ -425,7 +459,12 @@ int kick4(Traj4& T, int j, double dt) {
   }
 }
 
+int kicks_due(Traj4& T) {
+  return T.kicks.apply([&](int j, double dt) { return kick4(T, j, dt); });
+}
+
 int move4(Traj4& T, double dt) {
+  if (int rc = kicks_due(T)) return rc;
   launch_update_links(T.c->g, T.c->U64, copies_of(T.c), fws(T.c)->mom, dt, T.s, T.sx);   // copies too
   SAP_HIP_CHECK(T.c, hipGetLastError());
   return SAP_OK;
@@ -445,12 +484,17 @@ int step4(Traj4& T, int j, double dt) {
     return SAP_OK;
   };
   if (T.P->scheme[j] == 0) {
-    if ((rc = kick4(T, j, 0.5 * dt)) || (rc = inner(n, dt))) return rc;
-    return kick4(T, j, 0.5 * dt);
+    T.kicks.add(j, 0.5 * dt);
+    if ((rc = inner(n, dt))) return rc;
+    T.kicks.add(j, 0.5 * dt);
+    return SAP_OK;
   }
-  if ((rc = kick4(T, j, l * dt)) || (rc = inner(n / 2, 0.5 * dt))) return rc;
-  if ((rc = kick4(T, j, (1 - 2 * l) * dt)) || (rc = inner(n / 2, 0.5 * dt))) return rc;
-  return kick4(T, j, l * dt);
+  T.kicks.add(j, l * dt);
+  if ((rc = inner(n / 2, 0.5 * dt))) return rc;
+  T.kicks.add(j, (1 - 2 * l) * dt);
+  if ((rc = inner(n / 2, 0.5 * dt))) return rc;
+  T.kicks.add(j, l * dt);
+  return SAP_OK;
 }
 
 int hamiltonian4(Traj4& T, double* K, double S[5]) {
@@ -676,13 +720,14 @@ int hmc_trajectory(sap_ctx* c, double* U, const sap_hmc_params* P, sap_hmc_info*
   if ((rc = sap_pack_spinor(c, w->f[0], P->xi2, 1, SAP_F64, stream))) return rc;
   if ((rc = heat_bath(c, chi, w->f[0], &P->action_solve, s))) goto fail;
   {
-    Traj T = {c, P, phi1, chi, s, P->step_scale ? w->sx : nullptr};
+    Traj T = {c, P, phi1, chi, s, P->step_scale ? w->sx : nullptr, {}};
     double K0, K1;
     if ((rc = hamiltonian(T, &K0, &info->S_G0, &info->S_W0, &info->S_R0))) goto fail;
     info->H0 = K0 + info->S_G0 + info->S_W0 + info->S_R0;
     const double dt = P->tau / P->n_outer;
     for (int k = 0; k < P->n_outer; ++k)
       if ((rc = step1(T, dt))) goto fail;
+    if ((rc = kicks_due(T))) goto fail;
     if ((rc = hamiltonian(T, &K1, &info->S_G1, &info->S_W1, &info->S_R1))) goto fail;
     info->H1 = K1 + info->S_G1 + info->S_W1 + info->S_R1;
     info->dH = info->H1 - info->H0;
@@ -750,7 +795,7 @@ int hmc_trajectory_4pf(sap_ctx* c, double* U, const sap_hmc4_params* P, sap_hmc4
       (rc = heat_bath(c, chi4, stage, action_opts4(P, 4), s, 0)))
     goto fail;
   {
-    Traj4 T = {c, P, phi1, phi2, chi3, chi4, s, P->step_scale ? w->sx : nullptr};
+    Traj4 T = {c, P, phi1, phi2, chi3, chi4, s, P->step_scale ? w->sx : nullptr, {}};
     double K0, K1;
     if ((rc = hamiltonian4(T, &K0, info->S0))) goto fail;
     info->H0 = K0;
@@ -758,6 +803,7 @@ int hmc_trajectory_4pf(sap_ctx* c, double* U, const sap_hmc4_params* P, sap_hmc4
     const double dt = P->tau / P->n[4];
     for (int k = 0; k < P->n[4]; ++k)
       if ((rc = step4(T, 4, dt))) goto fail;
+    if ((rc = kicks_due(T))) goto fail;
     if ((rc = hamiltonian4(T, &K1, info->S1))) goto fail;
     info->H1 = K1;
     for (int j = 0; j < 5; ++j) info->H1 += info->S1[j];
