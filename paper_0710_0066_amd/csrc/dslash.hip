@@ -1959,6 +1959,11 @@ template <class R> static void launch_march1(const HopArgs<R>& A, hipStream_t st
   else launch_march<R, 1>(A, st);
 }
 
+template <class R> bool hop_is_split(const HopArgs<R>& A) {
+  return A.map == HOP_MAP_SITE || (A.map == HOP_MAP_MARCH1 && march1_order(A) >= 0);
+}
+template bool hop_is_split<double>(const HopArgs<double>&);
+
 template <class R> int hop_red_slots(const HopArgs<R>& A, int nlb) {
   if (A.map == HOP_MAP_SLABD && std::is_same<R, float>::value) return slabd_norm_slots(A.g, nlb);
   if (A.map == HOP_MAP_SITE) return split_chunks(A.g, nlb, false);

@@ -74,6 +74,7 @@ template <class R> struct HopArgs {
   int nlb = 0, nslot = 0, red = 0;
   // optional: nonzero where a system is still iterated; the others may be left as they are
   const int* active = nullptr;
+  int keep = 0;            // split kernel: leave unselected sites as they are (else zero)
   int rev = 0;             // split kernel, linear order: walk the lattice backwards
 };
 
@@ -108,6 +109,8 @@ constexpr int HOP_WALK_T = 8;   // slices per walk
 template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t s);
 // mapping of an untuned context for the full operator or the half hop (prec: sap_prec)
 int hop_default_map(const Geo& g, bool full, int prec, int nrhs);
+// does the launch A run the split kernel?
+template <class R> bool hop_is_split(const HopArgs<R>& A);
 // partials per system of nlb slices that the half hop A (its mapping, precision, lattice and
 // rhs) can write of its output (HopArgs::npart); 0: its mapping has none
 template <class R> int hop_red_slots(const HopArgs<R>& A, int nlb);

@@ -134,7 +134,7 @@ struct Fused {
   double* part = nullptr;
   int nlb = 0, nslot = 0, red = 0;
   const int* active = nullptr;
-  int rev = 0;
+  int keep = 0, rev = 0;
 };
 
 // out = a*x + b*D(in) on one parity or both, block-restricted
@@ -169,6 +169,7 @@ void hop(sap_ctx* c, Field<R> out, Field<R> in, Field<R> x, int parity_out, int 
   A.nslot = f.nslot;
   A.red = f.red;
   A.active = f.active;
+  A.keep = f.keep;
   A.rev = f.rev;
   launch_hop<R>(A, st);
 }
@@ -302,7 +303,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
                        hipStream_t q) -> Parts {
       const int nv = red == 3 ? 3 : 1;
       hop<R>(c, y, in, x, 0, nrhs, lb, colour, a, b, 0, g5o, q,
-             nslot ? Fused{part, nlb, nslot, red, live(v), turn()} : Fused{nullptr, 0, 0, 0, live(v), turn()});
+             nslot ? Fused{part, nlb, nslot, red, live(v), 0, turn()} : Fused{nullptr, 0, 0, 0, live(v), 0, turn()});
       Parts r = {part, nslot};
       if (!nslot) {
         if (red == 3) blas_cdot3<R>(G, nrhs, y, x, y, part, q);
@@ -316,7 +317,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
       return r;
     };
     auto hop_odd = [&](Field<R> in, int g5i, int v, hipStream_t q) {
-      hop<R>(c, T, in, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), g5i, 0, q, Fused{nullptr, 0, 0, 0, live(v), turn()});
+      hop<R>(c, T, in, NONE, 1, nrhs, lb, colour, Ar(0), Ar(1), g5i, 0, q, Fused{nullptr, 0, 0, 0, live(v), 0, turn()});
     };
     // ITERS_PER_GRAPH iterations on all systems (no host interaction; the state of the systems
     // starts and ends in version 0)
@@ -339,7 +340,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
           blas_bicg_p<R>(G, nrhs, P, S, Q, turned(), v, last, q);
           if (last.p) v ^= 1;
           hop_odd(P, 0, v, q);
-          hop<R>(c, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0, q, Fused{nullptr, 0, 0, 0, live(v), turn()});
+          hop<R>(c, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0, q, Fused{nullptr, 0, 0, 0, live(v), 0, turn()});
           blas_cdot3<R>(G, nrhs, Rr, Q, NONE, w->partB, q);
           blas_bicg_s<R>(G, nrhs, S, Q, turned(), v, {w->partB, n1}, w->partD, q);
           v ^= 1;
@@ -551,11 +552,14 @@ int sap::check_solve_opts(sap_ctx* c, const sap_solve_opts* o) {
 //
 // A full FP64 field [rhs][parity][tiles] is read as 2 * nrhs half fields of stride 12 Vhp,
 // so the per-system BLAS kernels apply; the host adds the two parities of every sum.
+constexpr int COEF_SLOTS = 8;
+
 struct SapWS {
   int nrhs_cap;
   double2 *r, *r0, *p, *v, *t, *ph, *sh, *kx, *kr, *ky, *mt;
   double2 *g1, *g2;     // series block solves: b_hat (even half), D_oe y (odd half)
-  double *part, *dev3, *coef;
+  double *part, *dev3, *coef;   // coef, hcoef: COEF_SLOTS sets of coefficients, used in turn
+  int slot;
   double *ck_res, *ck_add;   // device coefficients of the preconditioner's two fixed updates
   double *h3, *hcoef;
 };
@@ -590,11 +594,11 @@ static SapWS* sap_ws(sap_ctx* c) {
   for (double2** f : fields) ok = ok && hipMalloc((void**)f, fb) == hipSuccess;
   ok = ok && hipMalloc((void**)&a->part, 3 * nsys * nchunk * 8) == hipSuccess;
   ok = ok && hipMalloc((void**)&a->dev3, 3 * nsys * 8) == hipSuccess;
-  ok = ok && hipMalloc((void**)&a->coef, 6 * nsys * 8) == hipSuccess;
+  ok = ok && hipMalloc((void**)&a->coef, COEF_SLOTS * 6 * nsys * 8) == hipSuccess;
   ok = ok && hipMalloc((void**)&a->ck_res, 6 * nsys * 8) == hipSuccess;
   ok = ok && hipMalloc((void**)&a->ck_add, 6 * nsys * 8) == hipSuccess;
   ok = ok && hipHostMalloc((void**)&a->h3, 3 * nsys * 8, 0) == hipSuccess;
-  ok = ok && hipHostMalloc((void**)&a->hcoef, 12 * nsys * 8, 0) == hipSuccess;   // two coefficient sets
+  ok = ok && hipHostMalloc((void**)&a->hcoef, COEF_SLOTS * 6 * nsys * 8, 0) == hipSuccess;
   if (!ok) {
     sap_ws_free(a);
     return nullptr;
@@ -632,21 +636,23 @@ static int sap_bicgstab(sap_ctx* c, double* x, const double* b, int nrhs, const 
     }
     return SAP_OK;
   };
-  // y = c0 y + c1 u + c2 w on every rhs (coefficients per rhs, copied to both parities)
+  // y = c0 y + c1 u + c2 w on every rhs (coefficients per rhs, copied to both parities). An
+  // iteration uses four sets of coefficients and waits for its sums after the fourth, so that a
+  // set has been consumed long before its slot is written again.
   auto lin3 = [&](double2* y, const double2* u, const double2* w, const double2* q, const std::vector<zd>& c0,
                   const std::vector<zd>& c1, const std::vector<zd>& c2, bool want) -> int {
+    const size_t o = (size_t)6 * nh * a->slot;
+    a->slot = (a->slot + 1) % COEF_SLOTS;
     for (int r = 0; r < nrhs; ++r)
       for (int par = 0; par < 2; ++par) {
-        double* cf = a->hcoef + 6 * (2 * r + par);
+        double* cf = a->hcoef + o + 6 * (2 * r + par);
         cf[0] = c0[r].real(); cf[1] = c0[r].imag();
         cf[2] = c1[r].real(); cf[3] = c1[r].imag();
         cf[4] = c2[r].real(); cf[5] = c2[r].imag();
       }
-    SAP_HIP_CHECK(c, hipMemcpyAsync(a->coef, a->hcoef, 6 * nh * 8, hipMemcpyHostToDevice, st));
-    blas_lin3<double>(G, nh, H(y), H((double2*)u), w ? H((double2*)w) : NONE, q ? H((double2*)q) : NONE, a->coef,
+    SAP_HIP_CHECK(c, hipMemcpyAsync(a->coef + o, a->hcoef + o, 6 * nh * 8, hipMemcpyHostToDevice, st));
+    blas_lin3<double>(G, nh, H(y), H((double2*)u), w ? H((double2*)w) : NONE, q ? H((double2*)q) : NONE, a->coef + o,
                       want ? a->part : nullptr, st);
-    // the host buffer is rewritten by the next call: wait until the copy has been consumed
-    SAP_HIP_CHECK(c, hipStreamSynchronize(st));
     return SAP_OK;
   };
   auto cdot = [&](const double2* q, const double2* y, const double2* z, std::vector<zd>& dot,
@@ -678,49 +684,76 @@ static int sap_bicgstab(sap_ctx* c, double* x, const double* b, int nrhs, const 
   SAP_HIP_CHECK(c, hipMemcpyAsync(a->ck_res, a->hcoef, 6 * nh * 8, hipMemcpyHostToDevice, st));
   SAP_HIP_CHECK(c, hipMemcpyAsync(a->ck_add, a->hcoef + 6 * nh, 6 * nh * 8, hipMemcpyHostToDevice, st));
   SAP_HIP_CHECK(c, hipStreamSynchronize(st));
+  const double kap = c->geom.kappa;
+  const int lb = c->geom.l0;
+  // Y = the first N terms of the even-odd geometric series of W1 y = rhs on the blocks of a
+  // colour (Horner form y_e <- b_hat_e + k^2 D_eo D_oe y_e), then y_o = rhs_o + k D_oe y_e; the
+  // other blocks of y are set to zero, or (keep, split kernel only) left as they are
+  auto series = [&](double2* y, const double2* rhs, int colour, bool keep) {
+    const Field<double> RHS = full_field<double>((void*)rhs, Vhp), Y = full_field<double>(y, Vhp);
+    const Field<double> BH = full_field<double>(a->g1, Vhp), Z = full_field<double>(a->g2, Vhp);
+    const Field<double> NONE64 = {nullptr, 0, 0, 0};
+    Fused f;
+    f.keep = keep;
+    const int N = o->sap_block_terms;
+    hop<double>(c, N == 1 ? Y : BH, RHS, RHS, 0, nrhs, lb, colour, 1.0, kap, 0, 0, st, f);
+    for (int n = 1; n < N; ++n) {
+      hop<double>(c, Z, n == 1 ? BH : Y, NONE64, 1, nrhs, lb, colour, 0.0, 1.0, 0, 0, st, f);
+      hop<double>(c, Y, Z, BH, 0, nrhs, lb, colour, 1.0, kap * kap, 0, 0, st, f);
+    }
+    hop<double>(c, Y, Y, RHS, 1, nrhs, lb, colour, 1.0, kap, 0, 0, st, f);
+  };
+  // the argument of a hop of the colour's sites only, all hops of M kept
+  auto on_colour = [&](double2* out, const double2* in, const double2* x, double b, int colour) {
+    HopArgs<double> A = hop_args<double>(c, full_field<double>(out, Vhp), full_field<double>((void*)in, Vhp),
+                                         full_field<double>((void*)x, Vhp), -1, nrhs, 0, colour, 1.0, b, 0, 0);
+    A.slb = lb;
+    return A;
+  };
+  // with series block solves on the split kernel, a cycle's first two block steps write their
+  // sites of out in place: out vanishes on the colour being solved, so that its right-hand side
+  // is in + k D out on that colour
+  const HopArgs<double> probe = hop_args<double>(c, {}, {}, {}, 0, nrhs, lb, SAP_WHITE, 1.0, kap, 0, 0);
+  const bool in_place = o->sap_block_terms > 0 && hop_is_split(probe);
   // out = K in
   auto K = [&](double2* out, const double2* in) -> int {
-    SAP_HIP_CHECK(c, hipMemsetAsync(a->kx, 0, fullb, st));
+    double2* kx = in_place ? out : a->kx;
+    if (!in_place) SAP_HIP_CHECK(c, hipMemsetAsync(kx, 0, fullb, st));
     for (int cyc = 0; cyc < o->sap_ncy; ++cyc)
       for (int col = 0; col < 2; ++col) {
         const int colour = col == 0 ? SAP_BLACK : SAP_WHITE;
-        const double* rhs = (const double*)in;
-        if (cyc > 0 || col > 0) {
-          int rc = apply_op_any(c, a->mt, a->kx, nrhs, 0, 0, -1, SAP_F64, st);
-          if (rc) return rc;
+        const double2* rhs = in;
+        if (in_place && cyc == 0 && col > 0) {
+          launch_hop<double>(on_colour(a->kr, kx, in, kap, colour), st);
+          rhs = a->kr;
+        } else if (cyc > 0 || col > 0) {
+          // in - M kx on the colour's sites
+          launch_hop<double>(on_colour(a->mt, kx, kx, -kap, colour), st);
           blas_lin3<double>(G, nh, H(a->kr), H((double2*)in), H(a->mt), NONE, a->ck_res, nullptr, st);
-          rhs = (const double*)a->kr;
+          rhs = a->kr;
+        }
+        if (in_place && cyc == 0) {
+          series(kx, rhs, colour, col > 0);
+          SAP_HIP_CHECK(c, hipGetLastError());
+          continue;
         }
         if (o->sap_block_terms > 0) {
-          // y = the first N terms of the even-odd geometric series of W1 y = rhs on the blocks
-          // of this colour (Horner form y_e <- b_hat_e + k^2 D_eo D_oe y_e), then
-          // y_o = rhs_o + k D_oe y_e; every other block of y is set to zero
-          const Field<double> RHS = full_field<double>((void*)rhs, Vhp), Y = full_field<double>(a->ky, Vhp);
-          const Field<double> BH = full_field<double>(a->g1, Vhp), Z = full_field<double>(a->g2, Vhp);
-          const Field<double> NONE64 = {nullptr, 0, 0, 0};
-          const double kap = c->geom.kappa;
-          const int lb = c->geom.l0;
-          hop<double>(c, BH, RHS, RHS, 0, nrhs, lb, colour, 1.0, kap, 0, 0, st);
-          hop<double>(c, Y, RHS, RHS, 0, nrhs, lb, colour, 1.0, kap, 0, 0, st);
-          for (int n = 1; n < o->sap_block_terms; ++n) {
-            hop<double>(c, Z, Y, NONE64, 1, nrhs, lb, colour, 0.0, 1.0, 0, 0, st);
-            hop<double>(c, Y, Z, BH, 0, nrhs, lb, colour, 1.0, kap * kap, 0, 0, st);
-          }
-          hop<double>(c, Y, Y, RHS, 1, nrhs, lb, colour, 1.0, kap, 0, 0, st);
+          series(a->ky, rhs, colour, false);
           SAP_HIP_CHECK(c, hipGetLastError());
         } else {
+          const double* r64 = (const double*)rhs;
           int rc = o->inner_prec == SAP_F64
-                       ? solve_impl<double>(c, (double*)a->ky, rhs, nrhs, c->geom.l0, colour, &bo, binfo.data(), st)
+                       ? solve_impl<double>(c, (double*)a->ky, r64, nrhs, lb, colour, &bo, binfo.data(), st)
                    : o->inner_prec == SAP_F32
-                       ? solve_impl<float>(c, (double*)a->ky, rhs, nrhs, c->geom.l0, colour, &bo, binfo.data(), st)
-                       : solve_impl<h16>(c, (double*)a->ky, rhs, nrhs, c->geom.l0, colour, &bo, binfo.data(), st);
+                       ? solve_impl<float>(c, (double*)a->ky, r64, nrhs, lb, colour, &bo, binfo.data(), st)
+                       : solve_impl<h16>(c, (double*)a->ky, r64, nrhs, lb, colour, &bo, binfo.data(), st);
           if (rc) return rc;
           for (auto& e : binfo) block_iters += e.iters;
         }
-        blas_lin3<double>(G, nh, H(a->kx), H(a->ky), NONE, NONE, a->ck_add, nullptr, st);
+        blas_lin3<double>(G, nh, H(kx), H(a->ky), NONE, NONE, a->ck_add, nullptr, st);
         SAP_HIP_CHECK(c, hipGetLastError());
       }
-    SAP_HIP_CHECK(c, hipMemcpyAsync(out, a->kx, fullb, hipMemcpyDeviceToDevice, st));
+    if (kx != out) SAP_HIP_CHECK(c, hipMemcpyAsync(out, kx, fullb, hipMemcpyDeviceToDevice, st));
     return SAP_OK;
   };
 

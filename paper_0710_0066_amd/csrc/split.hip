@@ -209,6 +209,7 @@ __global__ __launch_bounds__(512) void hop_split_kernel(HopArgs<R> A, SplitGeo q
   if (A.active && !A.active[rhs * q.nblk + blk]) return;         // whole workgroup
   bool sel = true;
   if (A.slb) sel = A.block >= 0 ? blk == A.block : block_sel(blk, 1, -1, A.colour);
+  if (A.keep && !sel) return;                                    // whole workgroup
 
   if (sel) {
     cx<T> v[6];
