@@ -1890,15 +1890,16 @@ void launch_slabd16(const HopArgs<h16>& A, hipStream_t st) { launch_slabd<h16>(A
 // Measured (us, split / slab): FP32 24^3x48 1 rhs 30 / 39, 2 rhs 45 / 49, 3 rhs 62 / 60, 12 rhs
 // 309 / 256; FP64 2 rhs 123 / 145, 3 rhs 174 / 164, 12 rhs 656 / 564; 24x10x6x14 with 12 rhs,
 // where the slab tile is small, 10 / 15 and 20 / 27. FP16 (issue-bound: the split kernel only
-// pays while it adds wavefronts): half hop split up to 7e5, marching up to 4e6, then the LDS
-// slab (16^3x32 3 rhs 14 / 16 / 24 us for split / march1 / slabd, 8 rhs 31 / 27 / 26; 24^3x48
-// 2 rhs 39 / 36 / 47, 12 rhs 250 / 196 / 186). Full operator: marching (launch_march1; FP16 from
-// W = 4e5 on: 16^3x32 1 rhs 11.1 / 12.1 us for split / march1, 5 rhs 41 / 36).
+// pays while it adds wavefronts): half hop SITE up to 7e5, marching above (16^3x32 3 rhs 13 /
+// 16 us for site / march1, 8 rhs 31 / 27; 24^3x48 2 rhs 39 / 36, 12 rhs 250 / 196; the LDS slab,
+// 186 us there, reads links rounded in all three rows and so gives other roundings); full
+// operator SITE up to 4e5 (16^3x32 1 rhs 11.1 / 12.1 us, 5 rhs 41 / 36).
+// Full operator in FP32 and FP64: marching (launch_march1).
 int hop_default_map(const Geo& g, bool full, int prec, int nrhs) {
   const double W = 2.0 * g.Vh * nrhs;
   if (prec == SAP_F16) {
     if (W <= (full ? 4e5 : 7e5)) return HOP_MAP_SITE;
-    return full || W <= 4e6 ? HOP_MAP_MARCH1 : HOP_MAP_SLABD;
+    return HOP_MAP_MARCH1;
   }
   if (full || W <= 1.9e6) return HOP_MAP_MARCH1;
   int TA, TB, S, H;

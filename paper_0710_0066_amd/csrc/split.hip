@@ -86,7 +86,8 @@ __device__ __forceinline__ void split_hop(const HopArgs<R>& A, const SplitGeo& q
   if constexpr (is_h16<R>) {
     const SiteR<h16> in = site_r(A.in, rhs, 1 - p, jn, Vhp);
     unsigned e[9], sw[12];
-    load_link16x3_words(A.U + 48 * Vhp + lp * 36 * Vhp + (long long)(lj >> 6) * (36 * TILE) + 9 * MU * TILE, lj & 63, e);
+    load_link16_words(A.U + lp * 24 * Vhp + (long long)(lj >> 6) * (24 * TILE) + 6 * MU * TILE, lj & 63, e);
+    third_row16(e);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       const u4v v = *(const u4v*)(in.b + 4 * k * TILE);
