@@ -146,10 +146,14 @@ def lib_path() -> str:
     return _LIB_PATH
 
 
-def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+# the current device's current stream as an integer handle: the lookup that
+# torch.cuda.current_stream() wraps in a Stream object (0.2 us instead of 3.1 us, of the 3.1 us
+# a launch takes)
+_current_device, _current_raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
 
+
+def _stream():
+    return _current_raw_stream(_current_device())
 
 
 def _buf(ctx, t, nbytes, what, optional=False):
@@ -157,11 +161,13 @@ def _buf(ctx, t, nbytes, what, optional=False):
     pointers, so the tensor must be a contiguous floating-point or complex tensor on the
     context's device holding at least nbytes (an undersized buffer would become an
     out-of-bounds device access). None gives NULL when optional, else SapError."""
+    if (type(t) is torch.Tensor and t.is_cuda and (ctx is None or t.get_device() == ctx.device)
+            and (t.is_floating_point() or t.is_complex()) and t.is_contiguous() and t.nbytes >= nbytes):
+        return t.data_ptr()
     if t is None:
         if optional:
             return None
         raise SapError(SAP_E_ARG, f"{what} is None")
-    import torch
     if not isinstance(t, torch.Tensor):
         raise SapError(SAP_E_ARG, f"{what}: expected a torch.Tensor, got {type(t).__name__}")
     if t.device.type != "cuda" or (ctx is not None and t.device.index != ctx.device):
@@ -174,7 +180,7 @@ def _buf(ctx, t, nbytes, what, optional=False):
     have = t.numel() * t.element_size()
     if have < nbytes:
         raise SapError(SAP_E_ARG, f"{what}: {have} bytes, the call needs {nbytes}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _field(ctx, t, nrhs, prec, what, optional=False):
@@ -183,12 +189,12 @@ def _field(ctx, t, nrhs, prec, what, optional=False):
         raise SapError(SAP_E_ARG, f"nrhs must be a positive int, got {nrhs!r}")
     if prec not in (SAP_F64, SAP_F32, SAP_F16):
         raise SapError(SAP_E_ARG, f"unknown precision {prec!r}")
-    return _buf(ctx, t, _lib.sap_field_bytes(ctx.ptr, prec, nrhs), what, optional)
+    return _buf(ctx, t, nrhs * ctx.rhs_bytes[prec], what, optional)
 
 
 def _mom(ctx, t, what, optional=False):
     """A library-layout momentum / force field."""
-    return _buf(ctx, t, _lib.sap_momenta_bytes(ctx.ptr), what, optional)
+    return _buf(ctx, t, ctx.momenta_bytes, what, optional)
 
 
 def _check(ctx_ptr, rc, info=None):
@@ -466,8 +472,10 @@ class Context:
         rc = _lib.sap_create(ctypes.byref(g), ctypes.byref(p))
         _check(None, rc)
         self.ptr = p
-        import torch
         self.device = torch.cuda.current_device()     # sap_create bound the context to it
+        # sizes of the layout, which depend on the geometry alone
+        self.rhs_bytes = tuple(_lib.sap_field_bytes(p, prec, 1) for prec in (SAP_F64, SAP_F32, SAP_F16))
+        self.momenta_bytes = _lib.sap_momenta_bytes(p)
 
     def close(self):
         if getattr(self, "ptr", None):
