@@ -8,12 +8,16 @@ namespace sap {
 // sx (device, [L0][4], or null): per-link step scale s_mu(x0) multiplying c
 void launch_pair_force(const Geo& g, double* F, double c, const double2* a, const double2* b,
                        const double2* U, int lb, hipStream_t s, const double* sx = nullptr);
-// F += c * Im tr(lambda^a U A) (c = coef * beta / 6)
-void launch_gauge_force(const Geo& g, double* F, double c, const double2* U, hipStream_t s,
+// F += c * Im tr(lambda^a U A) (c = coef * beta / 6), also leaving the partials of the plaquette
+// sum in part. Q: 96*Vhp doubles of scratch, part: gauge_parts(g)
+int gauge_parts(const Geo& g);
+void launch_gauge_force(const Geo& g, double* F, double c, const double2* U, double* Q, double* part, hipStream_t s,
                         const double* sx = nullptr);
+// out[0] = the plaquette sum from those partials
+void launch_plaq_total(const Geo& g, const double* part, double* out, hipStream_t s);
 // out = in translated by n slices in x0 (out(x0) = in(x0 + n)); out != in
 void launch_shift_links(const Geo& g, double2* out, const double2* in, int n, hipStream_t s);
-// out[0] = sum_x sum_{mu>nu} Re tr U_P (part: ceil(Vh/128) doubles of scratch)
+// out[0] = sum_x sum_{mu>nu} Re tr U_P (part: gauge_parts(g) doubles of scratch)
 void launch_plaq_sum(const Geo& g, const double2* U, double* part, double* out, hipStream_t s);
 // out[0] = max over the links of max(max_e |(U U^+ - 1)_e|, |det U - 1|) (NaN if any is NaN)
 void launch_su3_dev(const Geo& g, const double2* U, double* part, double* out, hipStream_t s);

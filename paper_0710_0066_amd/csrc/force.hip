@@ -11,11 +11,13 @@
 //   Y = sum_k hb'_k (x) ha'_k^* (half spinors of (1 + gamma_mu) b(x) and of a(x+mu)),
 // with the x0 wrap phase -1 on the link at x0 = L0-1.
 // gauge force (Wilson plaquette action, Sec. 1): F^a = (beta/6) Im tr(lambda^a U A),
-// A = sum of the six staples of U_mu(x).
+// A = sum of the six staples of U_mu(x), from the plaquettes: U A = sum over nu of the
+// plaquette at x and the one at x - nu carried along U_nu(x - nu) (k_plaq, k_gauge_force).
 // T_U (Sec. 2, eq. 3): U <- exp(i dt P) U, exponential by scaling and squaring of a
 // degree-16 Taylor polynomial, then Gram-Schmidt reunitarisation with the third row the
 // conjugate cross product of the first two (exactly unitary, det 1 up to rounding).
 #include "force.h"
+#include "split.h"
 
 namespace sap {
 
@@ -164,57 +166,6 @@ void k_pair_force(Geo g, double* F, double c, const double2* a, const double2* b
   add_force(F, Vhp, p, j, mu, c * sgn * (sx ? sx[s.x0 * 4 + mu] : 1.0), v);
 }
 
-// Staple sum of U_mu(x):
-//   A = sum_{nu != mu} U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+ + U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu)
-__device__ M3 staples(const Geo& g, const double2* U, int p, long long j, const Site& s, int mu) {
-  const long long Vhp = g.Vhp;
-  M3 A;
-#pragma unroll
-  for (int e = 0; e < 9; ++e) A.m[e] = {0.0, 0.0};
-  const long long jpm = nbr(g, s, j, mu, +1);                 // x+mu, parity 1-p
-  const Site spm = decode(g, jpm, 1 - p);
-  // one direction at a time: unrolling would keep the links of all six staples live
-#pragma unroll 1
-  for (int nu = 0; nu < 4; ++nu) {
-    if (nu == mu) continue;
-    const long long jpn = nbr(g, s, j, nu, +1);               // x+nu, parity 1-p
-    const long long jmn = nbr(g, s, j, nu, -1);               // x-nu, parity 1-p
-    const long long jpmmn = nbr(g, spm, jpm, nu, -1);         // x+mu-nu, parity p
-    // U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+ (the memory fences keep the scheduler from
-    // loading the links of both staples at once, which would cost occupancy)
-    const M3 ab = mmul_nd(load_U(U, Vhp, 1 - p, jpm, nu), load_U(U, Vhp, 1 - p, jpn, mu));
-    asm volatile("" ::: "memory");
-    const M3 up = mmul_nd(ab, load_U(U, Vhp, p, j, nu));
-#pragma unroll
-    for (int e = 0; e < 9; ++e) A.m[e] = A.m[e] + up.m[e];
-    asm volatile("" ::: "memory");
-    // U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu) = (U_mu(x-nu) U_nu(x+mu-nu))^+ U_nu(x-nu)
-    const M3 t = mmul(load_U(U, Vhp, 1 - p, jmn, mu), load_U(U, Vhp, p, jpmmn, nu));
-    asm volatile("" ::: "memory");
-    const M3 lo = mmul_dn(t, load_U(U, Vhp, 1 - p, jmn, nu));
-#pragma unroll
-    for (int e = 0; e < 9; ++e) A.m[e] = A.m[e] + lo.m[e];
-    asm volatile("" ::: "memory");
-  }
-  return A;
-}
-
-// One work-item per link: a workgroup holds 64 sites of one parity (blockIdx.y) and one
-// wavefront per direction mu, so that the staple sums of the four links of a site run in
-// parallel and the registers of one staple sum decide the occupancy.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-void k_gauge_force(Geo g, double* F, double c, const double2* U, const double* sx) {
-  const int mu = threadIdx.x >> 6;
-  const int p = blockIdx.y;
-  const long long j = (long long)blockIdx.x * 64 + (threadIdx.x & 63);
-  if (j >= g.Vh) return;
-  const Site s = decode(g, j, p);
-  const M3 W = mmul(load_U(U, g.Vhp, p, j, mu), staples(g, U, p, j, s, mu));
-  double v[8];
-  im_tr_lambda(W, v);
-  add_force(F, g.Vhp, p, j, mu, c * (sx ? sx[s.x0 * 4 + mu] : 1.0), v);
-}
-
 __device__ __forceinline__ double wsum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
@@ -228,24 +179,171 @@ __device__ __forceinline__ double bsum256(double v) {
   return (threadIdx.x == 0) ? (sh[0] + sh[1]) + (sh[2] + sh[3]) : 0.0;
 }
 
-// Per-workgroup partial of sum_x sum_{mu>nu} Re tr U_mu(x) U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
-__global__ __launch_bounds__(256) void k_plaq(Geo g, const double2* U, double* part) {
-  const int p = threadIdx.x >> 7;
-  const long long j = (long long)blockIdx.x * 128 + (threadIdx.x & 127);
-  double acc = 0.0;
-  if (j < g.Vh) {
-    const Site s = decode(g, j, p);
-    for (int mu = 1; mu < 4; ++mu)
-      for (int nu = 0; nu < mu; ++nu) {
-        const long long jpm = nbr(g, s, j, mu, +1), jpn = nbr(g, s, j, nu, +1);
-        const M3 a = mmul(load_U(U, g.Vhp, p, j, mu), load_U(U, g.Vhp, 1 - p, jpm, nu));
-        const M3 b = mmul(load_U(U, g.Vhp, p, j, nu), load_U(U, g.Vhp, 1 - p, jpn, mu));
-        const M3 P = mmul_nd(a, b);
-        acc += P.m[0].r + P.m[4].r + P.m[8].r;
-      }
+// Sum over the NW wavefronts of a workgroup, valid in thread 0
+template <int NW> __device__ __forceinline__ double bsum(double v) {
+  __shared__ double sh[NW];
+  v = wsum(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double t = 0.0;
+  for (int w = 0; w < NW; ++w) t += sh[w];
+  return t;
+}
+
+// Order of the workgroups (64 sites of one parity each) of the gauge kernels: XCD k (workgroup
+// id % 8) owns the 64-site chunks [n k / 8, n (k + 1) / 8) of every slice and walks the slices
+// in order, both parities of a chunk together, so that the links of a slice are still in its
+// L2 when the next slice reads them as time neighbours (a whole slice of 24^3 is 8 MB of links,
+// twice an L2). A workgroup takes its chunk through `steps` slices. Slices of fewer than 16
+// chunks: XCDs take ranges of the whole lattice, one chunk per workgroup (piece 0).
+struct Walk {
+  int nslice, piece, steps, blocks;
+};
+inline Walk walk_of(const Geo& g, int steps) {
+  Walk w;
+  w.nslice = (g.V3h + 63) / 64;
+  w.piece = w.nslice >= 16 ? (w.nslice + 7) / 8 : 0;
+  w.steps = w.piece ? steps : 1;
+  w.blocks = w.piece ? 16 * ((g.L0 + steps - 1) / steps) * w.piece : (int)((g.Vh + 63) / 64 * 2);
+  return w;
+}
+// f(p, j) for the sites of this work-item
+template <class F> __device__ __forceinline__ void walk_sites(const Geo& g, const Walk& k, F f) {
+  const int lane = threadIdx.x & 63;
+  if (k.piece) {
+    const int xcd = blockIdx.x & 7, w = blockIdx.x >> 3, i = w >> 1;
+    const int xb = i / k.piece, lo = k.nslice * xcd / 8;
+    const int cs = lo + i - xb * k.piece;
+    if (cs >= k.nslice * (xcd + 1) / 8 || cs * 64 + lane >= g.V3h) return;
+#pragma unroll 1
+    for (int x = xb * k.steps; x < min((xb + 1) * k.steps, g.L0); ++x) f(w & 1, x * g.V3h + cs * 64 + lane);
+    return;
   }
-  const double t = bsum256(acc);
+  const int w = xcd_block(blockIdx.x, gridDim.x, false), j = (w >> 1) * 64 + lane;
+  if (j < g.Vh) f(w & 1, j);
+}
+
+// Plane (mu, nu), mu < nu, of index 0..5
+constexpr int PLANE_MU[6] = {0, 0, 0, 1, 1, 2}, PLANE_NU[6] = {1, 2, 3, 2, 3, 3};
+__host__ __device__ constexpr int plane_of(int mu, int nu) { return mu == 0 ? nu - 1 : mu == 1 ? nu + 1 : 5; }
+
+// P_{mu nu}(x) = U_mu(x) U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
+template <int MU, int NU>
+__device__ __forceinline__ M3 plaquette(const Geo& g, const SiteDiv& q, const double2* U, int p, int j) {
+  int x0;
+  const int jm = nbr32<MU, 0>(g, q, p, j, x0), jn = nbr32<NU, 0>(g, q, p, j, x0);
+  const M3 a = mmul_nd(load_U(U, g.Vhp, 1 - p, jm, NU), load_U(U, g.Vhp, 1 - p, jn, MU));
+  return mmul_nd(mmul(load_U(U, g.Vhp, p, j, MU), a), load_U(U, g.Vhp, p, j, NU));
+}
+
+// Plaquettes: one wavefront per plane for 64 sites of one parity. Writes the per-workgroup
+// partial of sum_x sum_{mu<nu} Re tr P and (STORE) the components q^a = Im tr(lambda^a P) at
+// p*48*Vhp + tiled(j, 8*plane + a, 48). Each plaquette is formed once, for the action and for
+// the four links it acts on.
+template <bool STORE>
+__global__ __launch_bounds__(384) void k_plaq(Geo g, SiteDiv q, Walk k, const double2* U, double* part, double* Q) {
+  const int plane = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double acc = 0.0;
+  walk_sites(g, k, [&](int p, int j) {
+    M3 P;
+    switch (plane) {
+      case 0: P = plaquette<0, 1>(g, q, U, p, j); break;
+      case 1: P = plaquette<0, 2>(g, q, U, p, j); break;
+      case 2: P = plaquette<0, 3>(g, q, U, p, j); break;
+      case 3: P = plaquette<1, 2>(g, q, U, p, j); break;
+      case 4: P = plaquette<1, 3>(g, q, U, p, j); break;
+      default: P = plaquette<2, 3>(g, q, U, p, j); break;
+    }
+    acc += P.m[0].r + P.m[4].r + P.m[8].r;
+    if (STORE) {
+      double v[8];
+      im_tr_lambda(P, v);
+      double* o = Q + p * 48 * g.Vhp + tiled(j, 8 * plane, 48);
+#pragma unroll
+      for (int a = 0; a < 8; ++a) o[a * TILE] = v[a];
+    }
+  });
+  const double t = bsum<6>(acc);
   if (threadIdx.x == 0) part[blockIdx.x] = t;
+}
+
+// tr(lambda^a U^+ H U) for H = sum_b q^b lambda^b / 2
+__device__ __forceinline__ void transport(const M3& U, const double q[8], double r[8]) {
+  const double r3 = 0.57735026918962576451;
+  const double h0 = 0.5 * (q[2] + r3 * q[7]), h1 = 0.5 * (r3 * q[7] - q[2]), h2 = -r3 * q[7];
+  const C h01 = {0.5 * q[0], -0.5 * q[1]}, h02 = {0.5 * q[3], -0.5 * q[4]}, h12 = {0.5 * q[5], -0.5 * q[6]};
+  M3 T;                                    // H U
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const C u0 = U.m[k], u1 = U.m[3 + k], u2 = U.m[6 + k];
+    T.m[k] = cfma(cfma(h0 * u0, h01, u1), h02, u2);
+    T.m[3 + k] = cfma(cjfma(h1 * u1, h01, u0), h12, u2);
+    T.m[6 + k] = cjfma(cjfma(h2 * u2, h02, u0), h12, u1);
+  }
+  auto z = [&](int i, int k) {             // (U^+ H U)_ik
+    C t = cjmul(U.m[i], T.m[k]);
+    t = cjfma(t, U.m[3 + i], T.m[3 + k]);
+    return cjfma(t, U.m[6 + i], T.m[6 + k]);
+  };
+  const C z01 = z(0, 1), z02 = z(0, 2), z12 = z(1, 2);
+  const double z0 = z(0, 0).r, z1 = z(1, 1).r, z2 = z(2, 2).r;
+  r[0] = 2.0 * z01.r; r[1] = -2.0 * z01.i;
+  r[2] = z0 - z1;
+  r[3] = 2.0 * z02.r; r[4] = -2.0 * z02.i;
+  r[5] = 2.0 * z12.r; r[6] = -2.0 * z12.i;
+  r[7] = (z0 + z1 - 2.0 * z2) * r3;
+}
+
+// v += s (q_plane(x) - q_plane(x - nu) carried along U_nu(x - nu)), s = +1 for mu < nu, else -1
+template <int MU, int NU>
+__device__ __forceinline__ void plane_force(const Geo& g, const SiteDiv& d, const double2* U, const double* Q, int p,
+                                            int j, double v[8]) {
+  if constexpr (MU != NU) {
+    constexpr int plane = MU < NU ? plane_of(MU, NU) : plane_of(NU, MU);
+    constexpr double s = MU < NU ? 1.0 : -1.0;
+    int x0;
+    const int jy = nbr32<NU, 1>(g, d, p, j, x0);
+    const double* qx = Q + p * 48 * g.Vhp + tiled(j, 8 * plane, 48);
+    const double* qy = Q + (1 - p) * 48 * g.Vhp + tiled(jy, 8 * plane, 48);
+    double y[8], r[8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) y[a] = qy[a * TILE];
+    transport(load_U(U, g.Vhp, 1 - p, jy, NU), y, r);
+#pragma unroll
+    for (int a = 0; a < 8; ++a) v[a] += s * (qx[a * TILE] - r[a]);
+  }
+}
+template <int MU>
+__device__ __forceinline__ void link_force(const Geo& g, const SiteDiv& d, const double2* U, const double* Q, int p,
+                                           int j, double v[8]) {
+  plane_force<MU, 0>(g, d, U, Q, p, j, v);
+  plane_force<MU, 1>(g, d, U, Q, p, j, v);
+  plane_force<MU, 2>(g, d, U, Q, p, j, v);
+  plane_force<MU, 3>(g, d, U, Q, p, j, v);
+}
+
+// Gauge force from the plaquette components Q of k_plaq: one wavefront per direction for 64
+// sites of one parity. U_mu A_mu = sum_nu (P_{mu nu}(x) + U_nu(y)^+ P_{nu mu}(y) U_nu(y)), y =
+// x - nu, of which the force takes the traceless anti-Hermitian part: 8 numbers per
+// plaquette, carried by the adjoint action of one link. A link reads 3 links and 6 sets of
+// components (816 B) instead of the 19 links of its staples (2.7 KB), in about half the
+// registers; both passes stream at the rate of HBM. On 24^3x48 the staple kernel took 596 us
+// (236 VGPRs, two wavefronts per SIMD, 12 TB/s from L2) and the separate action sum 250 us;
+// the passes take 204 (770 MB fetched and written) and 214 us (1.05 GB, 4.9 TB/s), the sum 5.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+void k_gauge_force(Geo g, SiteDiv d, Walk k, double* F, double c, const double2* U,
+                                                     const double* Q, const double* sx) {
+  const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  walk_sites(g, k, [&](int p, int j) {
+    double v[8] = {};
+    switch (mu) {
+      case 0: link_force<0>(g, d, U, Q, p, j, v); break;
+      case 1: link_force<1>(g, d, U, Q, p, j, v); break;
+      case 2: link_force<2>(g, d, U, Q, p, j, v); break;
+      default: link_force<3>(g, d, U, Q, p, j, v); break;
+    }
+    add_force(F, g.Vhp, p, j, mu, c * (sx ? sx[fdiv(d.dv, j) * 4 + mu] : 1.0), v);
+  });
 }
 
 // Per-workgroup maximum over the links of the largest deviation from SU(3): the largest
@@ -308,15 +406,13 @@ __global__ __launch_bounds__(256) void k_kinetic(Geo g, const double* P, double*
   if (threadIdx.x == 0) part[blockIdx.x] = 0.5 * t;
 }
 
-// one wavefront, as k_max_parts: a fixed order of additions, so the sum is bitwise
-// reproducible
-__global__ void k_sum_parts(int n, const double* part, double* out) {
-  const int l = threadIdx.x;
+// one workgroup: thread t takes part[t], part[t + 1024], ..., then a fixed tree: the sum is
+// bitwise reproducible
+__global__ __launch_bounds__(1024) void k_sum_parts(int n, const double* part, double* out) {
   double s = 0.0;
-  for (int i = l; i < n; i += 64) s += part[i];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  if (l == 0) out[0] = s;
+  for (int i = threadIdx.x; i < n; i += 1024) s += part[i];
+  s = bsum<16>(s);
+  if (threadIdx.x == 0) out[0] = s;
 }
 
 // exp(A) for anti-Hermitian 3x3 A (Taylor degree 16 after scaling by 2^-k, |A/2^k| <= 1/2)
@@ -556,15 +652,25 @@ void launch_pair_force(const Geo& g, double* F, double coef_times_minus_kappa, c
   hipLaunchKernelGGL(k_pair_force, dim3((unsigned)((g.Vh + 63) / 64), 2), dim3(256), 0, s, g, F,
                      coef_times_minus_kappa, a, b, U, lb, sx);
 }
-void launch_gauge_force(const Geo& g, double* F, double c, const double2* U, hipStream_t s, const double* sx) {
-  hipLaunchKernelGGL(k_gauge_force, dim3((unsigned)((g.Vh + 63) / 64), 2), dim3(256), 0, s, g, F, c, U, sx);
+constexpr int PLAQ_STEPS = 4, FORCE_STEPS = 1;
+int gauge_parts(const Geo& g) { return walk_of(g, PLAQ_STEPS).blocks; }
+void launch_gauge_force(const Geo& g, double* F, double c, const double2* U, double* Q, double* part, hipStream_t s,
+                        const double* sx) {
+  const SiteDiv d = site_div(g);
+  const Walk k = walk_of(g, PLAQ_STEPS), f = walk_of(g, FORCE_STEPS);
+  hipLaunchKernelGGL(k_plaq<true>, dim3(k.blocks), dim3(384), 0, s, g, d, k, U, part, Q);
+  hipLaunchKernelGGL(k_gauge_force, dim3(f.blocks), dim3(256), 0, s, g, d, f, F, c, U, Q, sx);
+}
+void launch_plaq_total(const Geo& g, const double* part, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(1024), 0, s, gauge_parts(g), part, out);
 }
 void launch_shift_links(const Geo& g, double2* out, const double2* in, int n, hipStream_t s) {
   hipLaunchKernelGGL(k_shift_links, dim3(site_blocks(g)), dim3(256), 0, s, g, out, in, n);
 }
 void launch_plaq_sum(const Geo& g, const double2* U, double* part, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_plaq, dim3(site_blocks(g)), dim3(256), 0, s, g, U, part);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, s, (int)site_blocks(g), part, out);
+  const Walk k = walk_of(g, PLAQ_STEPS);
+  hipLaunchKernelGGL(k_plaq<false>, dim3(k.blocks), dim3(384), 0, s, g, site_div(g), k, U, part, nullptr);
+  launch_plaq_total(g, part, out, s);
 }
 void launch_su3_dev(const Geo& g, const double2* U, double* part, double* out, hipStream_t s) {
   hipLaunchKernelGGL(k_su3_dev, dim3(site_blocks(g)), dim3(256), 0, s, g, U, part);
@@ -572,11 +678,11 @@ void launch_su3_dev(const Geo& g, const double2* U, double* part, double* out, h
 }
 void launch_kinetic(const Geo& g, const double* P, double* part, double* out, hipStream_t s) {
   hipLaunchKernelGGL(k_kinetic, dim3(site_blocks(g)), dim3(256), 0, s, g, P, part);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, s, (int)site_blocks(g), part, out);
+  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(1024), 0, s, (int)site_blocks(g), part, out);
 }
 void launch_norm2_full(const Geo& g, const double2* f, double* part, double* out, hipStream_t s) {
   hipLaunchKernelGGL(k_norm2_full, dim3(site_blocks(g)), dim3(256), 0, s, g, f, part);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, s, (int)site_blocks(g), part, out);
+  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(1024), 0, s, (int)site_blocks(g), part, out);
 }
 void launch_update_links(const Geo& g, double2* U, const LinkCopies& lc, const double* P, double dt, hipStream_t s,
                          const double* sx) {

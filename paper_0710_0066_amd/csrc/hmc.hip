@@ -10,6 +10,7 @@
 //   action      S_R = ||eta||^2,  eta = chi - Pi psi,  psi = M^{-1} D_dOm* chi,
 //   force       F = 2 Re <xi, dM psi> - 2 Re <P_Om* xi, dM chi>,  xi = M^{-dagger} Pi eta,
 // with M^{-dagger} = g5 M^{-1} g5 and W1^{-dagger} = g5 W1^{-1} g5.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include "force.h"
@@ -28,11 +29,11 @@ int sap_solve_eo_shift(sap_ctx* c, double* x, const double* b, int nrhs, int lb,
 struct ForceWS {
   double2* f[12];      // full FP64 spinor fields of one rhs
   double* mom;         // momenta (sap layout)
-  double* part;        // reduction partials (one per 128-site tile pair)
+  double* part;        // reduction partials (one per workgroup)
   double* scal;        // device scalars
   double* h_scal;      // pinned host mirror
   double* sx;          // per-link step scale s_mu(x0), [L0][4]
-  double2* Utmp;       // gauge field scratch (translations)
+  double2* Utmp;       // gauge field scratch (translations, plaquettes of the gauge force)
   double* prof;        // force profile: partials (2 * L0 * nck) then the result (2 * L0)
   long long iters;     // inner iterations accumulated by the drivers below
 };
@@ -47,7 +48,7 @@ int sap_force_create(sap_ctx* c) {
   bool ok = true;
   for (int i = 0; i < 12; ++i) ok = ok && hipMalloc((void**)&w->f[i], fb) == hipSuccess;
   ok = ok && hipMalloc((void**)&w->mom, (size_t)64 * c->Vhp * 8) == hipSuccess;
-  ok = ok && hipMalloc((void**)&w->part, (size_t)((c->Vh + 127) / 128 + 8) * 8) == hipSuccess;
+  ok = ok && hipMalloc((void**)&w->part, (size_t)(std::max((int)((c->Vh + 127) / 128), gauge_parts(c->g)) + 8) * 8) == hipSuccess;
   ok = ok && hipMalloc((void**)&w->scal, 64 * 8) == hipSuccess;
   ok = ok && hipHostMalloc((void**)&w->h_scal, 64 * 8, 0) == hipSuccess;
   ok = ok && hipMalloc((void**)&w->sx, (size_t)c->geom.L[0] * 4 * 8) == hipSuccess;
@@ -302,13 +303,17 @@ int eo_heat_bath(sap_ctx* c, double2* phi, const double2* xi, int kind, double r
   return solve_eo1(c, phi, w->f[4], rho, o, s);
 }
 
-int gauge_action_host(sap_ctx* c, double beta, double* S, hipStream_t s) {
+// S_G from the plaquette sum in scal (synchronises)
+int action_from_scal(sap_ctx* c, double beta, double* S, hipStream_t s) {
   ForceWS* w = fws(c);
-  launch_plaq_sum(c->g, c->U64, w->part, w->scal, s);
   SAP_HIP_CHECK(c, hipMemcpyAsync(w->h_scal, w->scal, 8, hipMemcpyDeviceToHost, s));
   SAP_HIP_CHECK(c, hipStreamSynchronize(s));
   *S = -beta / 3.0 * w->h_scal[0];
   return SAP_OK;
+}
+int gauge_action_host(sap_ctx* c, double beta, double* S, hipStream_t s) {
+  launch_plaq_sum(c->g, c->U64, fws(c)->part, fws(c)->scal, s);
+  return action_from_scal(c, beta, S, s);
 }
 
 int kinetic_host(sap_ctx* c, const double* P, double* K, hipStream_t s) {
@@ -361,7 +366,8 @@ int kick_pf(Traj& T, double dt) {
   return schwarz_terms(T.c, fws(T.c)->mom, -dt, T.chi, &T.P->force_solve, nullptr, T.s, T.sx);
 }
 int kick_g(Traj& T, double dt) {
-  launch_gauge_force(T.c->g, fws(T.c)->mom, -dt * T.P->beta / 6.0, T.c->U64, T.s, T.sx);
+  launch_gauge_force(T.c->g, fws(T.c)->mom, -dt * T.P->beta / 6.0, T.c->U64, (double*)fws(T.c)->Utmp, fws(T.c)->part,
+                     T.s, T.sx);
   SAP_HIP_CHECK(T.c, hipGetLastError());
   return SAP_OK;
 }
@@ -449,7 +455,7 @@ int kick4(Traj4& T, int j, double dt) {
   const sap_solve_opts* o = j ? force_opts4(T.P, j) : nullptr;
   switch (j) {
     case 0:
-      launch_gauge_force(c->g, mom, -dt * T.P->beta / 6.0, c->U64, T.s, T.sx);
+      launch_gauge_force(c->g, mom, -dt * T.P->beta / 6.0, c->U64, (double*)fws(c)->Utmp, fws(c)->part, T.s, T.sx);
       SAP_HIP_CHECK(c, hipGetLastError());
       return SAP_OK;
     case 1: return eo_pf_terms(c, mom, -dt, T.phi1, 1, T.P->rho, o, nullptr, T.s, T.sx);
@@ -622,9 +628,11 @@ int gauge_force(sap_ctx* c, double* F, double coef, double beta, double* S_G_out
   if (!std::isfinite(beta)) return sap_fail(c, SAP_E_ARG, "beta must be finite");
   if (!c->have_gauge) return sap_fail(c, SAP_E_STATE, "no gauge field set");
   hipStream_t s = (hipStream_t)stream;
-  launch_gauge_force(c->g, F, coef * beta / 6.0, c->U64, s);
+  ForceWS* w = fws(c);
+  launch_gauge_force(c->g, F, coef * beta / 6.0, c->U64, (double*)w->Utmp, w->part, s);
+  if (S_G_out) launch_plaq_total(c->g, w->part, w->scal, s);   // the force's own plaquettes
   SAP_HIP_CHECK(c, hipGetLastError());
-  if (S_G_out) return gauge_action_host(c, beta, S_G_out, s);
+  if (S_G_out) return action_from_scal(c, beta, S_G_out, s);
   return SAP_OK;
 }
 

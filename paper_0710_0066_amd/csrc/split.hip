@@ -23,44 +23,6 @@ namespace sap {
 
 namespace {
 
-__device__ __forceinline__ int fdiv(FastDiv d, int n) {
-  return (int)(((unsigned long long)(unsigned)n * d.m) >> d.s);
-}
-
-// the neighbour of site j of parity p in direction MU (DIR 0 forward, 1 backward), and the
-// x0 of the site where MU = 0
-template <int MU, int DIR>
-__device__ __forceinline__ int split_nbr(const Geo& g, const SplitGeo& q, int p, int j, int& x0) {
-  const int r = fdiv(q.d3, j), x3h = j - r * g.L3h;
-  x0 = 0;
-  if constexpr (MU == 0) {
-    x0 = fdiv(q.dv, j);
-    if (DIR == 0) return x0 == g.L0 - 1 ? j - (g.L0 - 1) * g.V3h : j + g.V3h;
-    return x0 == 0 ? j + (g.L0 - 1) * g.V3h : j - g.V3h;
-  } else {
-    const int r2 = fdiv(q.d2, r), x2 = r - r2 * g.L2;
-    if constexpr (MU == 2) {
-      if (DIR == 0) return x2 == g.L2 - 1 ? j - (g.L2 - 1) * g.L3h : j + g.L3h;
-      return x2 == 0 ? j + (g.L2 - 1) * g.L3h : j - g.L3h;
-    } else {
-      const int r3 = fdiv(q.d1, r2), x1 = r2 - r3 * g.L1;
-      const int st = g.L2 * g.L3h;
-      if constexpr (MU == 1) {
-        if (DIR == 0) return x1 == g.L1 - 1 ? j - (g.L1 - 1) * st : j + st;
-        return x1 == 0 ? j + (g.L1 - 1) * st : j - st;
-      } else {
-        const int b = (p + r3 + x1 + x2) & 1;
-        if (DIR == 0) {
-          const int h = x3h + b;
-          return j + b - (h == g.L3h ? g.L3h : 0);
-        }
-        const int h = x3h - 1 + b;
-        return j - 1 + b + (h < 0 ? g.L3h : 0);
-      }
-    }
-  }
-}
-
 // half spinor of hop (MU, DIR) of site j, zero where the hop is absent
 template <class R, int MU, int DIR>
 __device__ __forceinline__ void split_hop(const HopArgs<R>& A, const SplitGeo& q, int rhs, int p, int j, bool on,
@@ -69,7 +31,7 @@ __device__ __forceinline__ void split_hop(const HopArgs<R>& A, const SplitGeo& q
   const Geo& g = A.g;
   const long long Vhp = g.Vhp;
   int x0;
-  const int jn = split_nbr<MU, DIR>(g, q, p, j, x0);
+  const int jn = nbr32<MU, DIR>(g, q.site, p, j, x0);
   bool flip = false;
   if constexpr (MU == 0) {
     flip = DIR == 0 ? x0 == g.L0 - 1 : x0 == 0;
@@ -329,16 +291,6 @@ __global__ __launch_bounds__(512) void hop_split_kernel(HopArgs<R> A, SplitGeo q
   }
 }
 
-FastDiv fast_div(int d) {
-  // floor(n / d) = (n * m) >> s for 0 <= n < 2^31: s = 31 + ceil(log2 d), m = floor(2^s / d) + 1
-  FastDiv f;
-  int l = 0;
-  while ((1LL << l) < d) ++l;
-  f.s = 31 + l;
-  f.m = (unsigned)((1ULL << f.s) / (unsigned)d + 1);
-  return f;
-}
-
 }  // namespace
 
 int split_chunks(const Geo& g, int nlb, bool march) {
@@ -357,10 +309,7 @@ template <class R> void launch_split(const HopArgs<R>& A, bool march, hipStream_
   q.nchunk = split_chunks(g, q.len, march);
   q.nslice = (g.V3h + TILE - 1) / TILE;
   q.npiece = (q.nslice + 7) / 8;
-  q.d3 = fast_div(g.L3h);
-  q.d2 = fast_div(g.L2);
-  q.d1 = fast_div(g.L1);
-  q.dv = fast_div(g.V3h);
+  q.site = site_div(g);
   q.db = fast_div(A.lb ? A.lb : 1);
   const long long per = (long long)A.nrhs * (full ? 2 : 1);
   // linear order: a multiple of 8 workgroups gives each XCD a range of the lattice; where some
