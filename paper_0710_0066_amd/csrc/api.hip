@@ -70,7 +70,7 @@ int sap_solver_create(sap_ctx* ctx);     // solver.hip
 int sap_force_create(sap_ctx* ctx);      // hmc.hip
 void sap_force_destroy(sap_ctx* ctx);    // hmc.hip
 int sap_noalloc_setup(sap_ctx* ctx);     // noalloc.hip
-int su3_deviation_host(sap_ctx* c, double* dev, hipStream_t s);   // hmc.hip
+int load_gauge(sap_ctx* c, const double* U, double* dev, hipStream_t s);   // hmc.hip
 extern "C" {
 
 int sap_create(const sap_geom* g, sap_ctx** out) {
@@ -86,7 +86,6 @@ int sap_create(const sap_geom* g, sap_ctx** out) {
   c->Vhp = c->g.Vhp;
   c->have_gauge = false;
   c->U64 = nullptr;
-  c->U64c = nullptr;
   c->U32 = nullptr;
   c->U16 = nullptr;
   c->solver = nullptr;
@@ -99,7 +98,6 @@ int sap_create(const sap_geom* g, sap_ctx** out) {
   }
   const size_t nlink = (size_t)72 * c->Vhp, nlink2 = (size_t)48 * c->Vhp;   // 2-row copies: 6 of 9
   if (hipMalloc((void**)&c->U64, nlink * sizeof(double2)) != hipSuccess ||
-      hipMalloc((void**)&c->U64c, nlink2 * sizeof(double2)) != hipSuccess ||
       hipMalloc((void**)&c->U32, nlink2 * sizeof(float2)) != hipSuccess ||
       hipMalloc((void**)&c->U16, (nlink2 + nlink) * sizeof(__half2)) != hipSuccess) {   // 2-row + 3-row
     sap_destroy(c);
@@ -123,7 +121,6 @@ void sap_destroy(sap_ctx* ctx) {
   sap_solver_destroy(ctx);
   sap_force_destroy(ctx);
   if (ctx->U64) (void)hipFree(ctx->U64);
-  if (ctx->U64c) (void)hipFree(ctx->U64c);
   if (ctx->U32) (void)hipFree(ctx->U32);
   if (ctx->U16) (void)hipFree(ctx->U16);
   delete ctx;
@@ -134,13 +131,10 @@ int sap_set_gauge(sap_ctx* ctx, const double* U, void* stream) {
   if (!U) return sap_fail(ctx, SAP_E_ARG, "U is NULL");
   hipStream_t s = (hipStream_t)stream;
   ctx->have_gauge = false;
-  launch_pack_gauge(ctx->g, ctx->U64, nullptr, (const double2*)U, s);
-  launch_gauge_to_f32(ctx->g, ctx->U64c, ctx->U32, ctx->U16, ctx->U64, s);
-  SAP_HIP_CHECK(ctx, hipGetLastError());
   // the hop kernels rebuild the third row of every link from the first two, which holds
   // for SU(3) only: refuse anything else
   double dev = 0.0;
-  int rc = su3_deviation_host(ctx, &dev, s);
+  int rc = load_gauge(ctx, U, &dev, s);
   if (rc) return rc;
   if (!(dev <= SAP_SU3_TOL)) {
     char msg[160];

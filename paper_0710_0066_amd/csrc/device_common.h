@@ -43,6 +43,9 @@ template <class R> __device__ __forceinline__ cx<R> cjfma(cx<R> acc, cx<R> a, cx
   return acc;
 }
 
+// the larger of two values, NaN if either is
+__device__ __forceinline__ double nanmax(double a, double b) { return (a > b || a != a) ? a : b; }
+
 // third row of an SU(3) matrix from its first two (m[0..5], row-major): the rows are
 // orthonormal with unit determinant, so row 3 = conj(row 1 x row 2)
 template <class R> __device__ __forceinline__ void third_row(cx<R> m[9]) {

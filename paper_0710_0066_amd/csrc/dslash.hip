@@ -91,10 +91,11 @@ __device__ __forceinline__ void store_out_red(typename vec2<R>::type* ob, const 
   st_site<R, NT>(ob, j, v);
 }
 
-// The hop kernels read two-row link copies (FP64 or FP32) and rebuild the third row from
-// unitarity and unit determinant: row 3 = conj(row 1 x row 2). o24 is the offset of the
-// site's tile row, tiled(j, 0, 24) with the lane j % 64. FP64 entries are 16 bytes each
-// (entry e of link mu at o24 + (6 mu + e) * 64). The FP32 copy holds the six entries of a
+// The hop kernels read two rows of each link and rebuild the third from unitarity and unit
+// determinant: row 3 = conj(row 1 x row 2). o24 is the offset of the site's tile row in a
+// two-row copy, tiled(j, 0, 24) with the lane j % 64. FP64 kernels read the first six of
+// the nine entries of the whole links, 16 bytes each (entry e of link mu at tiled(j, 9 mu + e,
+// 36): 6 KB runs, so that a copy of their own would only cost its writing). The FP32 copy holds the six entries of a
 // link as three pairs, each pair one 16-byte word per lane: pair k = (2k, 2k + 1) of link mu
 // at float2 offset  tile * 24 * 64 + (6 mu + 2k) * 64 + 2 lane  (+1 for the odd entry),
 // so that a link takes three 16-byte loads.
@@ -111,7 +112,8 @@ __device__ __forceinline__ void load_link_at(const typename vec2<R>::type* U, lo
       m[2 * k + 1] = {v.z, v.w};
     }
   } else {
-    const typename vec2<R>::type* p = U + par * 24 * Vhp + o24 + 6 * mu * TILE;
+    const long long lane = o24 & (TILE - 1);
+    const typename vec2<R>::type* p = U + par * 36 * Vhp + (o24 - lane) / 2 * 3 + lane + 9 * mu * TILE;
 #pragma unroll
     for (int e = 0; e < 6; ++e) m[e] = ld<R>(p + e * TILE);
   }
@@ -136,7 +138,8 @@ __device__ __forceinline__ void load_link_raw(const typename vec2<R>::type* U, l
       m[2 * k + 1] = {v.z, v.w};
     }
   } else {
-    const typename vec2<R>::type* p = U + par * 24 * Vhp + o24 + 6 * mu * TILE;
+    const long long lane = o24 & (TILE - 1);
+    const typename vec2<R>::type* p = U + par * 36 * Vhp + (o24 - lane) / 2 * 3 + lane + 9 * mu * TILE;
 #pragma unroll
     for (int e = 0; e < 6; ++e) m[e] = ld<R>(p + e * TILE);
   }

@@ -19,8 +19,8 @@ void launch_plaq_total(const Geo& g, const double* part, double* out, hipStream_
 void launch_shift_links(const Geo& g, double2* out, const double2* in, int n, hipStream_t s);
 // out[0] = sum_x sum_{mu>nu} Re tr U_P (part: gauge_parts(g) doubles of scratch)
 void launch_plaq_sum(const Geo& g, const double2* U, double* part, double* out, hipStream_t s);
-// out[0] = max over the links of max(max_e |(U U^+ - 1)_e|, |det U - 1|) (NaN if any is NaN)
-void launch_su3_dev(const Geo& g, const double2* U, double* part, double* out, hipStream_t s);
+// out[0] = the largest of n partials (NaN if any is NaN)
+void launch_max_parts(int n, const double* part, double* out, hipStream_t s);
 void launch_kinetic(const Geo& g, const double* P, double* part, double* out, hipStream_t s);
 void launch_norm2_full(const Geo& g, const double2* f, double* part, double* out, hipStream_t s);
 // U <- exp(dt P) U on every link (scaled per link by sx when given), also writing the

@@ -346,48 +346,20 @@ void k_gauge_force(Geo g, SiteDiv d, Walk k, double* F, double c, const double2*
   });
 }
 
-// Per-workgroup maximum over the links of the largest deviation from SU(3): the largest
-// entry modulus of U U^+ - 1 and |det U - 1|. A NaN entry gives a NaN maximum (kept by
-// the comparisons below), so a non-finite field fails the check as well.
-__device__ __forceinline__ double nanmax(double a, double b) { return (a > b || a != a) ? a : b; }
-__global__ __launch_bounds__(256) void k_su3_dev(Geo g, const double2* U, double* part) {
-  __shared__ double sh[4];
-  const int p = threadIdx.x >> 7;
-  const long long j = (long long)blockIdx.x * 128 + (threadIdx.x & 127);
-  double dev = 0.0;
-  if (j < g.Vh) {
-    for (int mu = 0; mu < 4; ++mu) {
-      const M3 u = load_U(U, g.Vhp, p, j, mu);
-      const M3 uu = mmul_nd(u, u);
-#pragma unroll
-      for (int e = 0; e < 9; ++e) {
-        const double re = uu.m[e].r - ((e % 4 == 0) ? 1.0 : 0.0);
-        dev = nanmax(dev, sqrt(re * re + uu.m[e].i * uu.m[e].i));
-      }
-      // det = row 0 . (row 1 x row 2)
-      const C c0 = cmul(u.m[4], u.m[8]) - cmul(u.m[5], u.m[7]);
-      const C c1 = cmul(u.m[5], u.m[6]) - cmul(u.m[3], u.m[8]);
-      const C c2 = cmul(u.m[3], u.m[7]) - cmul(u.m[4], u.m[6]);
-      const C det = cmul(u.m[0], c0) + cmul(u.m[1], c1) + cmul(u.m[2], c2);
-      dev = nanmax(dev, sqrt((det.r - 1.0) * (det.r - 1.0) + det.i * det.i));
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) dev = nanmax(dev, __shfl_down(dev, off, 64));
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = dev;
-  __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = nanmax(nanmax(sh[0], sh[1]), nanmax(sh[2], sh[3]));
-}
-
-// one wavefront of 64 lanes: lane l takes part[l], part[l + 64], ... in order, then a
-// fixed shuffle tree combines the lanes (the result does not depend on timing)
-__global__ void k_max_parts(int n, const double* part, double* out) {
-  const int l = threadIdx.x;
+// one workgroup: thread t takes part[t], part[t + 1024], ..., then a fixed tree (the result
+// does not depend on timing)
+__global__ __launch_bounds__(1024) void k_max_parts(int n, const double* part, double* out) {
+  __shared__ double sh[16];
   double m = 0.0;
-  for (int i = l; i < n; i += 64) m = nanmax(m, part[i]);
+  for (int i = threadIdx.x; i < n; i += 1024) m = nanmax(m, part[i]);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = nanmax(m, __shfl_down(m, off, 64));
-  if (l == 0) out[0] = m;
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) m = nanmax(m, sh[w]);
+    out[0] = m;
+  }
 }
 
 // Per-workgroup partial of 1/2 sum p^2 over valid sites
@@ -672,9 +644,8 @@ void launch_plaq_sum(const Geo& g, const double2* U, double* part, double* out, 
   hipLaunchKernelGGL(k_plaq<false>, dim3(k.blocks), dim3(384), 0, s, g, site_div(g), k, U, part, nullptr);
   launch_plaq_total(g, part, out, s);
 }
-void launch_su3_dev(const Geo& g, const double2* U, double* part, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_su3_dev, dim3(site_blocks(g)), dim3(256), 0, s, g, U, part);
-  hipLaunchKernelGGL(k_max_parts, dim3(1), dim3(64), 0, s, (int)site_blocks(g), part, out);
+void launch_max_parts(int n, const double* part, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_max_parts, dim3(1), dim3(1024), 0, s, n, part, out);
 }
 void launch_kinetic(const Geo& g, const double* P, double* part, double* out, hipStream_t s) {
   hipLaunchKernelGGL(k_kinetic, dim3(site_blocks(g)), dim3(256), 0, s, g, P, part);

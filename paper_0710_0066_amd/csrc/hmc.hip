@@ -48,7 +48,7 @@ int sap_force_create(sap_ctx* c) {
   bool ok = true;
   for (int i = 0; i < 12; ++i) ok = ok && hipMalloc((void**)&w->f[i], fb) == hipSuccess;
   ok = ok && hipMalloc((void**)&w->mom, (size_t)64 * c->Vhp * 8) == hipSuccess;
-  ok = ok && hipMalloc((void**)&w->part, (size_t)(std::max((int)((c->Vh + 127) / 128), gauge_parts(c->g)) + 8) * 8) == hipSuccess;
+  ok = ok && hipMalloc((void**)&w->part, (size_t)(std::max({(int)((c->Vh + 127) / 128), gauge_parts(c->g), load_gauge_parts(c->g)}) + 8) * 8) == hipSuccess;
   ok = ok && hipMalloc((void**)&w->scal, 64 * 8) == hipSuccess;
   ok = ok && hipHostMalloc((void**)&w->h_scal, 64 * 8, 0) == hipSuccess;
   ok = ok && hipMalloc((void**)&w->sx, (size_t)c->geom.L[0] * 4 * 8) == hipSuccess;
@@ -325,8 +325,8 @@ int kinetic_host(sap_ctx* c, const double* P, double* K, hipStream_t s) {
   return SAP_OK;
 }
 
-void links_changed(sap_ctx* c, hipStream_t s) { launch_gauge_to_f32(c->g, c->U64c, c->U32, c->U16, c->U64, s); }
-LinkCopies copies_of(sap_ctx* c) { return LinkCopies{c->U64c, c->U32, c->U16}; }
+void links_changed(sap_ctx* c, hipStream_t s) { launch_gauge_to_f32(c->g, c->U32, c->U16, c->U64, s); }
+LinkCopies copies_of(sap_ctx* c) { return LinkCopies{c->U32, c->U16}; }
 
 // Momentum kicks of both integrators. The forces depend on the links only, so kicks between
 // two link moves commute and add: p -= dt_1 F_j, p -= dt_2 F_j is p -= (dt_1 + dt_2) F_j. A
@@ -518,10 +518,13 @@ int hamiltonian4(Traj4& T, double* K, double S[5]) {
 
 }  // namespace
 
-// Largest deviation of the context's FP64 links from SU(3) (host output; synchronises).
-int su3_deviation_host(sap_ctx* c, double* dev, hipStream_t s) {
+// Load the canonical links U into the context's copies; *dev: their largest deviation from
+// SU(3) (host output; synchronises).
+int load_gauge(sap_ctx* c, const double* U, double* dev, hipStream_t s) {
   ForceWS* w = fws(c);
-  launch_su3_dev(c->g, c->U64, w->part, w->scal, s);
+  launch_load_gauge(c->g, c->U64, c->U32, c->U16, (const double2*)U, w->part, s);
+  launch_max_parts(load_gauge_parts(c->g), w->part, w->scal, s);
+  SAP_HIP_CHECK(c, hipGetLastError());
   SAP_HIP_CHECK(c, hipMemcpyAsync(w->h_scal, w->scal, 8, hipMemcpyDeviceToHost, s));
   SAP_HIP_CHECK(c, hipStreamSynchronize(s));
   *dev = w->h_scal[0];

@@ -20,7 +20,7 @@ namespace sap {
 // ps = 0, no = 12*Vhp (a half2 and a float are both 4 bytes).
 // Gauge field: link (parity p, site j, mu, entry e = 3*row + col) at
 //   p*36*Vhp + tiled(j, 9*mu + e, 36)   (FP64);
-// the copies the hop kernels read (FP64, FP32, FP16) hold rows 0 and 1 only (e < 6), at
+// the copies the FP32 and FP16 hop kernels read hold rows 0 and 1 only (e < 6), at
 // p*24*Vhp + tiled(j, 6*mu + e, 24) (FP32: the entries of a tile row stored in pairs, one
 // 16-byte word per lane; FP16: a quad and a pair of entries per link, see
 // gauge_to_f32_kernel), and the kernels rebuild row 2 from
@@ -128,12 +128,15 @@ void launch_pack_spinor(const Geo& g, typename vec2<R>::type* out, const double2
 template <class R>
 void launch_unpack_spinor(const Geo& g, double2* out, const typename vec2<R>::type* in,
                           int nrhs, hipStream_t s);
-void launch_pack_gauge(const Geo& g, double2* U64, float2* U32, const double2* in, hipStream_t s);
+// canonical links -> the context's FP64 links and their reduced copies, with one partial per
+// workgroup (load_gauge_parts(g)) of the largest deviation from SU(3)
+int load_gauge_parts(const Geo& g);
+void launch_load_gauge(const Geo& g, double2* U64, float2* U32, __half2* U16, const double2* in, double* part,
+                       hipStream_t s);
 void launch_unpack_gauge(const Geo& g, double2* out, const double2* U64, hipStream_t s);
-// the reduced link copies of the hop kernels from the FP64 links: two-row FP64, FP32 and
-// FP16 copies, then the three-row FP16 copy of the LDS-staged FP16 hop (layouts in
-// layout.hip)
-void launch_gauge_to_f32(const Geo& g, double2* U64c, float2* U32, __half2* U16, const double2* U64, hipStream_t s);
+// the reduced link copies of the hop kernels from the FP64 links: two-row FP32 and FP16
+// copies, then the three-row FP16 copy of the LDS-staged FP16 hop (layouts in layout.hip)
+void launch_gauge_to_f32(const Geo& g, float2* U32, __half2* U16, const double2* U64, hipStream_t s);
 void launch_pack_spinor16(const Geo& g, __half2* out, const double2* in, int nrhs, hipStream_t s);
 void launch_unpack_spinor16(const Geo& g, double2* out, const __half2* in, int nrhs, hipStream_t s);
 void launch_pack_momenta(const Geo& g, double* out, const double* in, hipStream_t s);
@@ -157,8 +160,8 @@ struct sap_ctx {
   long long V, Vh, Vhp;
   int device;
   bool have_gauge;
-  double2* U64;   // tiled gauge layout, 72*Vhp complex (whole links: forces, link updates)
-  double2* U64c;  // two-row FP64 copy read by the hop kernels (48*Vhp complex)
+  double2* U64;   // tiled gauge layout, 72*Vhp complex (whole links: forces, link updates; the FP64
+                  // hop kernels read the first two rows of each)
   float2* U32;    // two-row FP32 copy
   __half2* U16;   // two-row FP16 copy (48*Vhp), then the three-row FP16 copy (72*Vhp) the
                   // LDS-staged FP16 hop reads (all copies kept in step with U64)
@@ -202,7 +205,7 @@ int check_solve_opts(sap_ctx* c, const sap_solve_opts* o);
 
 // the context's link copy for storage type S
 template <class S> inline const typename sap::vec2<S>::type* gauge_of(const sap_ctx* c) {
-  if constexpr (std::is_same<S, double>::value) return c->U64c;
+  if constexpr (std::is_same<S, double>::value) return c->U64;
   else if constexpr (std::is_same<S, float>::value) return c->U32;
   else return c->U16;
 }

@@ -55,37 +55,92 @@ __global__ void unpack_spinor_kernel(Geo g, double2* out, const typename vec2<R>
   }
 }
 
-__global__ void pack_gauge_kernel(Geo g, double2* U64, float2* U32, const double2* in) {
-  const long long V = 2 * g.Vh;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= V) return;
-  const Lex c = lex_coords(g, i);
-  const int p = (c.x0 + c.x1 + c.x2 + c.x3) & 1;
-  const long long j = i >> 1;
-  for (int mu = 0; mu < 4; ++mu)
-    for (int e = 0; e < 9; ++e) {
-      double2 v = in[(i * 4 + mu) * 9 + e];
-      long long k = p * 36 * g.Vhp + tiled(j, 9 * mu + e, 36);
-      U64[k] = v;
-      if (U32) U32[k] = make_float2((float)v.x, (float)v.y);
+// Canonical links (36 complex numbers per site, sites in lexicographic order) to and from the
+// tiled layout through LDS: a workgroup owns 64 neighbouring pairs of sites (2j, 2j + 1), one of
+// each parity, a tile of both parities and 72 KB of consecutive memory. The canonical side
+// moves in whole lines, 16 bytes per lane, and a work-item then holds one link (wavefront w:
+// parity w & 1, direction w >> 1). Loading also writes the reduced copies and the workgroup's
+// largest deviation from SU(3) (an entry of U U^+ - 1, or |det U - 1|; a NaN entry gives NaN).
+// Both are bound by memory. With a work-item per site, whose 36 numbers lie 576 bytes from its
+// neighbour's, the conversion took 317 us on 24^3x48 and storing 414 us; the copies (168 us)
+// and the check (108 us) read the links again.
+constexpr int LINK_PAIRS = 64;
+
+// site of this work-item's link within the workgroup's 128 lexicographic sites
+__device__ __forceinline__ int pair_site(const Geo& g, long long j, int p, int lane) {
+  return 2 * lane + decode(g, j, p).b;
+}
+
+__global__ __launch_bounds__(512) void load_gauge_kernel(Geo g, double2* U64, LinkCopies lc, const double2* in,
+                                                        double* part) {
+  extern __shared__ double2 sl[];
+  __shared__ double sh[8];
+  const long long base = (long long)blockIdx.x * (2 * LINK_PAIRS) * 36, n = 2 * g.Vh * 36;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const int i = threadIdx.x + 512 * k;
+    if (base + i < n) sl[i] = in[base + i];
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, p = w & 1, mu = w >> 1;
+  const long long j = (long long)blockIdx.x * LINK_PAIRS + lane;
+  double dev = 0.0;
+  if (j < g.Vh) {
+    const double2* u = sl + pair_site(g, j, p, lane) * 36 + 9 * mu;
+    double2 e[9];
+    cx<double> m[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      e[k] = u[k];
+      m[k] = {e[k].x, e[k].y};
+      U64[p * 36 * g.Vhp + tiled(j, 9 * mu + k, 36)] = e[k];
     }
+    write_link_copies(lc, g.Vhp, p, j, mu, e);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        cx<double> t = cmulj(m[3 * a], m[3 * b]) + cmulj(m[3 * a + 1], m[3 * b + 1]) + cmulj(m[3 * a + 2], m[3 * b + 2]);
+        const double re = t.r - (a == b ? 1.0 : 0.0);
+        dev = nanmax(dev, sqrt(re * re + t.i * t.i));
+      }
+    // det = row 0 . (row 1 x row 2)
+    const cx<double> c0 = cmul(m[4], m[8]) - cmul(m[5], m[7]);
+    const cx<double> c1 = cmul(m[5], m[6]) - cmul(m[3], m[8]);
+    const cx<double> c2 = cmul(m[3], m[7]) - cmul(m[4], m[6]);
+    const cx<double> det = cmul(m[0], c0) + cmul(m[1], c1) + cmul(m[2], c2);
+    dev = nanmax(dev, sqrt((det.r - 1.0) * (det.r - 1.0) + det.i * det.i));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) dev = nanmax(dev, __shfl_down(dev, off, 64));
+  if (lane == 0) sh[w] = dev;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < 8; ++k) dev = nanmax(dev, sh[k]);
+    part[blockIdx.x] = dev;
+  }
 }
 
-__global__ void unpack_gauge_kernel(Geo g, double2* out, const double2* U64) {
-  const long long V = 2 * g.Vh;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= V) return;
-  const Lex c = lex_coords(g, i);
-  const int p = (c.x0 + c.x1 + c.x2 + c.x3) & 1;
-  const long long j = i >> 1;
-  for (int mu = 0; mu < 4; ++mu)
-    for (int e = 0; e < 9; ++e)
-      out[(i * 4 + mu) * 9 + e] = U64[p * 36 * g.Vhp + tiled(j, 9 * mu + e, 36)];
+__global__ __launch_bounds__(512) void unpack_gauge_kernel(Geo g, double2* out, const double2* U64) {
+  extern __shared__ double2 sl[];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, p = w & 1, mu = w >> 1;
+  const long long j = (long long)blockIdx.x * LINK_PAIRS + lane;
+  if (j < g.Vh) {
+    double2* u = sl + pair_site(g, j, p, lane) * 36 + 9 * mu;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) u[k] = U64[p * 36 * g.Vhp + tiled(j, 9 * mu + k, 36)];
+  }
+  __syncthreads();
+  const long long base = (long long)blockIdx.x * (2 * LINK_PAIRS) * 36, n = 2 * g.Vh * 36;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const int i = threadIdx.x + 512 * k;
+    if (base + i < n) out[base + i] = sl[i];
+  }
 }
 
-// FP64 / FP32 / FP16 link copies keep the first two rows of each link (6 of 9 entries):
-// entry (parity p, site j, component c = 6 mu + e) of the FP64 and FP16 copies is at
-// p*24*Vhp + tiled(j, c, 24). The FP32 copy stores the entries of a tile row in pairs
+// FP32 / FP16 link copies keep the first two rows of each link (6 of 9 entries, component
+// c = 6 mu + e). The FP32 copy stores the entries of a tile row in pairs
 // (2k, 2k + 1) of one link, one 16-byte word per lane:
 //   p*24*Vhp + (j / 64)*24*64 + (c - c % 2)*64 + 2*(j % 64) + c % 2,
 // so that a link is three 16-byte loads per work-item. The FP16 copy stores the six
@@ -184,15 +239,19 @@ template void launch_pack_spinor<float>(const Geo&, float2*, const double2*, int
 template void launch_unpack_spinor<double>(const Geo&, double2*, const double2*, int, hipStream_t);
 template void launch_unpack_spinor<float>(const Geo&, double2*, const float2*, int, hipStream_t);
 
-void launch_pack_gauge(const Geo& g, double2* U64, float2* U32, const double2* in, hipStream_t s) {
-  hipLaunchKernelGGL(pack_gauge_kernel, dim3(nblk(2 * g.Vh, 128)), dim3(128), 0, s, g, U64, U32, in);
+constexpr size_t LINK_LDS = (size_t)2 * LINK_PAIRS * 36 * sizeof(double2);
+int load_gauge_parts(const Geo& g) { return (int)nblk(g.Vh, LINK_PAIRS); }
+void launch_load_gauge(const Geo& g, double2* U64, float2* U32, __half2* U16, const double2* in, double* part,
+                       hipStream_t s) {
+  hipLaunchKernelGGL(load_gauge_kernel, dim3(load_gauge_parts(g)), dim3(512), LINK_LDS, s, g, U64,
+                     LinkCopies{U32, U16}, in, part);
 }
 void launch_unpack_gauge(const Geo& g, double2* out, const double2* U64, hipStream_t s) {
-  hipLaunchKernelGGL(unpack_gauge_kernel, dim3(nblk(2 * g.Vh, 128)), dim3(128), 0, s, g, out, U64);
+  hipLaunchKernelGGL(unpack_gauge_kernel, dim3(load_gauge_parts(g)), dim3(512), LINK_LDS, s, g, out, U64);
 }
-void launch_gauge_to_f32(const Geo& g, double2* U64c, float2* U32, __half2* U16, const double2* U64, hipStream_t s) {
+void launch_gauge_to_f32(const Geo& g, float2* U32, __half2* U16, const double2* U64, hipStream_t s) {
   const long long n = 8LL * g.Vhp;   // links: 2 parities x Vhp sites x 4 directions
-  hipLaunchKernelGGL(gauge_to_f32_kernel, dim3(nblk(n, 256)), dim3(256), 0, s, g.Vhp, LinkCopies{U64c, U32, U16}, U64);
+  hipLaunchKernelGGL(gauge_to_f32_kernel, dim3(nblk(n, 256)), dim3(256), 0, s, g.Vhp, LinkCopies{U32, U16}, U64);
 }
 void launch_pack_spinor16(const Geo& g, __half2* out, const double2* in, int nrhs, hipStream_t s) {
   long long n = 2 * g.Vh * nrhs;

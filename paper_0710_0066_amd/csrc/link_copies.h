@@ -1,7 +1,7 @@
 // The reduced link copies the hop kernels read, written per link from its nine FP64
-// entries: two-row FP64, FP32 and FP16 copies and the three-row FP16 copy of the
-// LDS-staged FP16 hop (layouts in layout.hip). The copy kernel (layout.hip) and the link
-// update (force.hip) share this writer, so that an update keeps the copies in step without
+// entries: two-row FP32 and FP16 copies and the three-row FP16 copy of the
+// LDS-staged FP16 hop (layouts in layout.hip). The load and copy kernels (layout.hip) and
+// the link update (force.hip) share this writer, so that an update keeps the copies in step without
 // reading the FP64 links again.
 #pragma once
 #include "internal.h"
@@ -9,7 +9,6 @@
 namespace sap {
 
 struct LinkCopies {
-  double2* U64c;
   float2* U32;
   __half2* U16;   // two-row copy (48*Vhp entries), then the three-row copy (72*Vhp)
 };
@@ -20,8 +19,6 @@ __device__ __forceinline__ void write_link_copies(const LinkCopies& lc, long lon
   typedef float f4w __attribute__((ext_vector_type(4)));
   const long long tile = j / TILE, lane = j % TILE;
   auto h = [](double2 v) { return __builtin_bit_cast(unsigned, __floats2half2_rn((float)v.x, (float)v.y)); };
-#pragma unroll
-  for (int k = 0; k < 6; ++k) lc.U64c[p * 24 * Vhp + tiled(j, 6 * mu + k, 24)] = e[k];
   float2* u32 = lc.U32 + p * 24 * Vhp + tile * 24 * TILE + 6 * mu * TILE + 2 * lane;
 #pragma unroll
   for (int k = 0; k < 3; ++k)

@@ -73,7 +73,7 @@ __device__ __forceinline__ void split_hop(const HopArgs<R>& A, const SplitGeo& q
         m[2 * k + 1] = {t.z, t.w};
       }
     } else {
-      const double2* u = A.U + lp * 24 * Vhp + tiled(lj, 6 * MU, 24);
+      const double2* u = A.U + lp * 36 * Vhp + tiled(lj, 9 * MU, 36);
 #pragma unroll
       for (int k = 0; k < 6; ++k) m[k] = ld<R>(u + k * TILE);
     }
