@@ -14,7 +14,7 @@
 // A = sum of the six staples of U_mu(x), from the plaquettes: U A = sum over nu of the
 // plaquette at x and the one at x - nu carried along U_nu(x - nu) (k_plaq, k_gauge_force).
 // T_U (Sec. 2, eq. 3): U <- exp(i dt P) U, exponential by scaling and squaring of a
-// degree-16 Taylor polynomial, then Gram-Schmidt reunitarisation with the third row the
+// degree-16 Taylor polynomial, its powers reduced by the characteristic equation, then Gram-Schmidt reunitarisation with the third row the
 // conjugate cross product of the first two (exactly unitary, det 1 up to rounding).
 #include "force.h"
 #include "split.h"
@@ -387,30 +387,45 @@ __global__ __launch_bounds__(1024) void k_sum_parts(int n, const double* part, d
   if (threadIdx.x == 0) out[0] = s;
 }
 
-// exp(A) for anti-Hermitian 3x3 A (Taylor degree 16 after scaling by 2^-k, |A/2^k| <= 1/2)
-__device__ M3 expm_ah(const M3& A) {
+// exp(i H) for traceless Hermitian 3x3 H: Taylor degree 16 after scaling by 2^-k, |H / 2^k| <=
+// 1/2 (remainder 2e-20). H^3 = c1 H + c0 with c1 = tr H^2 / 2 and c0 = det H, so every power
+// is a_n + b_n H + d_n H^2 with real a, b, d: the sum takes a few scalar operations per term and
+// one matrix square, where the series in matrices took sixteen products (213 us of FP64 issue
+// in a link update of 24^3x48).
+__device__ __forceinline__ M3 expm_ih(M3 H) {
   double nrm = 0.0;
 #pragma unroll
-  for (int e = 0; e < 9; ++e) nrm += A.m[e].r * A.m[e].r + A.m[e].i * A.m[e].i;
+  for (int e = 0; e < 9; ++e) nrm += H.m[e].r * H.m[e].r + H.m[e].i * H.m[e].i;
   nrm = sqrt(nrm);
   int k = 0;
   while (nrm > 0.5 && k < 60) { nrm *= 0.5; ++k; }
   const double sc = ldexp(1.0, -k);
-  M3 B;
 #pragma unroll
-  for (int e = 0; e < 9; ++e) B.m[e] = sc * A.m[e];
-  // Horner: E = I + B(I + B/2(I + B/3(... (I + B/16))))
+  for (int e = 0; e < 9; ++e) H.m[e] = sc * H.m[e];
+  const M3 H2 = mmul(H, H);
+  const double c1 = 0.5 * (H2.m[0].r + H2.m[4].r + H2.m[8].r);
+  // det H = tr H^3 / 3 (traceless): tr(H^2 H)
+  double c0 = 0.0;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) c0 += H2.m[3 * i + j].r * H.m[3 * j + i].r - H2.m[3 * i + j].i * H.m[3 * j + i].i;
+  c0 *= 1.0 / 3.0;
+  // f = sum_n i^n / n! (a_n, b_n, d_n), from the last term down: (a, b, d) <- Horner in H
+  C f0 = {1.0, 0.0}, f1 = {0.0, 0.0}, f2 = {0.0, 0.0};
+#pragma unroll
+  for (int n = 16; n >= 1; --n) {
+    // f <- 1 + (i H / n) f:  H (f0 + f1 H + f2 H^2) = f2 c0 + (f0 + f2 c1) H + f1 H^2
+    const double inv = 1.0 / n;
+    const C g0 = inv * times_i(c0 * f2), g1 = inv * times_i(f0 + c1 * f2), g2 = inv * times_i(f1);
+    f0 = {1.0 + g0.r, g0.i};
+    f1 = g1;
+    f2 = g2;
+  }
   M3 E;
 #pragma unroll
-  for (int e = 0; e < 9; ++e) E.m[e] = {0.0, 0.0};
-  E.m[0] = E.m[4] = E.m[8] = {1.0, 0.0};
-  for (int n = 16; n >= 1; --n) {
-    M3 T = mmul(B, E);
-    const double inv = 1.0 / n;
-#pragma unroll
-    for (int e = 0; e < 9; ++e) E.m[e] = inv * T.m[e];
-    E.m[0].r += 1.0; E.m[4].r += 1.0; E.m[8].r += 1.0;
-  }
+  for (int e = 0; e < 9; ++e) E.m[e] = cmul(f1, H.m[e]) + cmul(f2, H2.m[e]);
+  E.m[0] = E.m[0] + f0; E.m[4] = E.m[4] + f0; E.m[8] = E.m[8] + f0;
   for (int i = 0; i < k; ++i) E = mmul(E, E);
   return E;
 }
@@ -439,41 +454,35 @@ __device__ M3 reunitarize(const M3& U) {
   return R;
 }
 
-// U_mu(x) <- exp(i dt P_mu(x)) U_mu(x), P = sum_a p^a lambda^a / 2
+// U_mu(x) <- exp(i dt P_mu(x)) U_mu(x), P = sum_a p^a lambda^a / 2, and the reduced copies of
+// the hop kernels from the new link in registers. One work-item per link, a wavefront per
+// direction for 64 sites of one parity (blockIdx.y).
 __global__ __launch_bounds__(256) void k_update_links(Geo g, double2* U, LinkCopies lc, const double* Pm, double dt0,
                                                       const double* sx) {
-  const int p = threadIdx.x >> 7;
-  const long long j = (long long)blockIdx.x * 128 + (threadIdx.x & 127);
+  const int mu = threadIdx.x >> 6, p = blockIdx.y;
+  const long long j = (long long)blockIdx.x * 64 + (threadIdx.x & 63);
   if (j >= g.Vh) return;
-  const int x0 = (int)(j / g.V3h);
-  for (int mu = 0; mu < 4; ++mu) {
-    const double dt = dt0 * (sx ? sx[x0 * 4 + mu] : 1.0);
-    if (dt == 0.0) continue;                   // inactive link: stays as it is
-    const double* q = Pm + p * 32 * g.Vhp + tiled(j, 8 * mu, 32);
-    double a[8];
+  const double dt = dt0 * (sx ? sx[(int)(j / g.V3h) * 4 + mu] : 1.0);
+  if (dt == 0.0) return;                       // inactive link: stays as it is
+  const double* q = Pm + p * 32 * g.Vhp + tiled(j, 8 * mu, 32);
+  double a[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) a[k] = q[k * TILE];
-    const double r3 = 0.57735026918962576451;
-    // P (Hermitian), then A = i dt P
-    C P[9];
-    P[0] = {0.5 * (a[2] + r3 * a[7]), 0.0};
-    P[4] = {0.5 * (-a[2] + r3 * a[7]), 0.0};
-    P[8] = {-r3 * a[7], 0.0};
-    P[1] = {0.5 * a[0], -0.5 * a[1]}; P[3] = {0.5 * a[0], 0.5 * a[1]};
-    P[2] = {0.5 * a[3], -0.5 * a[4]}; P[6] = {0.5 * a[3], 0.5 * a[4]};
-    P[5] = {0.5 * a[5], -0.5 * a[6]}; P[7] = {0.5 * a[5], 0.5 * a[6]};
-    M3 A;
+  for (int k = 0; k < 8; ++k) a[k] = dt * q[k * TILE];
+  const M3 V = load_U(U, g.Vhp, p, j, mu);
+  const double r3 = 0.57735026918962576451;
+  M3 H;                                        // dt P
+  H.m[0] = {0.5 * (a[2] + r3 * a[7]), 0.0};
+  H.m[4] = {0.5 * (-a[2] + r3 * a[7]), 0.0};
+  H.m[8] = {-r3 * a[7], 0.0};
+  H.m[1] = {0.5 * a[0], -0.5 * a[1]}; H.m[3] = {0.5 * a[0], 0.5 * a[1]};
+  H.m[2] = {0.5 * a[3], -0.5 * a[4]}; H.m[6] = {0.5 * a[3], 0.5 * a[4]};
+  H.m[5] = {0.5 * a[5], -0.5 * a[6]}; H.m[7] = {0.5 * a[5], 0.5 * a[6]};
+  const M3 Un = reunitarize(mmul(expm_ih(H), V));
+  store_U(U, g.Vhp, p, j, mu, Un);
+  double2 e[9];
 #pragma unroll
-    for (int e = 0; e < 9; ++e) A.m[e] = {-dt * P[e].i, dt * P[e].r};
-    const M3 E = expm_ah(A);
-    const M3 Un = reunitarize(mmul(E, load_U(U, g.Vhp, p, j, mu)));
-    store_U(U, g.Vhp, p, j, mu, Un);
-    // the reduced copies of the hop kernels, from the new link in registers
-    double2 e[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) e[k] = make_double2(Un.m[k].r, Un.m[k].i);
-    write_link_copies(lc, g.Vhp, p, j, mu, e);
-  }
+  for (int k = 0; k < 9; ++k) e[k] = make_double2(Un.m[k].r, Un.m[k].i);
+  write_link_copies(lc, g.Vhp, p, j, mu, e);
 }
 
 // U'(x0, ...) = U(x0 + n, ...): translation of the gauge field by n slices in x0
@@ -657,7 +666,7 @@ void launch_norm2_full(const Geo& g, const double2* f, double* part, double* out
 }
 void launch_update_links(const Geo& g, double2* U, const LinkCopies& lc, const double* P, double dt, hipStream_t s,
                          const double* sx) {
-  hipLaunchKernelGGL(k_update_links, dim3(site_blocks(g)), dim3(256), 0, s, g, U, lc, P, dt, sx);
+  hipLaunchKernelGGL(k_update_links, dim3((unsigned)((g.Vh + 63) / 64), 2), dim3(256), 0, s, g, U, lc, P, dt, sx);
 }
 void launch_spin_op(const Geo& g, int mode, int l0, double2* out, const double2* in, const double2* in2,
                     hipStream_t s, int outer) {
