@@ -573,7 +573,7 @@ __global__ __launch_bounds__(128) void hop_march_kernel(HopArgs<R> A, int nck) {
   const long long rem = l - x0 * per_slice;
   const int chunk = (int)(rem / ngroups);
   const int r0 = (int)(rem - (long long)chunk * ngroups) * NR;
-  if (x0 >= A.g.L0) return;
+  if (x0 >= A.g.L0 || hop_idle(A, r0, min(NR, A.nrhs - r0), x0, x0 + 1)) return;
   const int lo = (int)((long long)A.g.V3h * xcd / 8);
   const int hi = (int)((long long)A.g.V3h * (xcd + 1) / 8);
   int p, s;
@@ -921,6 +921,7 @@ void hop_slab_kernel(HopArgs<R> A, int TA, int TB) {
   const int x0a = (int)((long long)g.L0 * xcd / 8), x0b = (int)((long long)g.L0 * (xcd + 1) / 8);
   if (tile >= ntile || x0a >= x0b) return;      // whole workgroup, before any barrier
   const int nr = min(NR, A.nrhs - r0);
+  if (hop_idle(A, r0, nr, x0a, x0b)) return;    // likewise
   const int x1a = (tile / nt2) * TA, x2a = (tile % nt2) * TB;
   const int t = threadIdx.x;
   const bool act = t < S;
@@ -1351,7 +1352,7 @@ void hop_slabd_kernel(HopArgs<SR> A, int TA, int TB) {
   const int tile = l / A.nrhs;
   const int r0 = l - tile * A.nrhs;
   const int x0a = g.L0 * xcd / 8, x0b = g.L0 * (xcd + 1) / 8;
-  if (tile >= ntile || x0a >= x0b) return;      // whole workgroup, before any barrier
+  if (tile >= ntile || x0a >= x0b || hop_idle(A, r0, 1, x0a, x0b)) return;   // whole workgroup, before any barrier
   const int x1a = (tile / nt2) * TA, x2a = (tile % nt2) * TB;
   const int t = threadIdx.x;
   const bool act = t < S, hact = t < H;

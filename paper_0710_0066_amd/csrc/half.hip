@@ -105,6 +105,10 @@ __global__ __launch_bounds__(256) void hop16_kernel(HopArgs<h16> A) {
     j = chunk * 256 + threadIdx.x;
   }
   if (j >= A.g.Vh) return;
+  if (A.active) {
+    const int x0 = (int)(j / A.g.V3h);
+    if (hop_idle(A, rhs, 1, x0, x0 + 1)) return;
+  }
   hop16_site<1, G5I, G5O>(A, p, j, rhs, 1);
 }
 
@@ -122,7 +126,7 @@ __global__ __launch_bounds__(128) void hop16_march_kernel(HopArgs<h16> A, int nc
   const long long rem = l - x0 * per_slice;
   const int chunk = (int)(rem / ngroups);
   const int r0 = (int)(rem - (long long)chunk * ngroups) * NR;
-  if (x0 >= A.g.L0) return;
+  if (x0 >= A.g.L0 || hop_idle(A, r0, min(NR, A.nrhs - r0), x0, x0 + 1)) return;
   const int lo = (int)((long long)A.g.V3h * xcd / 8);
   const int hi = (int)((long long)A.g.V3h * (xcd + 1) / 8);
   int p, s;

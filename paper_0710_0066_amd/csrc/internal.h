@@ -72,11 +72,23 @@ template <class R> struct HopArgs {
   //   npart[3 (sys * nslot + k) + i].
   double* npart = nullptr;
   int nlb = 0, nslot = 0, red = 0;
-  // optional: nonzero where a system is still iterated; the others may be left as they are
+  // optional: nonzero where a system (rhs, x0 block; the blocks of slb, or the whole lattice) is
+  // still iterated; the output of the others may be left as it is
   const int* active = nullptr;
   int keep = 0;            // split kernel: leave unselected sites as they are (else zero)
   int rev = 0;             // split kernel, linear order: walk the lattice backwards
 };
+
+// has every system of the rhs r0 .. r0 + nr - 1 in the slices xa .. xb - 1 converged (HopArgs::active)?
+template <class R>
+__device__ __forceinline__ bool hop_idle(const HopArgs<R>& A, int r0, int nr, int xa, int xb) {
+  if (!A.active) return false;
+  const int len = A.slb ? A.slb : A.g.L0, nblk = A.g.L0 / len;
+  for (int r = r0; r < r0 + nr; ++r)
+    for (int b = xa / len; b <= (xb - 1) / len; ++b)
+      if (A.active[r * nblk + b]) return false;
+  return true;
+}
 
 // Work-item mappings of the hop kernel for several right-hand sides.
 enum { HOP_MAP_SITE = 0,    // split kernel: a site's eight hops on eight wavefronts (FP16: one

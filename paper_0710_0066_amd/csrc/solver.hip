@@ -288,7 +288,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
     int nslot = hop_red_slots(hop_args<R>(c, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0), nlb);
     if ((size_t)3 * nslot * nsys > w->part_cap) nslot = 0;       // no room in the partial buffers
     // several systems: those that have converged are skipped (version v of active)
-    auto live = [&](int v) { return nsys > 1 ? w->active + v * nsys : nullptr; };
+    auto live = [&](int v) { return w->active + v * nsys; };
     // y = a x + b D in on the even sites with its reductions red in part
     // consecutive kernels walk the lattice in opposite directions, so that each begins with
     // what the one before left in the caches
