@@ -73,13 +73,12 @@ template <class R> void blas_cg_s(const SysGrid& G, int nrhs, Field<R> sf, Field
 // 1 - v); x += alpha p, then p = r + beta p
 template <class R> void blas_cg_xp(const SysGrid& G, int nrhs, Field<R> x, Field<R> p, Field<R> r, const SysScal& S,
                                    int v, Parts ss, Parts rr, hipStream_t s);
-template <class Ro, class Ri> void blas_convert(const SysGrid& G, int nrhs, Field<Ro> out, Field<Ri> in,
-                                                int npar, hipStream_t s);
-template <class R> void blas_add_mixed(const SysGrid& G, int nrhs, Field<double> x, Field<R> e, hipStream_t s);
-// r = b - Ax over the first npar parities (2: both; 1: the even sites), npar * nchunk
-// partials ||r||^2 per system
-void blas_resid(const SysGrid& G, int nrhs, Field<double> r, Field<double> b, Field<double> Ax, double* part,
-                hipStream_t s, int npar = 2);
+// out = scale * in on the even sites at another precision, partial ||out||^2
+template <class R> void blas_convert(const SysGrid& G, int nrhs, Field<R> out, Field<double> in, double scale,
+                                     double* part, hipStream_t s);
+// even sites of the selected systems: x += e (e at another precision), w = b - aI x
+template <class R> void blas_add_resid(const SysGrid& G, int nrhs, Field<double> x, Field<R> e, Field<double> b,
+                                       Field<double> w, double aI, hipStream_t s);
 
 // ---- sums of partials, one wavefront per system in a fixed order
 void fin_sum(int nsys, Parts a, double* out, hipStream_t s);

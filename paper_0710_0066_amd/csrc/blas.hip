@@ -304,21 +304,26 @@ __global__ __launch_bounds__(BT<R>) void k_cg_xp(SysGrid G, Field<R> x, Field<R>
 
 // ---- precision changes and residuals ------------------------------------------------------
 
-// out = src (both parities if npar == 2), converting precision
+// out = scale * src on the even sites, converting precision, partial ||out||^2 (before any
+// rounding to FP16); zero on unselected systems
 template <class Ro>
-__global__ __launch_bounds__(BT<Ro>) void k_convert(SysGrid G, Field<Ro> out, Field<double> in, int npar) {
+__global__ __launch_bounds__(BT<Ro>) void k_convert(SysGrid G, Field<Ro> out, Field<double> in, double scale,
+                                                   double* part) {
   typedef arith_t<Ro> Ao;
-  const Tile t = tile_of(G, npar);
+  __shared__ double sh[BT<Ro> / 64];
+  const Tile t = tile_of(G);
+  double acc[1] = {0.0};
   if constexpr (is_h16<Ro>) {
     for (long long j = t.j0 + threadIdx.x; j < t.j1; j += BT<Ro>) {
-      const SiteR<double> ir = site_r(in, t.rhs, t.p, j, G.Vhp);
-      SiteW<Ro> ow = site_w(out, t.rhs, t.p, j, G.Vhp);
+      const SiteR<double> ir = site_r(in, t.rhs, 0, j, G.Vhp);
+      SiteW<Ro> ow = site_w(out, t.rhs, 0, j, G.Vhp);
 #pragma unroll
       for (int c = 0; c < 12; ++c) {
         const cx<double> v = get(ir, c);
-        cx<Ao> w = {(Ao)v.r, (Ao)v.i};
+        cx<Ao> w = {(Ao)(scale * v.r), (Ao)(scale * v.i)};
         if (!t.selected) w = {Ao(0), Ao(0)};
         put(ow, c, w);
+        acc[0] += abs2(w);
       }
       close(ow);
     }
@@ -327,61 +332,56 @@ __global__ __launch_bounds__(BT<Ro>) void k_convert(SysGrid G, Field<Ro> out, Fi
     for (long long j = t.j0 + (threadIdx.x & 63); j < t.j1; j += 64) {
       cx<double> v[2];
       cx<Ro> w[2];
-      ld_pair<double>(in, t.rhs, t.p, j, wv, v);
+      ld_pair<double>(in, t.rhs, 0, j, wv, v);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) w[i] = t.selected ? cx<Ro>{(Ro)v[i].r, (Ro)v[i].i} : cx<Ro>{Ro(0), Ro(0)};
-      st_pair<Ro>(out, t.rhs, t.p, j, wv, w);
+      for (int i = 0; i < 2; ++i) {
+        w[i] = t.selected ? cx<Ro>{(Ro)(scale * v[i].r), (Ro)(scale * v[i].i)} : cx<Ro>{Ro(0), Ro(0)};
+        acc[0] += abs2(w[i]);
+      }
+      st_pair<Ro>(out, t.rhs, 0, j, wv, w);
     }
   }
+  block_sums<BT<Ro>, 1>(acc, sh);
+  if (threadIdx.x == 0) part[t.part] = acc[0];
 }
 
-// x64 += e (both parities), e at the inner precision
+// even sites of the selected systems: x += e, e at the inner precision, and w = b - aI x
 template <class R>
-__global__ __launch_bounds__(BT<R>) void k_add_mixed(SysGrid G, Field<double> x, Field<R> e) {
-  const Tile t = tile_of(G, 2);
+__global__ __launch_bounds__(BT<R>) void k_add_resid(SysGrid G, Field<double> x, Field<R> e, Field<double> b,
+                                                    Field<double> w, double aI) {
+  const Tile t = tile_of(G);
   if (!t.selected) return;
   if constexpr (is_h16<R>) {
-    double2* xb = x.ptr + t.rhs * x.rs + t.p * x.ps;
     for (long long j = t.j0 + threadIdx.x; j < t.j1; j += BT<R>) {
-      const SiteR<R> er = site_r(e, t.rhs, t.p, j, G.Vhp);
+      const SiteR<R> er = site_r(e, t.rhs, 0, j, G.Vhp);
 #pragma unroll
       for (int c = 0; c < 12; ++c) {
         const long long o = tiled(j, c, 12);
-        cx<double> xv = ld<double>(xb + o);
-        const cx<arith_t<R>> ev = get(er, c);
-        xv.r += (double)ev.r;
-        xv.i += (double)ev.i;
-        st<double>(xb + o, xv);
+        const cx<float> ev = get(er, c);
+        cx<double> xv = ld<double>(x.ptr + t.rhs * x.rs + o);
+        const cx<double> bv = ld<double>(b.ptr + t.rhs * b.rs + o);
+        xv = {xv.r + (double)ev.r, xv.i + (double)ev.i};
+        st<double>(x.ptr + t.rhs * x.rs + o, xv);
+        st<double>(w.ptr + t.rhs * w.rs + o, {bv.r - aI * xv.r, bv.i - aI * xv.i});
       }
     }
   } else {
-    const int wv = threadIdx.x >> 6;
+    const int wave = threadIdx.x >> 6;
     for (long long j = t.j0 + (threadIdx.x & 63); j < t.j1; j += 64) {
-      cx<double> v[2];
-      cx<R> w[2];
-      ld_pair<double>(x, t.rhs, t.p, j, wv, v);
-      ld_pair<R>(e, t.rhs, t.p, j, wv, w);
+      cx<double> xv[2], bv[2], wv[2];
+      cx<R> ev[2];
+      ld_pair<double>(x, t.rhs, 0, j, wave, xv);
+      ld_pair<double>(b, t.rhs, 0, j, wave, bv);
+      ld_pair<R>(e, t.rhs, 0, j, wave, ev);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) v[i] = {v[i].r + (double)w[i].r, v[i].i + (double)w[i].i};
-      st_pair<double>(x, t.rhs, t.p, j, wv, v);
+      for (int i = 0; i < 2; ++i) {
+        xv[i] = {xv[i].r + (double)ev[i].r, xv[i].i + (double)ev[i].i};
+        wv[i] = {bv[i].r - aI * xv[i].r, bv[i].i - aI * xv[i].i};
+      }
+      st_pair<double>(x, t.rhs, 0, j, wave, xv);
+      st_pair<double>(w, t.rhs, 0, j, wave, wv);
     }
   }
-}
-
-// r = b - Ax (FP64, the first npar parities: 2 both, 1 even only), partial ||r||^2
-__global__ __launch_bounds__(BT<double>) void k_resid(SysGrid G, Field<double> r, Field<double> b,
-                                                     Field<double> Ax, double* part, int npar) {
-  __shared__ double sh[BT<double> / 64];
-  const Tile t = tile_of(G, npar);
-  double acc[1] = {0.0};
-  const bool sel = t.selected;
-  stream<double, 2, 1>(t, G.Vhp, {b, Ax}, {r}, [] { return true; },
-                       [&](const cx<double>* in, cx<double>* out) {
-                         out[0] = sel ? in[0] - in[1] : cx<double>{0.0, 0.0};
-                         acc[0] += abs2(out[0]);
-                       });
-  block_sums<BT<double>, 1>(acc, sh);
-  if (threadIdx.x == 0) part[t.part] = acc[0];
 }
 
 // ---- sums of partials outside the iterations: one workgroup, a wavefront per system ---------
@@ -795,16 +795,13 @@ template <class R> void blas_cg_xp(const SysGrid& G, int nrhs, Field<R> x, Field
                                    int v, Parts ss, Parts rr, hipStream_t s) {
   hipLaunchKernelGGL(k_cg_xp<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, x, p, r, S, v, ss, rr);
 }
-template <class Ro, class Ri> void blas_convert(const SysGrid& G, int nrhs, Field<Ro> out, Field<Ri> in,
-                                                int npar, hipStream_t s) {
-  hipLaunchKernelGGL(k_convert<Ro>, grid_of(G, nrhs, npar), dim3(BT<Ro>), 0, s, G, out, in, npar);
+template <class R> void blas_convert(const SysGrid& G, int nrhs, Field<R> out, Field<double> in, double scale,
+                                     double* part, hipStream_t s) {
+  hipLaunchKernelGGL(k_convert<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, out, in, scale, part);
 }
-template <class R> void blas_add_mixed(const SysGrid& G, int nrhs, Field<double> x, Field<R> e, hipStream_t s) {
-  hipLaunchKernelGGL(k_add_mixed<R>, grid_of(G, nrhs, 2), dim3(BT<R>), 0, s, G, x, e);
-}
-void blas_resid(const SysGrid& G, int nrhs, Field<double> r, Field<double> b, Field<double> Ax, double* part,
-                hipStream_t s, int npar) {
-  hipLaunchKernelGGL(k_resid, grid_of(G, nrhs, npar), dim3(BT<double>), 0, s, G, r, b, Ax, part, npar);
+template <class R> void blas_add_resid(const SysGrid& G, int nrhs, Field<double> x, Field<R> e, Field<double> b,
+                                       Field<double> w, double aI, hipStream_t s) {
+  hipLaunchKernelGGL(k_add_resid<R>, grid_of(G, nrhs), dim3(BT<R>), 0, s, G, x, e, b, w, aI);
 }
 void fin_sum(int nsys, Parts a, double* out, hipStream_t s) {
   hipLaunchKernelGGL(k_fin_sum, dim3(1), dim3(FT), 0, s, nsys, a, out);
@@ -865,7 +862,9 @@ template <class R> void blas_lin3(const SysGrid& G, int nrhs, Field<R> y, Field<
                              hipStream_t);                                                                    \
   template void blas_cg_xp<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, const SysScal&, int, Parts,  \
                               Parts, hipStream_t);                                                            \
-  template void blas_add_mixed<R>(const SysGrid&, int, Field<double>, Field<R>, hipStream_t);                 \
+  template void blas_convert<R>(const SysGrid&, int, Field<R>, Field<double>, double, double*, hipStream_t);  \
+  template void blas_add_resid<R>(const SysGrid&, int, Field<double>, Field<R>, Field<double>, Field<double>, \
+                                  double, hipStream_t);                                                       \
   template void blas_cdot3<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, double*, hipStream_t);       \
   template void blas_bicg_p<R>(const SysGrid&, int, Field<R>, Field<R>, Field<R>, const SysScal&, int, Parts, \
                                hipStream_t);                                                                  \
@@ -879,8 +878,5 @@ INST(float)
 INST(h16)
 template void blas_lin3<double>(const SysGrid&, int, Field<double>, Field<double>, Field<double>, Field<double>,
                                 const double*, double*, hipStream_t);
-template void blas_convert<double, double>(const SysGrid&, int, Field<double>, Field<double>, int, hipStream_t);
-template void blas_convert<float, double>(const SysGrid&, int, Field<float>, Field<double>, int, hipStream_t);
-template void blas_convert<h16, double>(const SysGrid&, int, Field<h16>, Field<double>, int, hipStream_t);
 
 }  // namespace sap

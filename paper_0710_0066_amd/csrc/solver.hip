@@ -16,9 +16,10 @@
 // partial sums (blas.hip), so that a CG iteration is six launches with the norms written by
 // the hops; converged systems are frozen while the others continue; the host reads one
 // counter every few iterations. On 16^3x32 with one rhs and FP32 inner iterations an
-// iteration went from 93 us in ten launches to 54 us.
-// Outer loop: FP64 defect correction r = b - A x (A applied in FP64), inner solve in
-// FP32 or FP64, x += e, until ||b - A x|| / ||b|| <= tol recomputed in FP64.
+// iteration went from 93 us in ten launches to 52 us.
+// Outer loop: FP64 defect correction on the even sites: r_e = b_hat - M_hat x_e in FP64, inner
+// solve in FP16, FP32 or FP64, x_e += e, x_o = b_o + k D_oe x_e, until ||b - A x|| / ||b|| <=
+// tol recomputed in FP64.
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -37,8 +38,8 @@ int apply_op_any(sap_ctx* ctx, void* out, const void* in, int nrhs, int lb, int 
 struct SolverWS {
   int max_rhs, max_sys;
   size_t part_cap;                       // doubles in each of partA ... partE
-  double2 *hx, *s, *r, *p, *q, *t;       // half fields (sized for FP64, max_rhs)
-  double2 *x64, *r64, *ax, *rin, *e;     // full fields
+  double2 *hx, *s, *r, *p, *q, *t, *e;   // half fields (sized for FP64, max_rhs)
+  double2 *r64, *ax;                     // full fields
   double *partA, *partB, *partC, *partD, *partE;
   double *gam, *ss, *alpha, *target2, *bnorm2, *rnorm2;
   double* cs;                            // BiCGstab: complex (rho, alpha, omega, beta) per system
@@ -81,8 +82,7 @@ extern "C" int sap_solver_create(sap_ctx* c) {
   auto A = [&](void** p, size_t n) { return hipMalloc(p, n) == hipSuccess; };
   bool ok = A((void**)&w->hx, half) && A((void**)&w->s, half) && A((void**)&w->r, half) &&
             A((void**)&w->p, half) && A((void**)&w->q, half) && A((void**)&w->t, half) &&
-            A((void**)&w->x64, full) && A((void**)&w->r64, full) && A((void**)&w->ax, full) &&
-            A((void**)&w->rin, full) && A((void**)&w->e, full) &&
+            A((void**)&w->e, half) && A((void**)&w->r64, full) && A((void**)&w->ax, full) &&
             A((void**)&w->partA, npart * 8) && A((void**)&w->partB, npart * 8) &&
             A((void**)&w->partC, npart * 8) && A((void**)&w->partD, npart * 8) &&
             A((void**)&w->partE, npart * 8);
@@ -113,7 +113,7 @@ static void drop_graphs(SolverWS* w) {
 extern "C" void sap_solver_destroy(sap_ctx* c) {
   SolverWS* w = ws_of(c);
   if (!w) return;
-  void* dev[] = {w->hx, w->s, w->r, w->p, w->q, w->t, w->x64, w->r64, w->ax, w->rin, w->e,
+  void* dev[] = {w->hx, w->s, w->r, w->p, w->q, w->t, w->e, w->r64, w->ax,
                  w->partA, w->partB, w->partC, w->partD, w->partE, w->gam, w->ss, w->alpha, w->target2,
                  w->bnorm2, w->rnorm2, w->cs, w->active, w->iters, w->flags, w->selected};
   for (void* p : dev)
@@ -189,10 +189,9 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
   const SysGrid G = make_sysgrid(Vh, c->g.V3h, lb, c->geom.L[0], colour, nrhs, std::is_same<R, h16>::value);
   const int nsys = G.nblk * nrhs;
   const double kap = c->geom.kappa;
-  const Ar kR = (Ar)kap, k2R = (Ar)(-kap * kap);
+  const Ar k2R = (Ar)(-kap * kap);
   const Ar aI = (Ar)(1.0 + rho);               // unit term of M_hat + rho
-  const size_t fullb = (size_t)24 * Vhp * nrhs * sizeof(double2);
-  const size_t fullR = full_bytes<R>(Vhp, nrhs), halfR = half_bytes<R>(Vhp, nrhs);
+  const size_t fullb = (size_t)24 * Vhp * nrhs * sizeof(double2), halfR = half_bytes<R>(Vhp, nrhs);
   if (rho != 0.0 && !eo_only) return sap_fail(c, SAP_E_ARG, "a shift needs the even-site system");
   // geometric series: terms t_0 = b_hat / (1 + rho), t_{n+1} = k^2 / (1 + rho) D_eo D_oe t_n,
   // residual (1 + rho) t_{n+1}: the series works on t, so b_hat and the target are scaled
@@ -201,9 +200,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
 
   Field<double> X = {(double2*)x, 24 * Vhp, 12 * Vhp}, B = {(double2*)b, 24 * Vhp, 12 * Vhp};
   Field<double> R64 = {w->r64, 24 * Vhp, 12 * Vhp}, AX = {w->ax, 24 * Vhp, 12 * Vhp};
-  Field<R> RIN = full_field<R>(w->rin, Vhp), E = full_field<R>(w->e, Vhp);
-  Field<R> Ee = E;                             // the even half of E
-  Ee.ps = 0;
+  Field<R> Ee = half_field<R>(w->e, Vhp);
   Field<R> S = half_field<R>(w->s, Vhp), Rr = half_field<R>(w->r, Vhp), P = half_field<R>(w->p, Vhp);
   Field<R> Q = half_field<R>(w->q, Vhp), T = half_field<R>(w->t, Vhp);
   Field<R> HX = half_field<R>(w->hx, Vhp);
@@ -223,7 +220,6 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
   // ||b||^2 per system; first residual r = b
   blas_norm2<double>(G, nrhs, B, 2, w->partA, st);
   fin_sum(nsys, {w->partA, n2}, w->bnorm2, st);
-  SAP_HIP_CHECK(c, hipMemcpyAsync(w->r64, b, fullb, hipMemcpyDeviceToDevice, st));
   SAP_HIP_CHECK(c, hipMemcpyAsync(w->rnorm2, w->bnorm2, nsys * 8, hipMemcpyDeviceToDevice, st));
   SAP_HIP_CHECK(c, hipMemcpyAsync(w->h_bnorm2, w->bnorm2, nsys * 8, hipMemcpyDeviceToHost, st));
 
@@ -249,13 +245,12 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
       break;
     }
     ++outer;
-    // inner right-hand side at the inner precision
-    blas_convert<R, double>(G, nrhs, RIN, R64, 2, st);
-    // b_hat_e = r_e + k D_eo r_o  (into S; times 1 / (1 + rho) for the series)
-    hop<R>(c, S, RIN, RIN, 0, nrhs, lb, colour, geom ? (Ar)shift_inv : Ar(1),
-           geom ? (Ar)(kap * shift_inv) : kR, 0, 0, st);
-    SAP_HIP_CHECK(c, hipMemsetAsync(w->e, 0, fullR, st));
-    blas_norm2<R>(G, nrhs, S, 1, w->partB, st);
+    // the even-site residual of x = 0: b_hat = b_e + k D_eo b_o
+    if (outer == 1 && !eo_only) hop<double>(c, R64, B, B, 0, nrhs, lb, colour, 1.0, kap, 0, 0, st);
+    // inner right-hand side, the even-site residual at the inner precision (into S; times
+    // 1 / (1 + rho) for the series)
+    blas_convert<R>(G, nrhs, S, outer == 1 && eo_only ? B : R64, geom ? shift_inv : 1.0, w->partB, st);
+    SAP_HIP_CHECK(c, hipMemsetAsync(w->e, 0, halfR, st));
     // stop the inner solve at ||s|| <= max(inner_tol ||b_hat||, 0.3 tol ||b||): the outer
     // residual after x += e equals the inner one up to rounding
     fin_targets(nsys, {w->partB, n1}, w->bnorm2, inner_tol * inner_tol,
@@ -287,9 +282,9 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
     const int nlb = lb ? lb : c->geom.L[0];
     int nslot = hop_red_slots(hop_args<R>(c, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0), nlb);
     if ((size_t)3 * nslot * nsys > w->part_cap) nslot = 0;       // no room in the partial buffers
-    // several systems: those that have converged are skipped (version v of active)
+    // converged systems are skipped (version v of active), also a single one: a graph runs up to
+    // seven iterations past its end
     auto live = [&](int v) { return w->active + v * nsys; };
-    // y = a x + b D in on the even sites with its reductions red in part
     // consecutive kernels walk the lattice in opposite directions, so that each begins with
     // what the one before left in the caches
     int dir = 0;
@@ -299,6 +294,7 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
       t.rev = turn();
       return t;
     };
+    // y = a x + b D in on the even sites with its reductions red in part
     auto hop_red = [&](Field<R> y, Field<R> in, Field<R> x, Ar a, Ar b, int g5o, double* part, int red, int v,
                        hipStream_t q) -> Parts {
       const int nv = red == 3 ? 3 : 1;
@@ -395,22 +391,27 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
       }
       total_iters += ITERS_PER_GRAPH;
     }
-    // e_o = r_o + k D_oe e_e ; x += e ; r = b - A x (FP64)
-    if (!eo_only) hop<R>(c, E, Ee, RIN, 1, nrhs, lb, colour, Ar(1), kR, 0, 0, st);
-    blas_add_mixed<R>(G, nrhs, X, E, st);
-    if (eo_only) {
-      // A x = (M_hat + rho) x_e on the even sites, via the odd half of AX
-      const Field<double> NONE64 = {nullptr, 0, 0};
-      hop<double>(c, AX, X, NONE64, 1, nrhs, lb, colour, 0.0, 1.0, 0, 0, st);
-      hop<double>(c, AX, AX, X, 0, nrhs, lb, colour, 1.0 + rho, -kap * kap, 0, 0, st);
-      blas_resid(G, nrhs, R64, B, AX, w->partA, st, 1);
-    } else {
-      int rc = apply_op_any(c, w->ax, x, nrhs, lb, colour < 3 ? colour : 0, colour < 3 ? -1 : colour - 3,
-                            SAP_F64, st);
-      if (rc) return rc;
-      blas_resid(G, nrhs, R64, B, AX, w->partA, st);
+    // x_e += e and, in FP64, x_o = b_o + k D_oe x_e, which leaves a residual on the even sites
+    // only: r_e = b_e - x_e + k D_eo x_o (even-site systems: r_e = b_e - (1 + rho) x_e +
+    // k^2 D_eo D_oe x_e), its norm summed by the hop where its mapping can. The
+    // loop is bound by memory, at 24^3x48 with 12 rhs by 1.5 GB fields: correcting both
+    // parities, M x and b - M x read and wrote about twice as many. FP16 BiCGstab on 24^3x2
+    // blocks (five corrections) 88.8 -> 81.7 ms, FP32 CG (three) 409 -> 404 ms.
+    blas_add_resid<R>(G, nrhs, X, Ee, B, R64, 1.0 + rho, st);
+    const Field<double> NONE64 = {nullptr, 0, 0};
+    if (eo_only) hop<double>(c, AX, X, NONE64, 1, nrhs, lb, colour, 0.0, 1.0, 0, 0, st);
+    else hop<double>(c, X, X, B, 1, nrhs, lb, colour, 1.0, kap, 0, 0, st);
+    const Field<double> XO = eo_only ? AX : X;
+    const double kr = eo_only ? kap * kap : kap;
+    int nr = hop_red_slots(hop_args<double>(c, R64, XO, R64, 0, nrhs, lb, colour, 1.0, kr, 0, 0), nlb);
+    if ((size_t)nr * nsys > w->part_cap) nr = 0;
+    hop<double>(c, R64, XO, R64, 0, nrhs, lb, colour, 1.0, kr, 0, 0, st,
+                nr ? Fused{w->partA, nlb, nr, 1} : Fused{});
+    if (!nr) {
+      blas_norm2<double>(G, nrhs, R64, 1, w->partA, st);
+      nr = n1;
     }
-    fin_sum(nsys, {w->partA, eo_only ? n1 : n2}, w->rnorm2, st);
+    fin_sum(nsys, {w->partA, nr}, w->rnorm2, st);
     SAP_HIP_CHECK(c, hipGetLastError());
   }
   if (info) {
