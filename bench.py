@@ -210,7 +210,7 @@ def hbm_probe(sap, torch, gib=2):
     return res
 
 
-KERNEL_SOURCES = ("dslash.hip", "half.hip", "site_io.h", "device_common.h", "internal.h")
+KERNEL_SOURCES = ("dslash.hip", "half.hip", "split.hip", "split.h", "site_io.h", "device_common.h", "internal.h")
 
 
 def kernel_source_hash():

@@ -216,9 +216,9 @@ size_t sap_field_bytes(const sap_ctx* ctx, sap_prec prec, int nrhs);
 size_t sap_momenta_bytes(const sap_ctx* ctx);
 
 /* Load the gauge field from the canonical layout (device, complex128) into the
- * context's FP64 links and the FP64, FP32 and FP16 copies the hop kernels read. The links
- * must be SU(3): the hop copies keep the first two rows of each link and the hop kernels
- * of every precision rebuild the third from unitarity and unit determinant (the force,
+ * context's FP64 links and the FP32 and FP16 copies the hop kernels read. The links must
+ * be SU(3): the hop kernels read the first two rows of each link (in FP64 of the links
+ * themselves) and rebuild the third from unitarity and unit determinant (the force,
  * gauge-force and link-update kernels read the whole FP64 links). Checked on the device:
  * if the largest entry modulus of U U^+ - 1 or |det U - 1| over all links exceeds 1e-10
  * (or is not finite) the call returns SAP_E_ARG and the context holds no gauge field

@@ -79,7 +79,10 @@ template <class R> struct HopArgs {
   int rev = 0;             // split kernel, linear order: walk the lattice backwards
 };
 
-// has every system of the rhs r0 .. r0 + nr - 1 in the slices xa .. xb - 1 converged (HopArgs::active)?
+// has every system of the rhs r0 .. r0 + nr - 1 in the slices xa .. xb - 1 converged
+// (HopArgs::active)? Such workgroups end at once: a graph of eight iterations runs up to seven
+// past the last system's end. FP16 BiCGstab on 24^3x48, 12 rhs, 24^3x2 blocks (corrections of
+// nine or ten iterations) 106 -> 91 ms, FP32 CG on 16^3x32 with one rhs 7.87 -> 7.67 ms.
 template <class R>
 __device__ __forceinline__ bool hop_idle(const HopArgs<R>& A, int r0, int nr, int xa, int xb) {
   if (!A.active) return false;
