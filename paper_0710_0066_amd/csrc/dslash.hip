@@ -53,15 +53,19 @@ __device__ __forceinline__ void store_out(typename vec2<R>::type* ob, const type
   st_site<R, NT>(ob, j, v);
 }
 
+// holds a sum where it is formed (left alone, the compiler moves FP64 sums behind later loads and
+// spills)
+__device__ __forceinline__ void pin(double& a) { asm volatile("" : "+v"(a)); }
+
 // store_out with reductions of the stored values v (red[0..2], see HopArgs::red): RED 1
-// ||v||^2; RED 3 <v, x> and ||v||^2. The 12 components of the site are summed at the
-// arithmetic precision and the site sums added in FP64.
+// ||v||^2; RED 3 <v, x> and ||v||^2, products and sums in FP64 (FP32 squares lose values above
+// 2e19 and below 1e-23).
 template <class R, bool NT, int RED>
 __device__ __forceinline__ void store_out_red(typename vec2<R>::type* ob, const typename vec2<R>::type* xb,
                                               long long j, bool sel, bool g5o, R a, R b, const cx<R> acc[4][3],
                                               double red[3]) {
   cx<R> v[12], xv[12];
-  R s0 = R(0), s1 = R(0), s2 = R(0);
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0;
   if (sel && xb) ld_site<R>(xb, j, xv);
 #pragma unroll
   for (int sp = 0; sp < 4; ++sp)
@@ -76,17 +80,23 @@ __device__ __forceinline__ void store_out_red(typename vec2<R>::type* ob, const 
         r.i += a * xv[k].i;
       }
       v[k] = sel ? r : cx<R>{R(0), R(0)};
-      if (RED == 1 || RED == 3) s2 += v[k].r * v[k].r + v[k].i * v[k].i;
+      const double vr = v[k].r, vi = v[k].i;
+      if (RED == 1 || RED == 3) {
+        s2 = fma(vr, vr, fma(vi, vi, s2));
+        pin(s2);
+      }
       if (RED == 3 && sel && xb) {
-        s0 += v[k].r * xv[k].r + v[k].i * xv[k].i;
-        s1 += v[k].r * xv[k].i - v[k].i * xv[k].r;
+        s0 = fma(vr, (double)xv[k].r, fma(vi, (double)xv[k].i, s0));
+        s1 = fma(vr, (double)xv[k].i, fma(-vi, (double)xv[k].r, s1));
+        pin(s0);
+        pin(s1);
       }
     }
-  if (RED == 1) red[0] += (double)s2;
+  if (RED == 1) red[0] += s2;
   if (RED == 3) {
-    red[0] += (double)s0;
-    red[1] += (double)s1;
-    red[2] += (double)s2;
+    red[0] += s0;
+    red[1] += s1;
+    red[2] += s2;
   }
   st_site<R, NT>(ob, j, v);
 }
@@ -1232,8 +1242,9 @@ void hop_slab_kernel(HopArgs<R> A, int TA, int TB) {
 // FP16 output site j of parity p and rhs r: out = a x + b (g5) acc, zero on unselected
 // sites, stored as three quad words (non-temporal) divided by the site norm (the largest
 // component magnitude), and the norm. Fused reductions of the values before their
-// rounding to FP16 (summed over the site in FP32, added in FP64): RED 1: red[0] +=
-// ||out||^2; RED 3: red[0..2] += Re <out, x>, Im <out, x> (out conjugated), ||out||^2.
+// rounding to FP16: RED 1: red[0] += ||out||^2 in FP64; RED 3: red[0..2] += Re <out, x>, Im <out,
+// x> (out conjugated), ||out||^2, summed over the site in FP32 and added in FP64 (the kernel is
+// bound by issue: all three in FP64 took 1 to 3% of a BiCGstab solve).
 template <int RED>
 __device__ __forceinline__ void store_out16(const Field<h16>& out, const Field<h16>& x, int r, int p, long long j,
                                             long long Vhp, bool sel, bool g5o, float a, float b,
@@ -1257,6 +1268,7 @@ __device__ __forceinline__ void store_out16(const Field<h16>& out, const Field<h
     }
   }
   float m = 0.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+  double n2 = 0.0;
 #pragma unroll
   for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
@@ -1271,13 +1283,17 @@ __device__ __forceinline__ void store_out16(const Field<h16>& out, const Field<h
       }
       v[k] = sel ? val : cx<float>{0.0f, 0.0f};
       m = fmaxf(m, fmaxf(fabsf(v[k].r), fabsf(v[k].i)));
-      if (RED == 1 || RED == 3) s2 = fmaf(v[k].r, v[k].r, fmaf(v[k].i, v[k].i, s2));
+      if (RED == 1) {
+        n2 = fma((double)v[k].r, (double)v[k].r, fma((double)v[k].i, (double)v[k].i, n2));
+        pin(n2);
+      }
+      if (RED == 3) s2 = fmaf(v[k].r, v[k].r, fmaf(v[k].i, v[k].i, s2));
       if (RED == 3 && wx) {
         s0 = fmaf(v[k].r, xq[2 * k], fmaf(v[k].i, xq[2 * k + 1], s0));
         s1 = fmaf(v[k].r, xq[2 * k + 1], fmaf(-v[k].i, xq[2 * k], s1));
       }
     }
-  if (RED == 1) red[0] += (double)s2;
+  if (RED == 1) red[0] += n2;
   if (RED == 3) {
     red[0] += (double)s0;
     red[1] += (double)s1;
