@@ -361,7 +361,9 @@ int schwarz_action(sap_ctx* ctx, const double* chi, const sap_solve_opts* opts, 
                    void* stream);
 
 /* Gauge force of the Wilson plaquette action S_G (Sec. 1): F += coef * dS_G/dw.
- * *S_G_out (host, may be NULL) receives S_G. */
+ * *S_G_out (host, may be NULL) receives S_G. Links that were loaded off SU(3) by more than
+ * FP64 rounding (1e-14) take a kernel that does not use U U^+ = 1; a captured call keeps the
+ * kernel of the links held at its capture. */
 int gauge_force(sap_ctx* ctx, double* F, double coef, double beta, double* S_G_out,
                 void* stream);
 

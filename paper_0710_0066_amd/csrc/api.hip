@@ -85,6 +85,7 @@ int sap_create(const sap_geom* g, sap_ctx** out) {
   c->Vh = c->g.Vh;
   c->Vhp = c->g.Vhp;
   c->have_gauge = false;
+  c->su3_dev = 0.0;
   c->U64 = nullptr;
   c->U32 = nullptr;
   c->U16 = nullptr;
@@ -142,6 +143,7 @@ int sap_set_gauge(sap_ctx* ctx, const double* U, void* stream) {
                   SAP_SU3_TOL);
     return sap_fail(ctx, SAP_E_ARG, msg);
   }
+  ctx->su3_dev = dev;
   ctx->have_gauge = true;
   return SAP_OK;
 }

@@ -13,6 +13,8 @@ void launch_pair_force(const Geo& g, double* F, double c, const double2* a, cons
 int gauge_parts(const Geo& g);
 void launch_gauge_force(const Geo& g, double* F, double c, const double2* U, double* Q, double* part, hipStream_t s,
                         const double* sx = nullptr);
+// the same force of links that are off SU(3) by more than rounding (no partials)
+void launch_staple_force(const Geo& g, double* F, double c, const double2* U, hipStream_t s, const double* sx = nullptr);
 // out[0] = the plaquette sum from those partials
 void launch_plaq_total(const Geo& g, const double* part, double* out, hipStream_t s);
 // out = in translated by n slices in x0 (out(x0) = in(x0 + n)); out != in

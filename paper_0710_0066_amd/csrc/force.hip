@@ -12,7 +12,8 @@
 // with the x0 wrap phase -1 on the link at x0 = L0-1.
 // gauge force (Wilson plaquette action, Sec. 1): F^a = (beta/6) Im tr(lambda^a U A),
 // A = sum of the six staples of U_mu(x), from the plaquettes: U A = sum over nu of the
-// plaquette at x and the one at x - nu carried along U_nu(x - nu) (k_plaq, k_gauge_force).
+// plaquette at x and the one at x - nu carried along U_nu(x - nu) (k_plaq, k_gauge_force);
+// for links that are off SU(3) by more than rounding from the staples (k_staple_force).
 // T_U (Sec. 2, eq. 3): U <- exp(i dt P) U, exponential by scaling and squaring of a
 // degree-16 Taylor polynomial, its powers reduced by the characteristic equation, then Gram-Schmidt reunitarisation with the third row the
 // conjugate cross product of the first two (exactly unitary, det 1 up to rounding).
@@ -346,6 +347,48 @@ void k_gauge_force(Geo g, SiteDiv d, Walk k, double* F, double c, const double2*
   });
 }
 
+// Gauge force from the staples,
+//   A = sum_{nu != mu} U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+ + U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu),
+// exact for any links: the plaquette form takes U U^+ = 1 for granted, which sap_set_gauge
+// only asks for to 1e-10. One work-item per link, a wavefront per direction for 64 sites of one
+// parity (blockIdx.y). The memory fences keep the scheduler from loading the links of several
+// staples at once, which would cost occupancy (236 VGPRs, two wavefronts per SIMD). 596 us on
+// 24^3x48, with the action's own pass 850, where the plaquette form takes 418.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void k_staple_force(Geo g, double* F, double c, const double2* U, const double* sx) {
+  const int mu = threadIdx.x >> 6, p = blockIdx.y;
+  const long long j = (long long)blockIdx.x * 64 + (threadIdx.x & 63), Vhp = g.Vhp;
+  if (j >= g.Vh) return;
+  const Site s = decode(g, j, p);
+  const long long jpm = nbr(g, s, j, mu, +1);                 // x+mu, parity 1-p
+  const Site spm = decode(g, jpm, 1 - p);
+  M3 A;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) A.m[e] = {0.0, 0.0};
+#pragma unroll 1
+  for (int nu = 0; nu < 4; ++nu) {
+    if (nu == mu) continue;
+    const long long jpn = nbr(g, s, j, nu, +1), jmn = nbr(g, s, j, nu, -1);   // parity 1-p
+    const long long jpmmn = nbr(g, spm, jpm, nu, -1);                         // x+mu-nu, parity p
+    const M3 ab = mmul_nd(load_U(U, Vhp, 1 - p, jpm, nu), load_U(U, Vhp, 1 - p, jpn, mu));
+    asm volatile("" ::: "memory");
+    const M3 up = mmul_nd(ab, load_U(U, Vhp, p, j, nu));
+#pragma unroll
+    for (int e = 0; e < 9; ++e) A.m[e] = A.m[e] + up.m[e];
+    asm volatile("" ::: "memory");
+    // the lower staple is (U_mu(x-nu) U_nu(x+mu-nu))^+ U_nu(x-nu)
+    const M3 t = mmul(load_U(U, Vhp, 1 - p, jmn, mu), load_U(U, Vhp, p, jpmmn, nu));
+    asm volatile("" ::: "memory");
+    const M3 lo = mmul_dn(t, load_U(U, Vhp, 1 - p, jmn, nu));
+#pragma unroll
+    for (int e = 0; e < 9; ++e) A.m[e] = A.m[e] + lo.m[e];
+    asm volatile("" ::: "memory");
+  }
+  double v[8];
+  im_tr_lambda(mmul(load_U(U, Vhp, p, j, mu), A), v);
+  add_force(F, Vhp, p, j, mu, c * (sx ? sx[s.x0 * 4 + mu] : 1.0), v);
+}
+
 // one workgroup: thread t takes part[t], part[t + 1024], ..., then a fixed tree (the result
 // does not depend on timing)
 __global__ __launch_bounds__(1024) void k_max_parts(int n, const double* part, double* out) {
@@ -635,6 +678,9 @@ void launch_pair_force(const Geo& g, double* F, double coef_times_minus_kappa, c
 }
 constexpr int PLAQ_STEPS = 4, FORCE_STEPS = 1;
 int gauge_parts(const Geo& g) { return walk_of(g, PLAQ_STEPS).blocks; }
+void launch_staple_force(const Geo& g, double* F, double c, const double2* U, hipStream_t s, const double* sx) {
+  hipLaunchKernelGGL(k_staple_force, dim3((unsigned)((g.Vh + 63) / 64), 2), dim3(256), 0, s, g, F, c, U, sx);
+}
 void launch_gauge_force(const Geo& g, double* F, double c, const double2* U, double* Q, double* part, hipStream_t s,
                         const double* sx) {
   const SiteDiv d = site_div(g);

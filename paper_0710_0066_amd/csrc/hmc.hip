@@ -325,6 +325,22 @@ int kinetic_host(sap_ctx* c, const double* P, double* K, hipStream_t s) {
   return SAP_OK;
 }
 
+// p += c dS_G/dw with the forms of force.hip; S_G's plaquette sum into scal when asked for. The
+// choice goes by the links that were loaded: moved links are unitary, but links at rest (a step
+// scale of zero) stay as they were.
+int add_gauge_force(sap_ctx* c, double* F, double coef, bool plaq, hipStream_t s, const double* sx = nullptr) {
+  ForceWS* w = fws(c);
+  if (c->su3_dev <= SAP_SU3_ROUNDED) {
+    launch_gauge_force(c->g, F, coef, c->U64, (double*)w->Utmp, w->part, s, sx);
+    if (plaq) launch_plaq_total(c->g, w->part, w->scal, s);   // the force's own plaquettes
+  } else {
+    launch_staple_force(c->g, F, coef, c->U64, s, sx);
+    if (plaq) launch_plaq_sum(c->g, c->U64, w->part, w->scal, s);
+  }
+  SAP_HIP_CHECK(c, hipGetLastError());
+  return SAP_OK;
+}
+
 void links_changed(sap_ctx* c, hipStream_t s) { launch_gauge_to_f32(c->g, c->U32, c->U16, c->U64, s); }
 LinkCopies copies_of(sap_ctx* c) { return LinkCopies{c->U32, c->U16}; }
 
@@ -366,10 +382,7 @@ int kick_pf(Traj& T, double dt) {
   return schwarz_terms(T.c, fws(T.c)->mom, -dt, T.chi, &T.P->force_solve, nullptr, T.s, T.sx);
 }
 int kick_g(Traj& T, double dt) {
-  launch_gauge_force(T.c->g, fws(T.c)->mom, -dt * T.P->beta / 6.0, T.c->U64, (double*)fws(T.c)->Utmp, fws(T.c)->part,
-                     T.s, T.sx);
-  SAP_HIP_CHECK(T.c, hipGetLastError());
-  return SAP_OK;
+  return add_gauge_force(T.c, fws(T.c)->mom, -dt * T.P->beta / 6.0, false, T.s, T.sx);
 }
 int kicks_due(Traj& T) {
   return T.kicks.apply([&](int j, double dt) { return j ? kick_pf(T, dt) : kick_g(T, dt); });
@@ -454,10 +467,7 @@ int kick4(Traj4& T, int j, double dt) {
   double* mom = fws(c)->mom;
   const sap_solve_opts* o = j ? force_opts4(T.P, j) : nullptr;
   switch (j) {
-    case 0:
-      launch_gauge_force(c->g, mom, -dt * T.P->beta / 6.0, c->U64, (double*)fws(c)->Utmp, fws(c)->part, T.s, T.sx);
-      SAP_HIP_CHECK(c, hipGetLastError());
-      return SAP_OK;
+    case 0: return add_gauge_force(c, mom, -dt * T.P->beta / 6.0, false, T.s, T.sx);
     case 1: return eo_pf_terms(c, mom, -dt, T.phi1, 1, T.P->rho, o, nullptr, T.s, T.sx);
     case 2: return eo_pf_terms(c, mom, -dt, T.phi2, 2, T.P->rho, o, nullptr, T.s, T.sx);
     case 3: return schwarz_terms(c, mom, -dt, T.chi3, o, nullptr, T.s, T.sx, c->geom.l0);
@@ -631,10 +641,7 @@ int gauge_force(sap_ctx* c, double* F, double coef, double beta, double* S_G_out
   if (!std::isfinite(beta)) return sap_fail(c, SAP_E_ARG, "beta must be finite");
   if (!c->have_gauge) return sap_fail(c, SAP_E_STATE, "no gauge field set");
   hipStream_t s = (hipStream_t)stream;
-  ForceWS* w = fws(c);
-  launch_gauge_force(c->g, F, coef * beta / 6.0, c->U64, (double*)w->Utmp, w->part, s);
-  if (S_G_out) launch_plaq_total(c->g, w->part, w->scal, s);   // the force's own plaquettes
-  SAP_HIP_CHECK(c, hipGetLastError());
+  if (int rc = add_gauge_force(c, F, coef * beta / 6.0, S_G_out != nullptr, s)) return rc;
   if (S_G_out) return action_from_scal(c, beta, S_G_out, s);
   return SAP_OK;
 }

@@ -175,6 +175,7 @@ struct sap_ctx {
   long long V, Vh, Vhp;
   int device;
   bool have_gauge;
+  double su3_dev;   // largest deviation from SU(3) of the links that were loaded
   double2* U64;   // tiled gauge layout, 72*Vhp complex (whole links: forces, link updates; the FP64
                   // hop kernels read the first two rows of each)
   float2* U32;    // two-row FP32 copy
@@ -190,6 +191,9 @@ struct sap_ctx {
 
 // largest deviation from SU(3) (|U U^+ - 1| entries, |det U - 1|) sap_set_gauge accepts
 constexpr double SAP_SU3_TOL = 1e-10;
+// links nearer than this to SU(3) are rounded FP64 matrices: their largest deviation is 1.3e-15
+// after a reunitarisation, 5e-15 for exponentials from eigenvectors (16^3x32)
+constexpr double SAP_SU3_ROUNDED = 1e-14;
 
 // precision code (sap_prec) of a storage type
 template <class S> constexpr int prec_of() {
