@@ -73,7 +73,8 @@ template <class R> struct HopArgs {
   double* npart = nullptr;
   int nlb = 0, nslot = 0, red = 0;
   // optional: nonzero where a system (rhs, x0 block; the blocks of slb, or the whole lattice) is
-  // still iterated; the output of the others may be left as it is
+  // still iterated; the output of the others may be left as it is (it is by the split, marching,
+  // slab and FP16 kernels; the other mappings compute it)
   const int* active = nullptr;
   int keep = 0;            // split kernel: leave unselected sites as they are (else zero)
   int rev = 0;             // split kernel, linear order: walk the lattice backwards
