@@ -229,7 +229,7 @@ static void full_op(sap_ctx* ctx, void* out, const void* in, int nrhs, int lb, i
   A.b = Ar(-ctx->geom.kappa);
   A.g5_in = 0;
   A.g5_out = 0;
-  A.map = hop_map_for(ctx, true, prec_of<R>(), nrhs);
+  A.map = hop_map_for(ctx, true, prec_of<R>(), nrhs, hop_use(A.g, lb, colour, block));
   launch_hop<R>(A, s);
 }
 
@@ -253,7 +253,7 @@ static void eo_hop(sap_ctx* ctx, void* out, const void* in, int nrhs, int parity
   A.b = Ar(1);
   A.g5_in = 0;
   A.g5_out = 0;
-  A.map = hop_map_for(ctx, false, prec_of<R>(), nrhs);
+  A.map = hop_map_for(ctx, false, prec_of<R>(), nrhs, HOP_ALL);
   launch_hop<R>(A, s);
 }
 

@@ -1919,17 +1919,29 @@ void launch_slabd16(const HopArgs<h16>& A, hipStream_t st) { launch_slabd<h16>(A
 // tile they choose keeps at most as many halo sites as tile sites and fills its wavefronts.
 // Measured (us, split / slab): FP32 24^3x48 1 rhs 30 / 39, 2 rhs 45 / 49, 3 rhs 62 / 60, 12 rhs
 // 309 / 256; FP64 2 rhs 123 / 145, 3 rhs 174 / 164, 12 rhs 656 / 564; 24x10x6x14 with 12 rhs,
-// where the slab tile is small, 10 / 15 and 20 / 27. FP16 (issue-bound: the split kernel only
-// pays while it adds wavefronts): half hop SITE up to 7e5, marching above (16^3x32 3 rhs 13 /
-// 16 us for site / march1, 8 rhs 31 / 27; 24^3x48 2 rhs 39 / 36, 12 rhs 250 / 196; the LDS slab,
-// 186 us there, reads links rounded in all three rows and so gives other roundings); full
-// operator SITE up to 4e5 (16^3x32 1 rhs 11.1 / 12.1 us, 5 rhs 41 / 36).
-// Full operator in FP32 and FP64: marching (launch_march1).
-int hop_default_map(const Geo& g, bool full, int prec, int nrhs) {
+// where the slab tile is small, 10 / 15 and 20 / 27. Full operator in FP32 and FP64: marching
+// (launch_march1).
+// FP16: SITE, and marching where that gains: its XCDs' eighths of a slice have to fill the
+// workgroups (95%; 48x24^2x4, 56%: M with 8 rhs 47 / 55 us for site / march1), slices of fewer than
+// 2000 sites per parity are too short, and there have to be enough workgroups. Half hop (us): 16^3x32
+// 8 rhs 28.4 / 28.9, 12 rhs 40.2 / 39.0; 12x24^3 5 rhs 25.6 / 25.1, 32x24^3 1 rhs (4.4e5) 2.7% slower;
+// 24^3x48 12 rhs 196 / 192 (the LDS slab, 186, reads links rounded in all three rows and so
+// gives other roundings). Full operator: 16^3x32 5 rhs 35.3 / 35.2, 8 rhs 53.7 / 51.3; 16x24^3 2
+// rhs (4.4e5) 5% slower. On some of the x0 blocks the site order leaves XCDs without work (16^3x32,
+// black blocks, 3 rhs 21.4 / 17.6; one block of 48x24^2x4, 8 rhs 30.8 / 15.9) unless each has as
+// many of them (64x16^3, 4 rhs: march1 6% slower). In a solve, where march1 leaves converged
+// systems out by the workgroup, 16^3x32 with 6 rhs (7.9e5) gains 2% and 24^3x48 with one (6.6e5)
+// loses 2%.
+int hop_default_map(const Geo& g, bool full, int prec, int nrhs, int use) {
   const double W = 2.0 * g.Vh * nrhs;
   if (prec == SAP_F16) {
-    if (W <= (full ? 4e5 : 7e5)) return HOP_MAP_SITE;
-    return HOP_MAP_MARCH1;
+    const int per = full ? 64 : 128, share = (g.V3h + 7) / 8, ck = (share + per - 1) / per;
+    const bool fits = g.V3h >= 2000 && 20 * share >= 19 * ck * per;
+    double line = full ? 6e5 : g.V3h >= 6000 ? 7e5 : 1.3e6;
+    if (use == HOP_EVENLY) line = 2e6;
+    if (use == HOP_UNEVENLY || use == HOP_BLOCK) line = 4e5;
+    if (use == HOP_SOLVE) line = 7e5;
+    return W > line && (fits || use >= HOP_BLOCK) ? HOP_MAP_MARCH1 : HOP_MAP_SITE;
   }
   if (full || W <= 1.9e6) return HOP_MAP_MARCH1;
   int TA, TB, S, H;

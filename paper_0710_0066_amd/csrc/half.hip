@@ -162,16 +162,26 @@ template <int NR> static void launch_march16(const HopArgs<h16>& A, hipStream_t 
 #undef SAP_M16
 }
 
-// few wavefronts: the eight hops of a site on the eight wavefronts of a workgroup. Measured
-// (us, split / site): half hop on 16^3x32, 1 rhs 6.6 / 7.2, 3 rhs 13.8 / 13.1, on
-// 16x8^3, 1 rhs 3.9 / 6.7; full operator on 16^3x32, 1 rhs 11.1 / 11.2, 3 rhs 26.5 / 23.7
+// Few wavefronts: the eight hops of a site on the eight wavefronts of a workgroup. Up to 1e5 sites
+// times rhs the site kernel's 256-site workgroups leave half of the 256 CUs idle, and a little
+// above 1.3e5 their second round is nearly empty. Measured (us, split / site): half hop on 16x8^3,
+// 1 rhs 3.9 / 6.4, 24x16^3 1 rhs 6.3 / 6.8, 16^3x32 1 rhs (1.31e5) 7.5 / 7.1, 16x12^3 5 rhs (1.38e5)
+// 8.3 / 8.9, 8 rhs 10.8 / 9.7; full operator on 16^3x32 11.8 / 10.9, 16x12^3 5 rhs 12.6 / 13.2. Where
+// workgroups have nothing to do the split kernel is left sooner, and it deals those of a few
+// blocks over all XCDs: 24x10x6x14 5 rhs (1.0e5), black blocks 8.7 / 10.5, one block 6.5 / 10.3;
+// half hops of a solve on it 0.03 to 0.13 of the solve.
 static bool site_is_split(const HopArgs<h16>& A) {
-  return 2.0 * A.g.Vh * A.nrhs <= (A.parity_out < 0 ? 1.5e5 : 3e5);
+  const double W = 2.0 * A.g.Vh * A.nrhs;
+  if (W <= 1e5) return true;
+  if (A.parity_out >= 0) return A.active ? W <= 3e5 : W > 1.32e5 && W <= 1.66e5;
+  return W <= 1.5e5 && (W > 1.32e5 || hop_use(A.g, A.slb, A.colour, A.block) >= HOP_UNEVENLY);
 }
 
+// with the reductions it adds to its output, the split kernel wins up to twice the sites: the site
+// kernel has none, and a norm pass takes 4 us there
 template <> int hop_red_slots<h16>(const HopArgs<h16>& A, int nlb) {
   if (A.map == HOP_MAP_SLABD) return slabd_norm_slots(A.g, nlb);
-  if (A.map == HOP_MAP_SITE && site_is_split(A)) return split_chunks(A.g, nlb, false);
+  if (A.map == HOP_MAP_SITE && 2.0 * A.g.Vh * A.nrhs <= 3e5) return split_chunks(A.g, nlb, false);
   return 0;
 }
 
@@ -193,7 +203,7 @@ template <> void launch_hop<h16>(const HopArgs<h16>& A, hipStream_t st) {
     default: break;
   }
   const bool full = A.parity_out < 0;
-  if (site_is_split(A)) {
+  if (A.npart || site_is_split(A)) {
     launch_split<h16>(A, false, st);
     return;
   }

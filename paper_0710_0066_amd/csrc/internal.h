@@ -124,7 +124,15 @@ constexpr int HOP_WALK_T = 8;   // slices per walk
 
 template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t s);
 // mapping of an untuned context for the full operator or the half hop (prec: sap_prec)
-int hop_default_map(const Geo& g, bool full, int prec, int nrhs);
+int hop_default_map(const Geo& g, bool full, int prec, int nrhs, int use);
+// what a launch computes: all sites, the blocks of a colour (as many in every eighth of x0, or
+// not), one block; or a half hop of a solve, which leaves out converged systems
+enum { HOP_ALL, HOP_EVENLY, HOP_UNEVENLY, HOP_BLOCK, HOP_SOLVE };
+inline int hop_use(const Geo& g, int slb, int colour, int block) {
+  if (slb && block >= 0) return HOP_BLOCK;
+  if (!slb || colour == 0) return HOP_ALL;
+  return g.L0 % (16 * slb) == 0 ? HOP_EVENLY : HOP_UNEVENLY;
+}
 // does the launch A run the split kernel?
 template <class R> bool hop_is_split(const HopArgs<R>& A);
 // partials per system of nlb slices that the half hop A (its mapping, precision, lattice and
@@ -203,10 +211,10 @@ template <class S> constexpr int prec_of() {
 
 // mapping used for a hop launch: the tuned (or set) one, else the rule on the lattice, the
 // precision and the number of rhs
-inline int hop_map_for(const sap_ctx* c, bool full, int prec, int nrhs) {
+inline int hop_map_for(const sap_ctx* c, bool full, int prec, int nrhs, int use) {
   const int m = c->hop_map[full ? 1 : 0][prec][nrhs > 64 ? 64 : nrhs];
   if (m >= 0) return m;
-  return sap::hop_default_map(c->g, full, prec, nrhs);
+  return sap::hop_default_map(c->g, full, prec, nrhs, use);
 }
 
 // error helpers (api.hip)

@@ -157,7 +157,7 @@ HopArgs<R> hop_args(sap_ctx* c, Field<R> out, Field<R> in, Field<R> x, int parit
   A.b = b;
   A.g5_in = g5i;
   A.g5_out = g5o;
-  A.map = hop_map_for(c, parity_out < 0, prec_of<R>(), nrhs);
+  A.map = hop_map_for(c, parity_out < 0, prec_of<R>(), nrhs, HOP_SOLVE);
   return A;
 }
 template <class R>
