@@ -15,7 +15,7 @@ struct SysGrid {
   int nchunk;       // ceil(Vb / per)
   int colour;
   int nrhs;
-  bool xcd;         // fields of a few MB: workgroups in the order of the split hop
+  bool xcd;         // workgroups in the order of the split hop (tile_of)
   long long Vh;
   long long Vhp;     // storage sites per parity (locates the site norms of FP16 fields)
 };
@@ -46,10 +46,15 @@ struct Parts {
 
 // Sites per workgroup: 64 while that gives up to about a thousand workgroups, then more, up to
 // 1024, and above that as many as keep a system at a thousand chunks (its partials are summed
-// again by every workgroup that needs the scalar). On 16^3x32 with one rhs a CG update takes 3 to 4 us with 64 sites per workgroup,
-// 6.4 to 9 us with the 1024 that suit 12 rhs on 24^3x48 (64 workgroups on 256 CUs). FP16
-// kernels take a site per work-item and keep at least 256.
-inline SysGrid make_sysgrid(long long Vh, int V3h, int lb, int L0, int colour, int nrhs, bool f16 = false) {
+// again by every workgroup that needs the scalar). On 16^3x32 with one rhs a CG update takes 3 to
+// 4 us with 64 sites per workgroup, 6.4 to 9 us with the 1024 that suit 12 rhs on 24^3x48 (64
+// workgroups on 256 CUs). FP16 kernels take a site per work-item and keep at least 256.
+// ranges: the hops of the solve give each XCD a range of the whole lattice (hop_in_ranges), so that
+// the updates may follow them. CG solves with it / without (ms): 16^3x32 1 rhs FP32 3.81 / 3.89,
+// FP64 5.69 / 5.75, FP16 blocks 2.93 / 3.04; 16x12^3 2 rhs FP32 2.31 / 2.38. Below 25000 sites times
+// rhs the index divisions cost more, above 200000 nothing is gained (16^3x32 5 rhs, FP64 1% lost).
+inline SysGrid make_sysgrid(long long Vh, int V3h, int lb, int L0, int colour, int nrhs, bool f16 = false,
+                            bool ranges = false) {
   SysGrid G;
   G.nblk = lb ? L0 / lb : 1;
   G.Vb = lb ? (long long)lb * V3h : Vh;
@@ -58,7 +63,7 @@ inline SysGrid make_sysgrid(long long Vh, int V3h, int lb, int L0, int colour, i
   G.nchunk = (int)((G.Vb + G.per - 1) / G.per);
   G.colour = lb ? colour : 0;
   G.nrhs = nrhs;
-  G.xcd = Vh * nrhs > 25000 && Vh * nrhs <= 200000;
+  G.xcd = ranges && Vh * nrhs > 25000 && Vh * nrhs <= 200000;
   G.Vh = Vh;
   G.Vhp = (Vh + TILE - 1) / TILE * TILE;
   return G;

@@ -67,11 +67,12 @@ struct Tile {
   long long part;     // index of this workgroup's partial
 };
 
-// Fields of a few MB (G.xcd): a one-dimensional grid, rhs fastest, then parity, chunk and
-// block, each XCD a contiguous range walked forwards or (rev) backwards, the order of the
-// split hop, whose outputs are then read by the XCD that wrote them. Else blockIdx = (chunk,
-// block, rhs * npar + parity): on larger fields the first order streams no faster (24^3x48
-// with 12 rhs: 10% slower), on smaller ones the divisions cost more than they give.
+// G.xcd: a one-dimensional grid, rhs fastest, then parity, chunk and block, each XCD a
+// contiguous range walked forwards or (rev) backwards, the order of the split hop, whose
+// outputs are then read by the XCD that wrote them. Else blockIdx = (chunk, block, rhs * npar +
+// parity): on larger fields the first order streams no faster (24^3x48 with 12 rhs: 10% slower),
+// on smaller ones the divisions cost more than they give, on some of the blocks it leaves XCDs
+// without work (black blocks of 24x16^3, 2 rhs, FP64 CG: 3.95 ms, 3.57 without).
 __device__ __forceinline__ Tile tile_of(const SysGrid& G, int npar = 1, bool rev = false) {
   Tile t;
   if (G.xcd) {

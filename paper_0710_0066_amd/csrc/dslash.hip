@@ -1985,11 +1985,13 @@ template <class R> static void launch_stream(const HopArgs<R>& A, hipStream_t st
 // while the input stays within 200 MB (the MALL holds 256 MB); the FP32 half hop (24^3x48,
 // 12 rhs: 329 / 309) always, the FP64 one (16^3x32, 12 rhs: 117 / 99; 24^3x48, 12 rhs:
 // 625 / 655) up to twice that input. Slices of fewer than 16 chunks of 64 sites leave some
-// of the 8 XCDs idle or short in this order and run in the linear one, and so do fields that
-// are read again from the XCDs' 32 MB of L2 when consecutive kernels give an XCD the same
-// sites (FP32 CG on 16^3x32: half hops 8.4 and 9.2 us marching, 7.7 and 8.2 linear and
-// alternating in direction). Launches on some of the blocks only march all the same: the
-// linear order gives each XCD a range of slices, which may hold no selected block.
+// of the 8 XCDs idle or short in this order and run in the linear one, and so do half hops of
+// inputs up to 27 MB, part of which is still in the XCDs' L2 (32 MB in all) when consecutive
+// kernels give an XCD the same sites. Solves on 16^3 slices, marching / linear (ms): FP64 CG at 19
+// MB 4.89 / 4.65, at 25 MB 6.00 / 5.69; FP32 CG at 19 MB 4.97 / 4.63, at 25 MB 5.77 / 5.31, at 38 MB
+// 7.53 / 7.06; FP64 CG at 38 MB 7.21 / 7.06, at 50 MB 9.02 / 9.10: the line lies low by up to a half.
+// Launches on some of the blocks march all the same: the linear order gives each XCD a
+// range of slices, which may hold no selected block.
 template <class R> static int march1_order(const HopArgs<R>& A) {
   const bool full = A.parity_out < 0, f32 = std::is_same<R, float>::value;
   const double in = 2.0 * A.g.Vh * A.nrhs * 24 * sizeof(R);      // bytes of the whole input field
@@ -2006,6 +2008,12 @@ template <class R> bool hop_is_split(const HopArgs<R>& A) {
   return A.map == HOP_MAP_SITE || (A.map == HOP_MAP_MARCH1 && march1_order(A) >= 0);
 }
 template bool hop_is_split<double>(const HopArgs<double>&);
+
+template <class R> bool hop_in_ranges(const HopArgs<R>& A) {
+  return !split_partial(A) && (A.map == HOP_MAP_SITE || (A.map == HOP_MAP_MARCH1 && march1_order(A) == 0));
+}
+template bool hop_in_ranges<double>(const HopArgs<double>&);
+template bool hop_in_ranges<float>(const HopArgs<float>&);
 
 template <class R> int hop_red_slots(const HopArgs<R>& A, int nlb) {
   if (A.map == HOP_MAP_SLABD && std::is_same<R, float>::value) return slabd_norm_slots(A.g, nlb);

@@ -184,6 +184,8 @@ template <> int hop_red_slots<h16>(const HopArgs<h16>& A, int nlb) {
   if (A.map == HOP_MAP_SITE && 2.0 * A.g.Vh * A.nrhs <= 3e5) return split_chunks(A.g, nlb, false);
   return 0;
 }
+// (the site kernel gives the XCDs ranges too)
+template <> bool hop_in_ranges<h16>(const HopArgs<h16>& A) { return A.map == HOP_MAP_SITE && !split_partial(A); }
 
 template <> void launch_hop<h16>(const HopArgs<h16>& A, hipStream_t st) {
   switch (A.map) {

@@ -135,6 +135,10 @@ inline int hop_use(const Geo& g, int slb, int colour, int block) {
 }
 // does the launch A run the split kernel?
 template <class R> bool hop_is_split(const HopArgs<R>& A);
+// do the workgroups of the half hop A give each XCD a range of the whole lattice (linear order,
+// every block)?
+template <class R> bool hop_in_ranges(const HopArgs<R>& A);
+template <> bool hop_in_ranges<h16>(const HopArgs<h16>& A);   // half.hip
 // partials per system of nlb slices that the half hop A (its mapping, precision, lattice and
 // rhs) can write of its output (HopArgs::npart); 0: its mapping has none
 template <class R> int hop_red_slots(const HopArgs<R>& A, int nlb);

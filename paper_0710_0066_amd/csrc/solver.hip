@@ -186,7 +186,8 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
   typedef typename arith<R>::type Ar;
   SolverWS* w = ws_of(c);
   const long long Vh = c->Vh, Vhp = c->Vhp;
-  const SysGrid G = make_sysgrid(Vh, c->g.V3h, lb, c->geom.L[0], colour, nrhs, std::is_same<R, h16>::value);
+  const bool ranges = hop_in_ranges(hop_args<R>(c, {}, {}, {}, 0, nrhs, lb, colour, Ar(1), Ar(1), 0, 0));
+  const SysGrid G = make_sysgrid(Vh, c->g.V3h, lb, c->geom.L[0], colour, nrhs, std::is_same<R, h16>::value, ranges);
   const int nsys = G.nblk * nrhs;
   const double kap = c->geom.kappa;
   const Ar k2R = (Ar)(-kap * kap);
@@ -615,8 +616,7 @@ static int sap_bicgstab(sap_ctx* c, double* x, const double* b, int nrhs, const 
   SapWS* a = sap_ws(c);
   if (!a) return sap_fail(c, SAP_E_NOMEM, "cannot allocate the Schwarz-preconditioned BiCGstab workspace");
   const long long Vhp = c->Vhp;
-  SysGrid G = make_sysgrid(c->Vh, c->g.V3h, 0, c->geom.L[0], 0, 2 * nrhs);
-  G.xcd = false;   // full lattice, one block
+  const SysGrid G = make_sysgrid(c->Vh, c->g.V3h, 0, c->geom.L[0], 0, 2 * nrhs);   // full lattice, one block
   const int nh = 2 * nrhs;                                                 // half-field systems
   auto H = [&](double2* f) { return Field<double>{f, 12 * Vhp, 0}; };
   const Field<double> NONE = {nullptr, 0, 0};
