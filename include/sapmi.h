@@ -105,7 +105,8 @@ typedef enum {
 } sap_method;
 
 typedef struct {
-  double tol;        /* stop when ||b - A x|| / ||b|| <= tol, recomputed in FP64 */
+  double tol;        /* stop when ||b - A x|| / ||b|| <= tol, recomputed in FP64 (see
+                      * true_rel_res) */
   int max_iter;      /* cap on inner iterations summed over outer cycles (SAP_SAP_BICGSTAB:
                       * on BiCGstab iterations) */
   sap_prec inner_prec; /* storage precision of the inner Krylov solve (FP32 arithmetic for
@@ -125,7 +126,10 @@ typedef struct {
 typedef struct {
   int iters;            /* inner iterations in which this system was still active */
   int outer;            /* defect-correction cycles */
-  double true_rel_res;  /* ||b - A x|| / ||b|| recomputed in FP64 at the end */
+  double true_rel_res;  /* ||b - A x|| / ||b|| recomputed in FP64 at the end: over the even
+                         * sites after a correction (x_o = b_o + kappa D_oe x_e, formed in
+                         * FP64, leaves its rounding on the odd ones: 1e-16 ||x||), over all
+                         * sites before the first and for SAP_SAP_BICGSTAB */
 } sap_solve_info;
 
 typedef struct {

@@ -4,10 +4,11 @@
 // the neighbour's norm scales the term in the FP32 reconstruction, and on store the
 // output site's norm is recomputed as its largest component magnitude.
 //
-// Two work-item mappings: one (output site, rhs) per work-item with workgroups
-// rhs-fastest and renumbered per XCD (SITE), and the x0-marching order of dslash.hip with
-// NR = 1, 2 or 4 rhs per work-item sharing every link load (MARCH1/2/4; the walking and
-// band maps, which exist for FP32/FP64 only, fall back to the marching order).
+// Work-item mappings: SITE is one (output site, rhs) per work-item with workgroups rhs-fastest and
+// renumbered per XCD, or on small launches and with fused reductions the split kernel
+// (split.hip); MARCH1/2/4 is the x0-marching order of dslash.hip with NR = 1, 2 or 4 rhs per
+// work-item sharing every link load (the walking, band and slab maps that exist for FP32/FP64
+// only fall back to it); SLABD, half hop, the LDS-staged slabs of dslash.hip.
 #include "internal.h"
 #include "site_io.h"
 #include "split.h"

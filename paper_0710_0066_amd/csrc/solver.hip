@@ -283,8 +283,9 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
     const int nlb = lb ? lb : c->geom.L[0];
     int nslot = hop_red_slots(hop_args<R>(c, Q, T, P, 0, nrhs, lb, colour, aI, k2R, 0, 0), nlb);
     if ((size_t)3 * nslot * nsys > w->part_cap) nslot = 0;       // no room in the partial buffers
-    // converged systems are skipped (version v of active), also a single one: a graph runs up to
-    // seven iterations past its end
+    // the updates skip converged systems (version v of active), also a single one, and so do the
+    // hops of the mappings that HopArgs::active names: a graph runs up to seven iterations past
+    // its end. Separate norm and dot passes run for every selected system.
     auto live = [&](int v) { return w->active + v * nsys; };
     // consecutive kernels walk the lattice in opposite directions, so that each begins with
     // what the one before left in the caches

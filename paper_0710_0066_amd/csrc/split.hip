@@ -9,8 +9,9 @@
 // over the wavefront and all loads of a site are in flight at once, and writes its half
 // spinor (two colour vectors) to LDS; after one barrier wavefronts 0..5 sum the eight hops
 // of a pair of components each (spin-colour components 2k, 2k + 1), form a x + b D in and
-// store the pair. 50 / 92 VGPRs (FP32 / FP64) instead of 128 and more leave 8 / 5 wavefronts
-// per SIMD.
+// store the pair. 50 / 92 VGPRs (FP32 / FP64) instead of 128 and more leave 8 / 4 wavefronts
+// per SIMD (workgroups of two per SIMD become resident whole). FP16 fields run the linear order
+// only: where their launches are large enough to march, one work-item per site is faster (half.hip).
 // What bounds it: memory latency up to about 10^4 sites, then L2 / MALL bandwidth (the links
 // and the eight-fold gather of the input). Measured per launch against one work-item per
 // site (us): half hop on 16x8^3, FP64 4.5 / 12.7, FP32 3.9 / 7.5; on 16^3x32, FP64 15.2 / 20.4, FP32
@@ -234,8 +235,7 @@ __global__ __launch_bounds__(512) void hop_split_kernel(HopArgs<R> A, SplitGeo q
       typedef unsigned u2w __attribute__((ext_vector_type(2)));
       const u2w o = {u_of(__floats2half2_rn(v[0].r * inv, v[0].i * inv)),
                      u_of(__floats2half2_rn(v[1].r * inv, v[1].i * inv))};
-      if (MARCH) __builtin_nontemporal_store(o, (u2w*)ob);
-      else *(u2w*)ob = o;
+      *(u2w*)ob = o;
       if (wave == 0) norm_ptr16(A.out, rhs, p, Vhp)[j] = m;
     }
   } else if constexpr (is_f32<R>) {
@@ -319,8 +319,12 @@ template <class R> void launch_split(const HopArgs<R>& A, bool march, hipStream_
   const dim3 grid((unsigned)n), blk(512);
 #define SAP_SPLIT(FULL, RED)                                                                             \
   do {                                                                                                   \
-    if (march) hipLaunchKernelGGL((hop_split_kernel<R, FULL, RED, true>), grid, blk, 0, st, A, q);       \
-    else hipLaunchKernelGGL((hop_split_kernel<R, FULL, RED, false>), grid, blk, 0, st, A, q);            \
+    if constexpr (!is_h16<R>)                                                                            \
+      if (march) {                                                                                       \
+        hipLaunchKernelGGL((hop_split_kernel<R, FULL, RED, true>), grid, blk, 0, st, A, q);              \
+        break;                                                                                           \
+      }                                                                                                  \
+    hipLaunchKernelGGL((hop_split_kernel<R, FULL, RED, false>), grid, blk, 0, st, A, q);                 \
   } while (0)
   if (full) SAP_SPLIT(true, 0);
   else if (A.npart && A.red == 1) SAP_SPLIT(false, 1);
