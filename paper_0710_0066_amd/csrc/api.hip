@@ -93,6 +93,7 @@ int sap_create(const sap_geom* g, sap_ctx** out) {
   c->forces = nullptr;
   c->sapws = nullptr;
   std::memset(c->hop_map, -1, sizeof(c->hop_map));
+  std::memset(c->hop_tuned, 0, sizeof(c->hop_tuned));
   if (hipGetDevice(&c->device) != hipSuccess) {
     delete c;
     return sap_fail(nullptr, SAP_E_HIP, "hipGetDevice failed (no HIP device?)");

@@ -1939,7 +1939,7 @@ int hop_default_map(const Geo& g, bool full, int prec, int nrhs, int use) {
     const bool fits = g.V3h >= 2000 && 20 * share >= 19 * ck * per;
     double line = full ? 6e5 : g.V3h >= 6000 ? 7e5 : 1.3e6;
     if (use == HOP_EVENLY) line = 2e6;
-    if (use == HOP_UNEVENLY || use == HOP_BLOCK) line = 4e5;
+    if (use == HOP_UNEVENLY || use == HOP_BLOCK) line = fits ? 2.4e5 : 4e5;
     if (use == HOP_SOLVE) line = 7e5;
     return W > line && (fits || use >= HOP_BLOCK) ? HOP_MAP_MARCH1 : HOP_MAP_SITE;
   }
@@ -1991,12 +1991,32 @@ template <class R> static void launch_stream(const HopArgs<R>& A, hipStream_t st
 // MB 4.89 / 4.65, at 25 MB 6.00 / 5.69; FP32 CG at 19 MB 4.97 / 4.63, at 25 MB 5.77 / 5.31, at 38 MB
 // 7.53 / 7.06; FP64 CG at 38 MB 7.21 / 7.06, at 50 MB 9.02 / 9.10: the line lies low by up to a half.
 // Launches on some of the blocks march all the same: the linear order gives each XCD a
-// range of slices, which may hold no selected block.
+// range of slices, which may hold no selected block. The full operator on them runs the
+// register-blocked body from some 1e5 sites times rhs: the split kernel's large workgroups take
+// as long to pass over the other blocks as to compute these. Measured (us, register-blocked /
+// split): black blocks, 16^3x32 FP32 2 rhs 12.2 / 16.6, 8 rhs 41.9 / 53.7, 12x24^3 FP64 1 rhs 16.5
+// / 19.8, 16x12^3 (slices of 864 sites) FP64 5 rhs 14.6 / 22.2; one block of 24^3x48 FP32 1 rhs
+// 13.7 / 23.2, 2 rhs 22.6 / 42.7. Not on slices of fewer than 800 sites, whose
+// eighths fill its wavefronts badly (one block of 64x10^3 FP32 2 rhs 9.5 / 6.4), and not one rhs
+// (FP64, where its chunks divide evenly over the XCDs, up to three) on 32 slices or more (black
+// blocks of 24^3x48 FP64 79.8 / 67.6, 16^3x32 FP32 10.0 / 9.8, FP64 2 rhs 28.1 / 27.0) but a single
+// block of a large lattice.
 template <class R> static int march1_order(const HopArgs<R>& A) {
-  const bool full = A.parity_out < 0, f32 = std::is_same<R, float>::value;
-  const double in = 2.0 * A.g.Vh * A.nrhs * 24 * sizeof(R);      // bytes of the whole input field
-  if (!((!full && f32) || in <= (full ? 200e6 : 400e6))) return -1;
-  return A.g.V3h >= 16 * TILE && (full || in > 27e6 || split_partial(A)) ? 1 : 0;
+  const Geo& g = A.g;
+  const bool full = A.parity_out < 0, f32 = std::is_same<R, float>::value, part = split_partial(A);
+  const double W = 2.0 * g.Vh * A.nrhs, in = W * 24 * sizeof(R);      // bytes of the whole input field
+  if (A.map == HOP_MAP_MARCH1_REG) return -1;
+  if (A.map != HOP_MAP_MARCH1_SPLIT) {
+    if (!((!full && f32) || in <= (full ? 200e6 : 400e6))) return -1;
+    const int nslice = (g.V3h + TILE - 1) / TILE;
+    const bool fits = 20 * nslice >= 19 * 8 * ((nslice + 7) / 8);     // an eighth of a slice, in whole chunks
+    const bool long_few = g.L0 >= 32 && A.nrhs <= (f32 || !fits ? 1 : 3) && !(A.block >= 0 && W > 5e5);
+    if (full && part && g.V3h >= 800 && W > (A.block < 0 ? 1.2e5 : A.nrhs > 1 ? 1.35e5 : 1.7e5) && !long_few) return -1;
+  }
+  return g.V3h >= 16 * TILE && (full || in > 27e6 || part) ? 1 : 0;
+}
+template <class R> static bool is_march1(const HopArgs<R>& A) {
+  return A.map == HOP_MAP_MARCH1 || A.map == HOP_MAP_MARCH1_REG || A.map == HOP_MAP_MARCH1_SPLIT;
 }
 template <class R> static void launch_march1(const HopArgs<R>& A, hipStream_t st) {
   const int order = march1_order(A);
@@ -2005,12 +2025,12 @@ template <class R> static void launch_march1(const HopArgs<R>& A, hipStream_t st
 }
 
 template <class R> bool hop_is_split(const HopArgs<R>& A) {
-  return A.map == HOP_MAP_SITE || (A.map == HOP_MAP_MARCH1 && march1_order(A) >= 0);
+  return A.map == HOP_MAP_SITE || (is_march1(A) && march1_order(A) >= 0);
 }
 template bool hop_is_split<double>(const HopArgs<double>&);
 
 template <class R> bool hop_in_ranges(const HopArgs<R>& A) {
-  return !split_partial(A) && (A.map == HOP_MAP_SITE || (A.map == HOP_MAP_MARCH1 && march1_order(A) == 0));
+  return !split_partial(A) && (A.map == HOP_MAP_SITE || (is_march1(A) && march1_order(A) == 0));
 }
 template bool hop_in_ranges<double>(const HopArgs<double>&);
 template bool hop_in_ranges<float>(const HopArgs<float>&);
@@ -2018,7 +2038,7 @@ template bool hop_in_ranges<float>(const HopArgs<float>&);
 template <class R> int hop_red_slots(const HopArgs<R>& A, int nlb) {
   if (A.map == HOP_MAP_SLABD && std::is_same<R, float>::value) return slabd_norm_slots(A.g, nlb);
   if (A.map == HOP_MAP_SITE) return split_chunks(A.g, nlb, false);
-  if (A.map == HOP_MAP_MARCH1 && march1_order(A) >= 0) return split_chunks(A.g, nlb, march1_order(A) == 1);
+  if (is_march1(A) && march1_order(A) >= 0) return split_chunks(A.g, nlb, march1_order(A) == 1);
   return 0;
 }
 template int hop_red_slots<double>(const HopArgs<double>&, int);
@@ -2032,7 +2052,9 @@ template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t st) {
   }
   switch (A.map) {
     case HOP_MAP_SITE: launch_split<R>(A, false, st); return;
-    case HOP_MAP_MARCH1: launch_march1<R>(A, st); return;
+    case HOP_MAP_MARCH1:
+    case HOP_MAP_MARCH1_REG:
+    case HOP_MAP_MARCH1_SPLIT: launch_march1<R>(A, st); return;
     case HOP_MAP_MARCH2: launch_march<R, 2>(A, st); return;
     case HOP_MAP_MARCH4: launch_march<R, 4>(A, st); return;
     case HOP_MAP_WALK1:

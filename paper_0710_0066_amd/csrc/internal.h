@@ -119,7 +119,10 @@ enum { HOP_MAP_SITE = 0,    // split kernel: a site's eight hops on eight wavefr
        HOP_MAP_SLABD = 20,  // even-odd FP32 / FP16 hop only: the slab order with the slice
                             //   and its x1 / x2 halo staged in LDS by direct memory-to-LDS
                             //   loads, 1 rhs per work-item (FP64: as SLAB1)
-       HOP_NMAP = 21 };
+       HOP_NMAP = 21,
+       // MARCH1 (FP32 / FP64) with its kernel fixed, as the autotuner may choose: the register-
+       // blocked or the split one
+       HOP_MAP_MARCH1_REG = 21, HOP_MAP_MARCH1_SPLIT = 22 };
 constexpr int HOP_WALK_T = 8;   // slices per walk
 
 template <class R> void launch_hop(const HopArgs<R>& A, hipStream_t s);
@@ -198,8 +201,10 @@ struct sap_ctx {
   void* solver;   // solver workspace (solver.hip)
   void* forces;   // force / trajectory workspace (hmc.hip)
   void* sapws;    // Schwarz-preconditioned BiCGstab workspace (solver.hip), allocated by sap_create
-  // tuned hop mapping per [full operator?][precision (sap_prec)][nrhs] (-1: not tuned)
+  // tuned or set hop mapping per [full operator?][precision (sap_prec)][nrhs] (-1: neither), and
+  // whether it was tuned
   signed char hop_map[2][3][65];
+  bool hop_tuned[2][3][65];
 };
 
 // largest deviation from SU(3) (|U U^+ - 1| entries, |det U - 1|) sap_set_gauge accepts
@@ -214,10 +219,13 @@ template <class S> constexpr int prec_of() {
 }
 
 // mapping used for a hop launch: the tuned (or set) one, else the rule on the lattice, the
-// precision and the number of rhs
+// precision and the number of rhs. The tuner times launches on every site; the full operator on
+// some of the blocks goes by the rule (24^3x48 in FP32, one block, one rhs: 22.6 us with the
+// mapping tuned for the whole lattice, 13.8 by the rule).
 inline int hop_map_for(const sap_ctx* c, bool full, int prec, int nrhs, int use) {
-  const int m = c->hop_map[full ? 1 : 0][prec][nrhs > 64 ? 64 : nrhs];
-  if (m >= 0) return m;
+  const int n = nrhs > 64 ? 64 : nrhs, m = c->hop_map[full][prec][n];
+  const bool part = full && (use == sap::HOP_EVENLY || use == sap::HOP_UNEVENLY || use == sap::HOP_BLOCK);
+  if (m >= 0 && !(part && c->hop_tuned[full][prec][n])) return m;
   return sap::hop_default_map(c->g, full, prec, nrhs, use);
 }
 
