@@ -476,8 +476,11 @@ static int tune_one(sap_ctx* c, bool full, int nrhs, hipStream_t st, float* us_o
       if (us_out) us_out[m] = -1.0f;
       continue;
     }
-    // MARCH1 has two kernels in FP32 and FP64: the faster one stands for it
-    const bool two = m == HOP_MAP_MARCH1 && !f16;
+    // MARCH1 has two kernels in FP32 and FP64: for the full operator the faster one stands for it.
+    // The half hop leaves the choice to its rule: the register-blocked one adds no reductions, so
+    // that a solve loses more than the hop gains (12x24^3 FP64 1 rhs: hop 18.2 / 18.6 us, series
+    // solve of the blocks 2.56 / 2.41 ms).
+    const bool two = m == HOP_MAP_MARCH1 && !f16 && full;
     float map_ms = 1e30f;
     for (int t = 0; t < (two ? 2 : 1); ++t) {
       A.map = two ? HOP_MAP_MARCH1_REG + t : m;
