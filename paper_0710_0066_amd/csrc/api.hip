@@ -94,6 +94,7 @@ int sap_create(const sap_geom* g, sap_ctx** out) {
   c->sapws = nullptr;
   std::memset(c->hop_map, -1, sizeof(c->hop_map));
   std::memset(c->hop_tuned, 0, sizeof(c->hop_tuned));
+  std::memset(c->hop_solve, -1, sizeof(c->hop_solve));
   if (hipGetDevice(&c->device) != hipSuccess) {
     delete c;
     return sap_fail(nullptr, SAP_E_HIP, "hipGetDevice failed (no HIP device?)");

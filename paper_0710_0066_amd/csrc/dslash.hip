@@ -2028,6 +2028,7 @@ template <class R> bool hop_is_split(const HopArgs<R>& A) {
   return A.map == HOP_MAP_SITE || (is_march1(A) && march1_order(A) >= 0);
 }
 template bool hop_is_split<double>(const HopArgs<double>&);
+template bool hop_is_split<float>(const HopArgs<float>&);
 
 template <class R> bool hop_in_ranges(const HopArgs<R>& A) {
   return !split_partial(A) && (A.map == HOP_MAP_SITE || (is_march1(A) && march1_order(A) == 0));

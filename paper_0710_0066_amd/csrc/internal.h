@@ -201,10 +201,11 @@ struct sap_ctx {
   void* solver;   // solver workspace (solver.hip)
   void* forces;   // force / trajectory workspace (hmc.hip)
   void* sapws;    // Schwarz-preconditioned BiCGstab workspace (solver.hip), allocated by sap_create
-  // tuned or set hop mapping per [full operator?][precision (sap_prec)][nrhs] (-1: neither), and
-  // whether it was tuned
+  // tuned or set hop mapping per [full operator?][precision (sap_prec)][nrhs] (-1: neither),
+  // whether it was tuned, and that of the half hops of a solve
   signed char hop_map[2][3][65];
   bool hop_tuned[2][3][65];
+  signed char hop_solve[3][65];
 };
 
 // largest deviation from SU(3) (|U U^+ - 1| entries, |det U - 1|) sap_set_gauge accepts
@@ -223,7 +224,7 @@ template <class S> constexpr int prec_of() {
 // some of the blocks goes by the rule (24^3x48 in FP32, one block, one rhs: 22.6 us with the
 // mapping tuned for the whole lattice, 13.8 by the rule).
 inline int hop_map_for(const sap_ctx* c, bool full, int prec, int nrhs, int use) {
-  const int n = nrhs > 64 ? 64 : nrhs, m = c->hop_map[full][prec][n];
+  const int n = nrhs > 64 ? 64 : nrhs, m = use == sap::HOP_SOLVE ? c->hop_solve[prec][n] : c->hop_map[full][prec][n];
   const bool part = full && (use == sap::HOP_EVENLY || use == sap::HOP_UNEVENLY || use == sap::HOP_BLOCK);
   if (m >= 0 && !(part && c->hop_tuned[full][prec][n])) return m;
   return sap::hop_default_map(c->g, full, prec, nrhs, use);

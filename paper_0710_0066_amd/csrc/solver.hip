@@ -455,8 +455,8 @@ static int tune_one(sap_ctx* c, bool full, int nrhs, hipStream_t st, float* us_o
   hipEvent_t e0, e1;
   SAP_HIP_CHECK(c, hipEventCreate(&e0));
   SAP_HIP_CHECK(c, hipEventCreate(&e1));
-  int best = HOP_MAP_SITE;
-  float best_ms = 1e30f;
+  int best = HOP_MAP_SITE, solve = HOP_MAP_SITE;
+  float best_ms = 1e30f, solve_ms = 1e30f;
   for (int m = 0; m < HOP_NMAP; ++m) {
     const bool one_rhs_alias = m == HOP_MAP_LANE4 || m == HOP_MAP_WAVE4 ||
                                (m >= HOP_SWEEP && m != HOP_MAP_MARCH1 && m != HOP_MAP_WALK1 &&
@@ -476,11 +476,14 @@ static int tune_one(sap_ctx* c, bool full, int nrhs, hipStream_t st, float* us_o
       if (us_out) us_out[m] = -1.0f;
       continue;
     }
-    // MARCH1 has two kernels in FP32 and FP64: for the full operator the faster one stands for it.
-    // The half hop leaves the choice to its rule: the register-blocked one adds no reductions, so
-    // that a solve loses more than the hop gains (12x24^3 FP64 1 rhs: hop 18.2 / 18.6 us, series
-    // solve of the blocks 2.56 / 2.41 ms).
-    const bool two = m == HOP_MAP_MARCH1 && !f16 && full;
+    // MARCH1 has two kernels in FP32 and FP64, and the faster one stands for it. Solves leave the
+    // choice to its rule: the register-blocked one adds no reductions, so that they lose more than
+    // the hop gains (12x24^3 FP64 1 rhs: hop 18.2 / 18.6 us, series solve of the blocks 2.56 / 2.41 ms).
+    const bool two = m == HOP_MAP_MARCH1 && !f16;
+    A.map = m;
+    int rule = m;
+    if constexpr (!std::is_same<R, h16>::value)
+      if (two) rule = hop_is_split(A) ? HOP_MAP_MARCH1_SPLIT : HOP_MAP_MARCH1_REG;
     float map_ms = 1e30f;
     for (int t = 0; t < (two ? 2 : 1); ++t) {
       A.map = two ? HOP_MAP_MARCH1_REG + t : m;
@@ -496,6 +499,7 @@ static int tune_one(sap_ctx* c, bool full, int nrhs, hipStream_t st, float* us_o
       if (hipGetLastError() != hipSuccess) ms = 1e30f;   // variant not launchable here
       map_ms = std::min(map_ms, ms);
       if (ms < best_ms) { best_ms = ms; best = A.map; }
+      if (A.map == rule && ms < solve_ms) { solve_ms = ms; solve = m; }
     }
     if (us_out) us_out[m] = map_ms * 1e3f;
   }
@@ -503,6 +507,7 @@ static int tune_one(sap_ctx* c, bool full, int nrhs, hipStream_t st, float* us_o
   (void)hipEventDestroy(e1);
   c->hop_map[full ? 1 : 0][prec_of<R>()][nrhs] = (signed char)best;
   c->hop_tuned[full ? 1 : 0][prec_of<R>()][nrhs] = true;
+  if (!full) c->hop_solve[prec_of<R>()][nrhs] = (signed char)solve;
   return SAP_OK;
 }
 
@@ -535,6 +540,7 @@ extern "C" int sap_set_hop_map(sap_ctx* c, int full, sap_prec prec, int nrhs, in
   if (c->solver) drop_graphs(ws_of(c));
   c->hop_map[full ? 1 : 0][prec][nrhs] = (signed char)map;
   c->hop_tuned[full ? 1 : 0][prec][nrhs] = false;
+  if (!full) c->hop_solve[prec][nrhs] = (signed char)map;
   return SAP_OK;
 }
 
