@@ -46,7 +46,7 @@ struct SolverWS {
                                          // (gam, cs and active: two versions)
   int *active, *iters, *flags, *selected;
   // pinned host mirrors
-  double *h_rnorm2, *h_bnorm2;
+  double *h_rnorm2, *h_bnorm2;            // h_bnorm2: then ||b||^2 of each parity, two per system
   int *h_flags, *h_iters, *h_selected;
   // captured inner-loop graphs (ITERS_PER_GRAPH CG iterations each), replayed on the
   // caller's stream; captured on a private non-blocking stream of default priority
@@ -93,7 +93,7 @@ extern "C" int sap_solver_create(sap_ctx* c) {
        A((void**)&w->iters, ns * 4) &&
        A((void**)&w->flags, 16) && A((void**)&w->selected, ns * 4);
   ok = ok && hipHostMalloc((void**)&w->h_rnorm2, ns * 8, 0) == hipSuccess &&
-       hipHostMalloc((void**)&w->h_bnorm2, ns * 8, 0) == hipSuccess &&
+       hipHostMalloc((void**)&w->h_bnorm2, 3 * ns * 8, 0) == hipSuccess &&
        hipHostMalloc((void**)&w->h_flags, 16, 0) == hipSuccess &&
        hipHostMalloc((void**)&w->h_iters, ns * 4, 0) == hipSuccess &&
        hipHostMalloc((void**)&w->h_selected, ns * 4, 0) == hipSuccess;
@@ -219,11 +219,15 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
   SAP_HIP_CHECK(c, hipMemsetAsync(w->iters, 0, nsys * 4, st));
   SAP_HIP_CHECK(c, hipMemsetAsync(x, 0, fullb, st));
 
-  // ||b||^2 per system; first residual r = b
+  // ||b||^2 per system (the first residual), of even-site systems also by parity
   blas_norm2<double>(G, nrhs, B, 2, w->partA, st);
   fin_sum(nsys, {w->partA, n2}, w->bnorm2, st);
-  SAP_HIP_CHECK(c, hipMemcpyAsync(w->rnorm2, w->bnorm2, nsys * 8, hipMemcpyDeviceToDevice, st));
   SAP_HIP_CHECK(c, hipMemcpyAsync(w->h_bnorm2, w->bnorm2, nsys * 8, hipMemcpyDeviceToHost, st));
+  double* const par2 = w->h_bnorm2 + w->max_sys;
+  if (eo_only) {
+    fin_sum(2 * nsys, {w->partA, n1}, w->gam, st);
+    SAP_HIP_CHECK(c, hipMemcpyAsync(par2, w->gam, 2 * nsys * 8, hipMemcpyDeviceToHost, st));
+  }
 
   const double tol = o->tol;
   const double inner_tol = (std::is_same<R, double>::value && o->inner_tol <= 0) ? tol : o->inner_tol;
@@ -231,10 +235,13 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
   int outer = 0;
   int status = SAP_OK;
   for (;;) {
-    SAP_HIP_CHECK(c, hipMemcpyAsync(w->h_rnorm2, w->rnorm2, nsys * 8, hipMemcpyDeviceToHost, st));
+    if (outer) SAP_HIP_CHECK(c, hipMemcpyAsync(w->h_rnorm2, w->rnorm2, nsys * 8, hipMemcpyDeviceToHost, st));
     SAP_HIP_CHECK(c, hipStreamSynchronize(st));
     bool all = true, finite = true;
     for (int s = 0; s < nsys; ++s) {
+      // (a source of the even-site system that does not vanish on the odd sites has no solution)
+      if (!outer) w->h_rnorm2[s] = w->h_bnorm2[s];
+      else if (eo_only) w->h_rnorm2[s] += par2[2 * s + 1];
       if (!w->h_selected[s]) continue;
       const double bb = w->h_bnorm2[s], rr = w->h_rnorm2[s];
       if (!std::isfinite(rr) || !std::isfinite(bb)) finite = false;
@@ -419,7 +426,6 @@ static int solve_impl(sap_ctx* c, double* x, const double* b, int nrhs, int lb, 
   }
   if (info) {
     SAP_HIP_CHECK(c, hipMemcpyAsync(w->h_iters, w->iters, nsys * 4, hipMemcpyDeviceToHost, st));
-    SAP_HIP_CHECK(c, hipMemcpyAsync(w->h_rnorm2, w->rnorm2, nsys * 8, hipMemcpyDeviceToHost, st));
     SAP_HIP_CHECK(c, hipStreamSynchronize(st));
     for (int s = 0; s < nsys; ++s) {
       const double bb = w->h_bnorm2[s];
