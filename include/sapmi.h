@@ -270,16 +270,17 @@ int apply_Dslash_eo(sap_ctx* ctx, void* out, const void* in, int nrhs, int parit
 /* Autotuner of the hop kernel for nrhs right-hand sides (1 <= nrhs <= max_rhs): times each
  * work-item mapping on this context's lattice for the full operator and the even-odd hop
  * in FP64 and FP32, and keeps the fastest for every later call with that nrhs (apply_M,
- * apply_W1_block, apply_Dslash_eo and the solvers). The mappings: 0 site (the eight hops of
+ * apply_W1_block on all blocks, apply_Dslash_eo and the solvers; the blocks of one colour and
+ * single blocks go by the rule of untuned calls). The mappings: 0 site (the eight hops of
  * 64 sites of one rhs on the eight wavefronts of a workgroup; FP16 storage on larger
- * launches: one site and rhs per work-item), 1 lane4 (4 rhs sharing link loads within a wavefront), 2 wave4 (4 rhs on
- * the 4 wavefronts of a workgroup), 3 stream (even-odd hop only: x0-streaming, time
+ * launches: one site and rhs per work-item), 1 lane4 (4 rhs sharing link loads within a
+ * wavefront), 2 wave4 (4 rhs on the 4 wavefronts of a workgroup), 3 stream (even-odd hop only: x0-streaming, time
  * neighbours kept in registers, each input slice staged in LDS), 4..6 = 0..2 with the
  * workgroups rhs-slowest, 7 / 8 reg2 / reg4 (each loaded link applied to 2 / 4 rhs held in
  * registers), 9 / 10 reg2 / reg4 group-slowest, 11 / 12 / 13 march1 / 2 / 4 (regN with
  * each of the 8 XCDs owning 1/8 of every x0 slice and walking the slices in increasing
  * x0; march1 in FP32 and FP64 runs the site kernel in that order while the field fits the
- * MALL), 14 / 15 walk1 / walk2 (even-odd hop: each work-item walks 8 slices at a fixed
+ * MALL, but not the full operator on some of many blocks; the tuner tries both kernels), 14 / 15 walk1 / walk2 (even-odd hop: each work-item walks 8 slices at a fixed
  * spatial site with 1 / 2 rhs, loads every time neighbour once and carries its
  * projection in registers; the full operator runs them as march1 / march2), 16 band1
  * (even-odd hop: each XCD owns a band of x0 slices and each work-item steps through it at
@@ -297,8 +298,8 @@ int apply_Dslash_eo(sap_ctx* ctx, void* out, const void* in, int nrhs, int parit
  * us_out (host, may be NULL): 126 floats, microseconds per launch (-1: not applicable),
  * ordered [full f64, full f32, even-odd f64, even-odd f32, full f16, even-odd f16] x the
  * 21 mappings. Uses the solver
- * workspace; synchronises. Untuned calls choose by the lattice, the precision and nrhs:
- * site or march1 while the fields fit the MALL, the LDS slabs above. */
+ * workspace; synchronises. Untuned calls choose by the lattice, the precision, nrhs and the
+ * selected blocks: site or march1 while the fields fit the MALL, the LDS slabs above. */
 int sap_tune(sap_ctx* ctx, int nrhs, float* us_out, void* stream);
 
 /* Set the hop mapping used for nrhs right-hand sides by hand (map: 0 site, 1 lane4,

@@ -482,15 +482,15 @@ static int tune_one(sap_ctx* c, bool full, int nrhs, hipStream_t st, float* us_o
       if (us_out) us_out[m] = -1.0f;
       continue;
     }
-    // MARCH1 has two kernels in FP32 and FP64, and the faster one stands for it. Solves leave the
-    // choice to its rule: the register-blocked one adds no reductions, so that they lose more than
+    // MARCH1 has two kernels in FP32 and FP64, and both are candidates; us_out has the time of the
+    // one that its rule picks, as a context would run it with the mapping set by hand. Solves
+    // leave the choice to the rule: the register-blocked one adds no reductions, so that they lose more than
     // the hop gains (12x24^3 FP64 1 rhs: hop 18.2 / 18.6 us, series solve of the blocks 2.56 / 2.41 ms).
     const bool two = m == HOP_MAP_MARCH1 && !f16;
     A.map = m;
     int rule = m;
     if constexpr (!std::is_same<R, h16>::value)
       if (two) rule = hop_is_split(A) ? HOP_MAP_MARCH1_SPLIT : HOP_MAP_MARCH1_REG;
-    float map_ms = 1e30f;
     for (int t = 0; t < (two ? 2 : 1); ++t) {
       A.map = two ? HOP_MAP_MARCH1_REG + t : m;
       for (int k = 0; k < 2; ++k) launch_hop<R>(A, st);
@@ -503,11 +503,11 @@ static int tune_one(sap_ctx* c, bool full, int nrhs, hipStream_t st, float* us_o
       SAP_HIP_CHECK(c, hipEventElapsedTime(&ms, e0, e1));
       ms /= reps;
       if (hipGetLastError() != hipSuccess) ms = 1e30f;   // variant not launchable here
-      map_ms = std::min(map_ms, ms);
       if (ms < best_ms) { best_ms = ms; best = A.map; }
-      if (A.map == rule && ms < solve_ms) { solve_ms = ms; solve = m; }
+      if (A.map != rule) continue;
+      if (us_out) us_out[m] = ms * 1e3f;
+      if (ms < solve_ms) { solve_ms = ms; solve = m; }
     }
-    if (us_out) us_out[m] = map_ms * 1e3f;
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
