@@ -1249,7 +1249,7 @@ void hop_slab_kernel(HopArgs<R> A, int TA, int TB) {
 // component magnitude), and the norm. Fused reductions of the values before their
 // rounding to FP16: RED 1: red[0] += ||out||^2 in FP64; RED 3: red[0..2] += Re <out, x>, Im <out,
 // x> (out conjugated), ||out||^2, summed over the site in FP32 and added in FP64 (the kernel is
-// bound by issue: all three in FP64 took 1 to 3% of a BiCGstab solve).
+// bound by issue: all three in FP64 took up to 2% of a BiCGstab solve).
 template <int RED>
 __device__ __forceinline__ void store_out16(const Field<h16>& out, const Field<h16>& x, int r, int p, long long j,
                                             long long Vhp, bool sel, bool g5o, float a, float b,
@@ -1273,7 +1273,6 @@ __device__ __forceinline__ void store_out16(const Field<h16>& out, const Field<h
     }
   }
   float m = 0.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
-  double n2 = 0.0;
 #pragma unroll
   for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
@@ -1288,21 +1287,25 @@ __device__ __forceinline__ void store_out16(const Field<h16>& out, const Field<h
       }
       v[k] = sel ? val : cx<float>{0.0f, 0.0f};
       m = fmaxf(m, fmaxf(fabsf(v[k].r), fabsf(v[k].i)));
-      if (RED == 1) {
-        n2 = fma((double)v[k].r, (double)v[k].r, fma((double)v[k].i, (double)v[k].i, n2));
-        pin(n2);
-      }
       if (RED == 3) s2 = fmaf(v[k].r, v[k].r, fmaf(v[k].i, v[k].i, s2));
       if (RED == 3 && wx) {
         s0 = fmaf(v[k].r, xq[2 * k], fmaf(v[k].i, xq[2 * k + 1], s0));
         s1 = fmaf(v[k].r, xq[2 * k + 1], fmaf(-v[k].i, xq[2 * k], s1));
       }
     }
-  if (RED == 1) red[0] += n2;
   if (RED == 3) {
     red[0] += (double)s0;
     red[1] += (double)s1;
     red[2] += (double)s2;
+  }
+  if (RED == 1) {   // after the maximum: among its operations the sum cost 2 to 4% of a CG solve
+    double n2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      n2 = fma((double)v[k].r, (double)v[k].r, fma((double)v[k].i, (double)v[k].i, n2));
+      pin(n2);
+    }
+    red[0] += n2;
   }
   const float inv = m > 0.0f ? 1.0f / m : 0.0f;
   __half2* ob = out.ptr + r * out.rs + p * out.ps + sidx<h16>(j, 0);
